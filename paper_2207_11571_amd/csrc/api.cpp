@@ -119,6 +119,21 @@ static void host_basis(int P, BasisTab& T) {
             T.Dhat[i * n + j] = (double)(D[j][i] * w[j] / w[i]);
         }
     }
+    // parity halves
+    const int H = n / 2, M = (n + 1) / 2;
+    auto dhat = [&](int i, int m) { return D[m][i] * w[m] / w[i]; };
+    for (int i = 0; i < M; ++i) {
+        const int ii = n - 1 - i;
+        T.lS[i] = (double)(0.5L * (bp[i] / w[i] + bp[ii] / w[ii]));
+        T.lT[i] = (double)(0.5L * (bp[i] / w[i] - bp[ii] / w[ii]));
+        T.iE[i] = (double)(i == ii ? bp[i] : 0.5L * (bp[i] + bp[ii]));
+        T.iO[i] = (double)(0.5L * (bp[i] - bp[ii]));
+        for (int m = 0; m < M; ++m) {
+            const int mm = n - 1 - m;
+            if (m < H) T.nS[i * H + m] = (double)(-0.5L * (dhat(i, m) - dhat(i, mm)));
+            if (i < H) T.nT[i * M + m] = (double)(m == mm ? -dhat(i, m) : -0.5L * (dhat(i, m) + dhat(i, mm)));
+        }
+    }
 }
 
 // 1D filter G1[a][j] from P_src to P_dst nodes (Sec. 2: nodal -> modal -> truncate -> nodal)
@@ -181,7 +196,6 @@ WsLayout ws_layout(const Mesh& m) {
     WsLayout L;
     size_t off = 0;
     const size_t E = (size_t)m.E;
-    L.desc = off;     off += align256(4 * sizeof(SolveDesc));
     L.qtr0 = off;     off += align256(E * 6 * 5 * m.n_f * sizeof(double));
     L.qtr1 = off;     off += align256(E * 6 * 5 * m.n_f * sizeof(double));
     L.fv = off;       off += align256(E * 6 * 4 * m.n_f * sizeof(double));
@@ -230,13 +244,6 @@ DescList single_list(const SolveDesc* d, int E) {
     return dl;
 }
 
-DescList single_list(const SolveDesc* d, const SolveDesc& host, int E) {
-    DescList dl = single_list(d, E);
-    dl.inl = 1;
-    dl.d0 = host;
-    return dl;
-}
-
 // ----------------------------------------------------------------- internal API used by server/nn
 
 int residual_impl(const Mesh& m, const double* q, double* dqdt, char* ws, hipStream_t st) {
@@ -246,12 +253,9 @@ int residual_impl(const Mesh& m, const double* q, double* dqdt, char* ws, hipStr
     d.out = dqdt;
     d.qtr_in = (const double*)(ws + L.qtr0);
     d.qtr_out = (double*)(ws + L.qtr0);
-    SolveDesc* dd = (SolveDesc*)(ws + L.desc);
-    DG_HIP(launch_write_descs(&d, 1, dd, st));
-    const DescList dl = single_list(dd, d, m.E);
-    DG_HIP(launch_traces(m.PP, dl, st));
-    if (m.ph.viscous) DG_HIP(launch_grad(m.PP, dl, st));
-    DG_HIP(launch_resid(m.PP, 0, dl, 0.0, 0.0, 1, st));
+    DG_HIP(launch_traces(m.PP, d, st));
+    if (m.ph.viscous) DG_HIP(launch_grad(m.PP, d, st));
+    DG_HIP(launch_resid(m.PP, 0, d, 0.0, 0.0, 1, st));
     return DG_OK;
 }
 
@@ -275,11 +279,7 @@ int rk_impl(const Mesh& m, double* q, double* k, double dt, int n_steps, const n
         d[p].qtr_in = (const double*)(ws + (par == 0 ? L.qtr0 : L.qtr1));
         d[p].qtr_out = (double*)(ws + (par == 0 ? L.qtr1 : L.qtr0));
     }
-    SolveDesc* dd = (SolveDesc*)(ws + L.desc);
-    DG_HIP(launch_write_descs(d, 4, dd, st));
-    DescList dl[4];
-    for (int p = 0; p < 4; ++p) dl[p] = single_list(dd + p, d[p], m.E);
-    DG_HIP(launch_traces(m.PP, dl[1], st));   // traces of q into qtr0
+    DG_HIP(launch_traces(m.PP, d[1], st));   // traces of q into qtr0
     // P = 3 on a mesh that fills the GPU with 16-element blocks: the BR1
     // pass and the network in one launch, at every stage (Eq. (4)) or, for
     // the post-step correction (Algorithm 1), at the first stage, whose BR1
@@ -293,7 +293,7 @@ int rk_impl(const Mesh& m, double* q, double* k, double dt, int n_steps, const n
             if (rc != DG_OK) return rc;
         }
         for (int s = 0; s < 3; ++s) {
-            const DescList& l = dl[(post && model && s == 2 ? 2 : 0) + par];
+            const SolveDesc& l = d[(post && model && s == 2 ? 2 : 0) + par];
             if (fused && (!post || s == 0)) {
                 int rc = grad_net_impl(model, m, l, q, (double*)(ws + L.forcing), st);
                 if (rc != DG_OK) return rc;
@@ -483,9 +483,6 @@ int dg_profile_steps(const dg_mesh* mh, double* q, double* k, double dt, int32_t
         d[p].qtr_in = (const double*)(ws + (p == 0 ? L.qtr0 : L.qtr1));
         d[p].qtr_out = (double*)(ws + (p == 0 ? L.qtr1 : L.qtr0));
     }
-    SolveDesc* dd = (SolveDesc*)(ws + L.desc);
-    DG_HIP(launch_write_descs(d, 2, dd, st));
-    const DescList dl[2] = {single_list(dd, d[0], m.E), single_list(dd + 1, d[1], m.E)};
     const int n_ev = 2 * (1 + 9 * n_steps);
     std::vector<hipEvent_t> ev(n_ev);
     for (auto& e : ev) DG_HIP(hipEventCreate(&e));
@@ -497,7 +494,7 @@ int dg_profile_steps(const dg_mesh* mh, double* q, double* k, double dt, int32_t
     };
     int err = DG_OK;
     do {
-        if (mark(0) != hipSuccess || launch_traces(m.PP, dl[1], st) != hipSuccess || hipEventRecord(ev[ie++], st) != hipSuccess) {
+        if (mark(0) != hipSuccess || launch_traces(m.PP, d[1], st) != hipSuccess || hipEventRecord(ev[ie++], st) != hipSuccess) {
             err = set_error(DG_EHIP, "trace launch failed");
             break;
         }
@@ -508,11 +505,11 @@ int dg_profile_steps(const dg_mesh* mh, double* q, double* k, double dt, int32_t
                 if (fused) {
                     // the fused BR1-and-network launch, timed as the network's
                     if (mark(2) != hipSuccess) err = set_error(DG_EHIP, "event failed");
-                    else if ((err = grad_net_impl(model, m, dl[par], q, (double*)(ws + L.forcing), st)) == DG_OK &&
+                    else if ((err = grad_net_impl(model, m, d[par], q, (double*)(ws + L.forcing), st)) == DG_OK &&
                              hipEventRecord(ev[ie++], st) != hipSuccess)
                         err = set_error(DG_EHIP, "event failed");
                 } else if (m.ph.viscous) {
-                    if (mark(1) != hipSuccess || launch_grad(m.PP, dl[par], st) != hipSuccess ||
+                    if (mark(1) != hipSuccess || launch_grad(m.PP, d[par], st) != hipSuccess ||
                         hipEventRecord(ev[ie++], st) != hipSuccess)
                         err = set_error(DG_EHIP, "grad launch failed");
                 }
@@ -523,7 +520,7 @@ int dg_profile_steps(const dg_mesh* mh, double* q, double* k, double dt, int32_t
                         err = set_error(DG_EHIP, "event failed");
                 }
                 if (err == DG_OK && (mark(3) != hipSuccess ||
-                                     launch_resid(m.PP, 1, dl[par], kRkA[s], kRkB[s], s == 0, st) != hipSuccess ||
+                                     launch_resid(m.PP, 1, d[par], kRkA[s], kRkB[s], s == 0, st) != hipSuccess ||
                                      hipEventRecord(ev[ie++], st) != hipSuccess))
                     err = set_error(DG_EHIP, "resid launch failed");
                 par ^= 1;

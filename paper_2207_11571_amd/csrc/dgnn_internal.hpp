@@ -13,6 +13,7 @@
 namespace dgnn {
 
 constexpr int kMaxPP = DG_MAX_ORDER + 1;   // nodes per direction at the highest order
+constexpr int kMaxHalf = (kMaxPP + 1) / 2;   // of them, up to and with the middle one
 constexpr int kMaxLayers = 8;               // weight layers of the forcing network
 constexpr int kMaxDevices = 64;             // GPUs a process can build meshes on
 
@@ -34,6 +35,16 @@ struct BasisTab {
     double dface[2][kMaxPP];
     double lface_p[2];
     double lface_m[2];
+    // The same operators split by parity about the middle of the line (the
+    // nodes are symmetric), for lines held in registers: with H = PP / 2
+    // pairs, M = (PP + 1) / 2, mirrored index i' = P - i,
+    //   nS[i*H + m] = -(Dhat[i][m] - Dhat[i][m']) / 2,  nT[i*M + m] = -(Dhat[i][m] + Dhat[i][m']) / 2
+    // (-Dhat[i][m] at the middle m), lS[i] = (bpw[i] + bpw[i']) / 2, lT[i] = (bpw[i] - bpw[i']) / 2
+    // (lS = bpw at the middle i), iE[m] = (bp[m] + bp[m']) / 2 (bp at the middle), iO[m] = (bp[m] - bp[m']) / 2
+    double nS[kMaxHalf * (kMaxHalf - 1)];
+    double nT[kMaxHalf * (kMaxHalf - 1)];
+    double lS[kMaxHalf], lT[kMaxHalf];
+    double iE[kMaxHalf], iO[kMaxHalf];
 };
 
 // Per-solve physical constants, in the form the kernels use them.
@@ -58,27 +69,21 @@ struct SolveDesc {
     const double* forcing;  // s(q) [5][E][n_p] added to the residual, or null
     const double* post;     // update mode: q += dt post after the stage update
                             // (a post-step correction), or null
-    const double* qtr_in;   // face traces of q   [E][6][5][n_f]
+    const double* qtr_in;   // face traces of q   [E][6][5][n_f], in the frame of the face
     double* qtr_out;        // face traces of the updated q (update mode)
-    double* fv;             // one-sided viscous normal fluxes [E][6][4][n_f]
+    double* fv;             // one-sided viscous normal fluxes [E][6][4][n_f], likewise
     int N, E;
     double dt;
     Phys ph;
 };
 
 // The solves one stage launch works on (by value, in the kernel arguments):
-// blocks [blk[i], blk[i+1]) work on *d[i], one element per block.
+// elements [blk[i], blk[i+1]) are *d[i]'s.
 constexpr int kMaxDescs = 32;
 struct DescList {
     const SolveDesc* d[kMaxDescs];
     int blk[kMaxDescs + 1];
     int n;
-    // one solve whose descriptor the host also has: a copy travels in the
-    // kernel arguments (inl = 1), so the stage kernels read its fields
-    // there instead of through the pointer (two dependent loads fewer
-    // before a block's first data load)
-    int inl;
-    SolveDesc d0;
 };
 
 // Forcing-network description passed by value to the network kernels.
@@ -127,7 +132,7 @@ namespace dgnn {
 
 // workspace layout of one mesh, in bytes from the workspace base
 struct WsLayout {
-    size_t desc, qtr0, qtr1, fv, forcing, partial, total;
+    size_t qtr0, qtr1, fv, forcing, partial, total;
 };
 WsLayout ws_layout(const Mesh& m);
 
@@ -141,16 +146,20 @@ hipError_t upload_basis_tables(const BasisTab* host_tabs /* index P-1 */);
 hipError_t scratch_setup(int dev);
 void* scratch_device_ptr(int dev);
 hipError_t launch_write_descs(const SolveDesc* host, int n, SolveDesc* dev, hipStream_t st);
+hipError_t launch_traces(int PP, const SolveDesc& S, hipStream_t st);
 hipError_t launch_traces(int PP, const DescList& dl, hipStream_t st);
 // compute units of the current device
 int cu_count();
+hipError_t launch_grad(int PP, const SolveDesc& S, hipStream_t st);
 hipError_t launch_grad(int PP, const DescList& dl, hipStream_t st);
 // k_grad and the forcing network in one launch (P = 3, one solve, E a
 // multiple of 16, the network reading all n_p nodes of its variables);
 // hipErrorInvalidValue otherwise
-hipError_t launch_grad_net(int PP, const DescList& dl, const NetArgs& na, const NetTarget& T, hipStream_t st);
-hipError_t launch_resid(int PP, int update, const DescList& dl, double rkA, double rkB, int first_stage,
+hipError_t launch_grad_net(int PP, const SolveDesc& S, const NetArgs& na, const NetTarget& T, hipStream_t st);
+hipError_t launch_resid(int PP, int update, const SolveDesc& S, double rkA, double rkB, int first_stage,
                         hipStream_t st);
+// the stage update of a list of solves, all viscous
+hipError_t launch_resid(int PP, const DescList& dl, double rkA, double rkB, int first_stage, hipStream_t st);
 hipError_t launch_tgv(int PP, const Phys& ph, int N, double* q, hipStream_t st);
 hipError_t launch_diag(int PP, const Phys& ph, int N, const double* q, double* partial,
                        double* out, hipStream_t st);
@@ -238,8 +247,6 @@ extern const double kRkA[3];
 extern const double kRkB[3];
 int make_mesh(const dg_params* prm, Mesh& M);
 DescList single_list(const SolveDesc* d, int E);
-// the same with the host's copy of the descriptor carried along
-DescList single_list(const SolveDesc* d, const SolveDesc& host, int E);
 int residual_impl(const Mesh& m, const double* q, double* dqdt, char* ws, hipStream_t st);
 int diag_impl(const Mesh& m, const double* q, double* out_dev, char* ws, hipStream_t st);
 int project_impl(const Mesh& src, const Mesh& dst, const double* f_src, double* f_dst, hipStream_t st);

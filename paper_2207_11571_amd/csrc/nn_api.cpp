@@ -107,7 +107,7 @@ bool grad_net_fusable(const nn_model* m, const Mesh& mesh) {
            mesh.E / net_rows_per_block() >= cu_count() && m->dims[0] == m->n_in * mesh.n_p;
 }
 
-int grad_net_impl(const nn_model* m, const Mesh& mesh, const DescList& dl, const double* q, double* out,
+int grad_net_impl(const nn_model* m, const Mesh& mesh, const SolveDesc& S, const double* q, double* out,
                   hipStream_t st) {
     const NetArgs na = net_args(m);
     NetTarget tg;
@@ -115,7 +115,7 @@ int grad_net_impl(const nn_model* m, const Mesh& mesh, const DescList& dl, const
     tg.out = out;
     tg.E = mesh.E;
     tg.blk_begin = 0;
-    NN_HIP(launch_grad_net(mesh.PP, dl, na, tg, st));
+    NN_HIP(launch_grad_net(mesh.PP, S, na, tg, st));
     return DG_OK;
 }
 

@@ -42,8 +42,8 @@ int net_forcing_batch(const nn_model* m, int n_p, const NetTarget* targets, int 
 // whether the stage's BR1 pass and the network (write mode, out = s(q)) can
 // run as one launch (launch_grad_net) on this mesh
 bool grad_net_fusable(const nn_model* m, const Mesh& mesh);
-// the BR1 pass of the stage described by dl and out = s(q) in one launch
-int grad_net_impl(const nn_model* m, const Mesh& mesh, const DescList& dl, const double* q, double* out,
+// the BR1 pass of the stage described by S and out = s(q) in one launch
+int grad_net_impl(const nn_model* m, const Mesh& mesh, const SolveDesc& S, const double* q, double* out,
                   hipStream_t st);
 
 }  // namespace dgnn

@@ -308,7 +308,7 @@ static int step_group(solve_server* S, int PP, std::vector<Solve*>& v, hipStream
                 int rc = net_forcing_batch(nt.first, PP * PP * PP, nt.second.data(), (int)nt.second.size(), st);
                 if (rc) return rc;
             }
-            if (launch_resid(PP, 1, dl, kRkA[stg], kRkB[stg], stg == 0, st) != hipSuccess)
+            if (launch_resid(PP, dl, kRkA[stg], kRkB[stg], stg == 0, st) != hipSuccess)
                 return set_error(DG_EHIP, "resid launch failed");
         }
         for (Solve* s : v) s->par ^= 1;

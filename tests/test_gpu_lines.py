@@ -1,0 +1,71 @@
+"""GPU tests of the line kernels' edges: groups of several small elements that
+the mesh does not fill, every order with and without viscous fluxes and the
+closure, and lists of solves of different sizes in one launch.
+
+Tolerance of the parity checks: float64 on both sides, summation order only --
+1e-12 relative L2 per variable, as for the other residual and step checks.
+"""
+import numpy as np
+import pytest
+
+import synthetic
+from helpers import field_parity, say
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module")
+def B():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2207_11571_amd import binding
+    binding.lib()
+    return binding
+
+
+# P = 1: groups of five elements (8 = 5 + 3, 1); P = 2: of two (27, 1)
+@pytest.mark.parametrize("N,P", [(2, 1), (1, 1), (3, 2), (1, 2), (2, 3), (2, 4), (2, 5), (2, 6), (2, 7), (2, 8)])
+@pytest.mark.parametrize("Cs,viscous", [(0.0, True), (0.1, True), (0.0, False)])
+def test_stage_kernels(B, N, P, Cs, viscous):
+    """Residual and two Runge-Kutta steps against the oracle."""
+    from oracle import dg, rk
+    say("stage kernels", N, P, Cs, viscous)
+    prm = dg.Params(N=N, P=P, Re=100.0, Cs=Cs, viscous=viscous)
+    q0 = synthetic.random_state(N, P, seed=40 + P, momentum=0.3)
+    m = B.Mesh(N, P, 100.0, Cs=Cs, viscous=viscous)
+    q = torch.from_numpy(q0).cuda()
+    k = m.field(float("nan"))   # contents on entry are ignored
+    out = m.field(0.0)
+    B.dg_residual(m, q, out)
+    dt = 0.2 * dg.stable_dt(dg.to_blocks(q0, N, P), prm)
+    B.dg_rk_step(m, q, k, dt, 2)
+    torch.cuda.synchronize()
+    ref = dg.to_flat(dg.residual(dg.to_blocks(q0, N, P), prm))
+    l2, li = field_parity(out.cpu().numpy(), ref, 1e-12)
+    assert np.all(l2 < 1e-12) and np.all(li < 1e-11), (l2, li)
+    ref = dg.to_flat(rk.integrate(dg.to_blocks(q0, N, P), dt, 2, lambda s, t: dg.residual(s, prm)))
+    l2, li = field_parity(q.cpu().numpy(), ref, 1e-12)
+    assert np.all(l2 < 1e-12) and np.all(li < 1e-11), (l2, li)
+
+
+@pytest.mark.parametrize("P", [1, 2, 4, 5, 7])
+def test_list_of_solves(B, P):
+    """Solves of one order, different meshes and closures, batched by the
+    server: each ends bitwise in the library's own stepping of it."""
+    say("list of solves", P)
+    reqs = [dict(Re=200.0, N=3, Cs=0.0), dict(Re=30.0, N=2, Cs=0.1), dict(Re=1600.0, N=1, Cs=0.0)]
+    srv = B.Server(64 << 20, max_slots=8)
+    t_end = 0.02 if P < 4 else 0.005
+    ids = [srv.submit(Re=r["Re"], P=P, N=r["N"], t_end=t_end, Cs=r["Cs"], want_state=True) for r in reqs]
+    srv.drain()
+    for rid, r in zip(ids, reqs):
+        _, st = srv.poll(rid)
+        assert st.state == B.SOLVE_DONE, st.error
+        m = B.Mesh(r["N"], P, r["Re"], Cs=r["Cs"])
+        q, k = m.field(), m.field(0.0)
+        B.dg_init_tgv(m, q)
+        B.dg_rk_step(m, q, k, st.dt, st.n_steps)
+        torch.cuda.synchronize()
+        assert np.array_equal(q.cpu().numpy().ravel(), srv.results(rid)[1])
+    srv.close()
