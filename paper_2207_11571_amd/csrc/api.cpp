@@ -280,11 +280,11 @@ int rk_impl(const Mesh& m, double* q, double* k, double dt, int n_steps, const n
         d[p].qtr_out = (double*)(ws + (par == 0 ? L.qtr1 : L.qtr0));
     }
     DG_HIP(launch_traces(m.PP, d[1], st));   // traces of q into qtr0
-    // P = 3 on a mesh that fills the GPU with 16-element blocks: the BR1
-    // pass and the network in one launch, at every stage (Eq. (4)) or, for
-    // the post-step correction (Algorithm 1), at the first stage, whose BR1
-    // pass reads the same state q^n the network is evaluated on
-    const bool fused = model && grad_net_fusable(model, m);
+    // P = 3: the BR1 pass and the network in one launch where that pays, at
+    // every stage (Eq. (4)) or, for the post-step correction (Algorithm 1), at
+    // the first stage, whose BR1 pass reads the same state q^n the network is
+    // evaluated on
+    const bool fused = grad_net_form(model, m) != kGradNetApart;
     int par = 0;
     for (int n = 0; n < n_steps; ++n) {
         // post-step correction (Algorithm 1): s from the state at the start of the step
@@ -498,7 +498,7 @@ int dg_profile_steps(const dg_mesh* mh, double* q, double* k, double dt, int32_t
             err = set_error(DG_EHIP, "trace launch failed");
             break;
         }
-        const bool fused = model && grad_net_fusable(model, m);
+        const bool fused = grad_net_form(model, m) == kGradNetFused;
         int par = 0;
         for (int n = 0; n < n_steps && err == DG_OK; ++n)
             for (int s = 0; s < 3 && err == DG_OK; ++s) {

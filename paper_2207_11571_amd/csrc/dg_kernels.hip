@@ -117,16 +117,14 @@ __global__ void __launch_bounds__(Line<PP>::NT) __attribute__((amdgpu_waves_per_
 // same block.  The same device code as k_grad and k_net_forcing, so the same
 // numbers.  One solve per launch (its descriptor in the kernel arguments),
 // E a multiple of 16.
-template <int PP>
+template <int PP, int K0, int ACT>
 __global__ void __launch_bounds__(kRowThreads) k_grad_net(SolveDesc S, NetArgs na, NetTarget T) {
     using L = Line<PP>;
     static_assert(L::NT == 64 && L::NP == 64 && L::EPG == 1, "one element per wavefront, one node per lane");
     constexpr int NP = L::NP;
     extern __shared__ __attribute__((aligned(16))) double gsm[];
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    int pmax = 0;
-    for (int l = 0; l <= na.n_layers; ++l) pmax = pmax > na.pdims[l] ? pmax : na.pdims[l];
-    const int ld = pmax + kLdPad;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int ld = na.ld;
     uint16_t* bufA = (uint16_t*)(gsm + kRowWaves * GradLds<PP>::N);
     uint16_t* bufB = bufA + kRows * ld;
     const int e0 = blockIdx.x * kRows;
@@ -134,6 +132,8 @@ __global__ void __launch_bounds__(kRowThreads) k_grad_net(SolveDesc S, NetArgs n
     double q[1][5];
     grad_group<PP>(S, __builtin_amdgcn_readfirstlane(e0 + wave), lane, gsm + wave * GradLds<PP>::N, q);
 
+    FirstTile<K0 ? K0 : 1> first;
+    if constexpr (K0 > 0) first.load(na, wave, lane);
     // row `wave` of the network input: column j NP + n is node n of
     // variable in_var[j]
     const int din = na.dims[0], pin = na.pdims[0];
@@ -141,12 +141,40 @@ __global__ void __launch_bounds__(kRowThreads) k_grad_net(SolveDesc S, NetArgs n
     for (int j = 0; j < na.n_in; ++j) {
         const int v = na.in_var[j];
         const double qv = v == 0 ? q[0][0] : (v == 1 ? q[0][1] : (v == 2 ? q[0][2] : (v == 3 ? q[0][3] : q[0][4])));
-        row[j * NP + lane] = f2bf(net_input(na, NP, v, lane, qv));
+        row[j * NP + lane] = f2bf(net_input(na, NP, j, lane, qv));
     }
     for (int c = din + lane; c < pin; c += 64) row[c] = f2bf(0.0f);
     net_zero_unforced(na, NP, T, e0, threadIdx.x);
     __syncthreads();
-    net_block_forward(na, NP, T, e0, 0, bufA, bufB, ld, wave, lane);
+    if constexpr (K0 > 0) net256_forward<K0, ACT>(na, NP, T, e0, 0, bufA, bufB, ld, wave, lane, first);
+    else net_block_forward(na, NP, T, e0, 0, bufA, bufB, ld, wave, lane);
+}
+
+// The same two on a mesh that does not fill the GPU with such blocks: the
+// first blocks do the network of sixteen elements each, the others the BR1
+// pass of sixteen elements, side by side on different CUs in one launch
+// (512 elements: 12.3 us, against 12.3 us for the network and 4.0 us for the
+// BR1 pass).
+template <int PP, int K0, int ACT>
+__global__ void __launch_bounds__(kRowThreads) k_grad_beside_net(SolveDesc S, NetArgs na, NetTarget T, int net_blocks) {
+    using L = Line<PP>;
+    static_assert(L::NT == 64 && L::EPG == 1, "one element per wavefront");
+    extern __shared__ __attribute__((aligned(16))) double gsm[];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    if ((int)blockIdx.x >= net_blocks) {
+        const int e = ((int)blockIdx.x - net_blocks) * kRowWaves + wave;
+        double q[1][5];
+        if (e < S.E) grad_group<PP>(S, e, lane, gsm + wave * GradLds<PP>::N, q);
+        return;
+    }
+    const int ld = na.ld, e0 = blockIdx.x * kRows;
+    uint16_t* bufA = (uint16_t*)gsm;
+    uint16_t* bufB = bufA + kRows * ld;
+    FirstTile<K0> first;
+    net_gather<K0>(na, L::NP, T, e0, bufA, ld, wave, lane, first);
+    net_zero_unforced(na, L::NP, T, e0, threadIdx.x);
+    __syncthreads();
+    net256_forward<K0, ACT>(na, L::NP, T, e0, 0, bufA, bufB, ld, wave, lane, first);
 }
 
 template <int PP, int UPDATE, int VISC>
@@ -487,28 +515,63 @@ int cu_count() {
     return cus[dev];
 }
 
-hipError_t launch_grad_net(int PPv, const SolveDesc& S, const NetArgs& na, const NetTarget& T, hipStream_t st) {
-    if (PPv != 4 || T.E % kRows != 0 || na.dims[0] != na.n_in * 64) return hipErrorInvalidValue;
-    int pmax = 0;
-    for (int l = 0; l <= na.n_layers; ++l) pmax = pmax > na.pdims[l] ? pmax : na.pdims[l];
-    const size_t smem = (size_t)kRowWaves * GradLds<4>::N * sizeof(double) +
-                        (size_t)2 * kRows * (pmax + kLdPad) * sizeof(uint16_t);
-    // the dynamic LDS limit, raised once per device to the largest size asked
+// the dynamic LDS limit of a kernel, raised once per device to the largest
+// size asked; `slot` names the kernel
+constexpr int kNetKernels = 9;
+static hipError_t allow_lds(const void* kernel, int slot, size_t smem) {
     static std::mutex mu;
-    static size_t set_for[kMaxDevices] = {};
+    static size_t set_for[kNetKernels][kMaxDevices] = {};
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return e;
     if (dev < 0 || dev >= kMaxDevices) return hipErrorInvalidDevice;
-    {
-        std::lock_guard<std::mutex> lk(mu);
-        if (set_for[dev] < smem) {
-            e = hipFuncSetAttribute((const void*)k_grad_net<4>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
-            if (e != hipSuccess) return e;
-            set_for[dev] = smem;
-        }
+    std::lock_guard<std::mutex> lk(mu);
+    if (set_for[slot][dev] < smem) {
+        e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+        if (e != hipSuccess) return e;
+        set_for[slot][dev] = smem;
     }
-    hipLaunchKernelGGL(k_grad_net<4>, dim3(T.E / kRows), dim3(kRowThreads), smem, st, S, na, T);
+    return hipSuccess;
+}
+
+// Two corrected steps of 8^3 elements take 130 us apart, 114 us beside; 16^3
+// elements fill every CU with one fused block (one step 118 us).  In between,
+// blocks of both kinds would take more than one round of the CUs.
+GradNetForm grad_net_form(const NetArgs& na, int E) {
+    if (E % kRows == 0 && E / kRows >= cu_count()) return kGradNetFused;
+    const int k0 = net256_steps(na);
+    const int blocks = (E + kRows - 1) / kRows;
+    return (k0 == 6 || k0 == 10) && 2 * blocks <= cu_count() ? kGradNetBeside : kGradNetApart;
+}
+
+hipError_t launch_grad_net(int PPv, const SolveDesc& S, const NetArgs& na, const NetTarget& T, hipStream_t st) {
+    const GradNetForm form = grad_net_form(na, T.E);
+    if (PPv != 4 || form == kGradNetApart || na.dims[0] != na.n_in * 64) return hipErrorInvalidValue;
+    const size_t rows = (size_t)2 * kRows * na.ld * sizeof(uint16_t);
+    const size_t grad = (size_t)kRowWaves * GradLds<4>::N * sizeof(double);
+    const int k0 = net256_steps(na);
+    const int nw = k0 == 10 ? (na.act ? 1 : 2) : (k0 == 6 ? (na.act ? 3 : 4) : 0);
+    if (form == kGradNetBeside) {
+        const size_t smem = rows > grad ? rows : grad;
+        const auto kernel = nw == 1   ? k_grad_beside_net<4, 10, 1>
+                            : nw == 2 ? k_grad_beside_net<4, 10, 0>
+                            : nw == 3 ? k_grad_beside_net<4, 6, 1>
+                                      : k_grad_beside_net<4, 6, 0>;
+        const hipError_t e = allow_lds((const void*)kernel, 4 + nw, smem);
+        if (e != hipSuccess) return e;
+        const int blocks = (T.E + kRows - 1) / kRows;
+        hipLaunchKernelGGL(kernel, dim3(2 * blocks), dim3(kRowThreads), smem, st, S, na, T, blocks);
+        return hipGetLastError();
+    }
+    const size_t smem = grad + rows;
+    const auto kernel = nw == 1   ? k_grad_net<4, 10, 1>
+                        : nw == 2 ? k_grad_net<4, 10, 0>
+                        : nw == 3 ? k_grad_net<4, 6, 1>
+                        : nw == 4 ? k_grad_net<4, 6, 0>
+                                  : k_grad_net<4, 0, 0>;
+    const hipError_t e = allow_lds((const void*)kernel, nw, smem);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(kernel, dim3(T.E / kRows), dim3(kRowThreads), smem, st, S, na, T);
     return hipGetLastError();
 }
 

@@ -96,10 +96,15 @@ struct NetArgs {
     const uint16_t* WT[kMaxLayers];  // bf16 [pdims[l]][pdims[l+1]], zero padded
     const float* b[kMaxLayers];      // float32 [dims[l+1]]
     double mu_in[5], sig_in[5], mu_out[5], sig_out[5], mask[5];
+    // per input variable j: mean and 1 / sigma (per-variable normalisation)
+    double in_mu[5], in_isig[5];
+    // per output variable: s = out_scale[j] yhat + out_shift[j] (mask applied)
+    double out_scale[5], out_shift[5];
     // the network reads variables in_var[0..n_in) (input column j n_p + n is
     // node n of variable in_var[j]) and forces out_var[0..n_out) likewise
     int n_in, n_out;
     int in_var[5], out_var[5];
+    int ld;                          // row length of activations in LDS: widest layer, padded
     // per-node normalisation (null: per variable): device [4][5 col_np] doubles,
     // mu_in, sigma_in, mu_out, sigma_out of row column v col_np + n
     const double* col;
@@ -152,9 +157,15 @@ hipError_t launch_traces(int PP, const DescList& dl, hipStream_t st);
 int cu_count();
 hipError_t launch_grad(int PP, const SolveDesc& S, hipStream_t st);
 hipError_t launch_grad(int PP, const DescList& dl, hipStream_t st);
-// k_grad and the forcing network in one launch (P = 3, one solve, E a
-// multiple of 16, the network reading all n_p nodes of its variables);
-// hipErrorInvalidValue otherwise
+// How the BR1 pass and the forcing network of a P = 3 stage run on E elements:
+// in one block per sixteen elements where those fill the GPU (one per CU),
+// side by side in one launch where both together leave CUs free, else in two
+// launches.
+enum GradNetForm { kGradNetApart, kGradNetBeside, kGradNetFused };
+GradNetForm grad_net_form(const NetArgs& na, int E);
+// k_grad and the forcing network in one launch (P = 3, one solve, the network
+// reading all n_p nodes of its variables); hipErrorInvalidValue where the form
+// is apart
 hipError_t launch_grad_net(int PP, const SolveDesc& S, const NetArgs& na, const NetTarget& T, hipStream_t st);
 hipError_t launch_resid(int PP, int update, const SolveDesc& S, double rkA, double rkB, int first_stage,
                         hipStream_t st);
@@ -178,6 +189,7 @@ hipError_t launch_net_refresh_layer(const NetArgs& na, const float* params, int6
                                     uint16_t* wbf, int64_t wbf_off, int64_t wtbf_off, hipStream_t st);
 hipError_t launch_fill_f32(float* p, float v, size_t n, hipStream_t st);
 int net_rows_per_block();
+int net_row_pad();
 
 // training: per-row-block forward / loss / backward data chain, then the
 // weight-gradient products reduced over the batch, then Adam

@@ -65,7 +65,15 @@ NetArgs net_args(const nn_model* m) {
         na.mask[v] = m->mask[v];
         na.in_var[v] = m->in_var[v];
         na.out_var[v] = m->out_var[v];
+        na.in_mu[v] = m->norm[m->in_var[v]];
+        na.in_isig[v] = 1.0 / m->norm[5 + m->in_var[v]];
+        const int o = m->out_var[v];
+        na.out_scale[v] = m->mask[o] * m->norm[15 + o];
+        na.out_shift[v] = m->mask[o] * m->norm[10 + o];
     }
+    int pmax = 0;
+    for (int l = 0; l <= m->n_layers; ++l) pmax = pmax > m->pdims[l] ? pmax : m->pdims[l];
+    na.ld = pmax + net_row_pad();
     na.n_in = m->n_in;
     na.n_out = m->n_out;
     na.col = m->col_norm;
@@ -99,12 +107,9 @@ int net_forcing_impl(const nn_model* m, const Mesh& mesh, const double* q, doubl
     return DG_OK;
 }
 
-bool grad_net_fusable(const nn_model* m, const Mesh& mesh) {
-    // the fused launch pays off once its 16-element blocks fill the GPU (one
-    // per CU); on smaller meshes the separate BR1 launch spreads the
-    // elements over all CUs and wins
-    return m && mesh.PP == 4 && mesh.ph.viscous && mesh.E % net_rows_per_block() == 0 &&
-           mesh.E / net_rows_per_block() >= cu_count() && m->dims[0] == m->n_in * mesh.n_p;
+GradNetForm grad_net_form(const nn_model* m, const Mesh& mesh) {
+    if (!m || mesh.PP != 4 || !mesh.ph.viscous || m->dims[0] != m->n_in * mesh.n_p) return kGradNetApart;
+    return grad_net_form(net_args(m), mesh.E);
 }
 
 int grad_net_impl(const nn_model* m, const Mesh& mesh, const SolveDesc& S, const double* q, double* out,

@@ -161,14 +161,15 @@ __device__ __forceinline__ floatx4 mma_frags(const bf16x8 (&b)[kMaxKS], const ui
     return acc;
 }
 
-// normalised network input of node n of variable v, value qv (Sec. 2.2:
-// per-variable, or per-node when the model carries column statistics)
-__device__ __forceinline__ float net_input(const NetArgs& na, int NP, int v, int n, double qv) {
+// normalised network input of node n of the j-th variable read, value qv
+// (Sec. 2.2: per-variable, or per-node when the model carries column
+// statistics)
+__device__ __forceinline__ float net_input(const NetArgs& na, int NP, int j, int n, double qv) {
     if (na.col) {
-        const int cc = v * NP + n;
-        return (float)((qv - na.col[cc]) / na.col[5 * NP + cc]);
+        const int cc = na.in_var[j] * NP + n;
+        return (float)((qv - gmem(na.col)[cc]) / gmem(na.col)[5 * NP + cc]);
     }
-    return (float)((qv - na.mu_in[v]) / na.sig_in[v]);
+    return (float)((qv - na.in_mu[j]) * na.in_isig[j]);
 }
 
 // write mode: the variables the network does not force get s = 0 (rows
@@ -183,6 +184,198 @@ __device__ __forceinline__ void net_zero_unforced(const NetArgs& na, int NP, con
         bool forced = false;
         for (int j = 0; j < na.n_out; ++j) forced = forced || na.out_var[j] == v;
         if (e < T.E && !forced) gmem(T.out)[v * vs + (size_t)e * NP + n] = 0.0;
+    }
+}
+
+// ---- networks whose hidden layers are all 256 wide, as the ones of the
+// accuracy studies and the throughput workload: one column tile of each
+// hidden layer for each of the sixteen wavefronts, eight K steps.
+//
+// What a launch takes is one block's chain: states, dependent layers, the
+// forcing, and the 590 KB of weights that each block reads from L2 at 64 B a
+// clock (9200 clocks).  The general form below spent 40 k clocks on it (512
+// elements, 320-256-256-256-320: 18.3 us a launch; 12.1 k until the rows were
+// in LDS, entry after entry with two divisions each; 2 k a layer issuing the
+// next tile's loads in one run, all sixteen wavefronts at once, before 1.9 k
+// of epilogue; 1.3 k a layer of products, each behind its own LDS read).
+// Here the loads are issued between the rows of the epilogue, and the step
+// counts are template arguments: counts known at run time put a branch around
+// each load and copies of registers in flight where the branches meet.
+// 12.3 us a launch; with the BR1 pass of 16^3 elements 25.2 -> 19.8 us.
+
+// The loads are scheduled as written between these.
+__device__ __forceinline__ void net_fence() { __builtin_amdgcn_sched_barrier(0); }
+
+// waits until a loaded value is in its register
+__device__ __forceinline__ void arrived(double& x) { asm volatile("" : "+v"(x)); }
+
+// fragments [S0, S1) of the tile whose lane offset is vo
+template <int S0, int S1, int N>
+__device__ __forceinline__ void load_steps(bf16x8 (&b)[N], __amdgpu_buffer_rsrc_t rs, int vo) {
+#pragma unroll
+    for (int s = S0; s < S1; ++s) b[s] = weight_frag(rs, vo, s);
+}
+
+// C tile = A[16][32 KS] (LDS rows from arow) times the fragments b
+template <int KS, int N>
+__device__ __forceinline__ floatx4 mma_steps(const bf16x8 (&b)[N], const uint16_t* arow) {
+    bf16x8 a[KS];
+#pragma unroll
+    for (int s = 0; s < KS; ++s) a[s] = *(const bf16x8*)(arow + 32 * s);
+    floatx4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int s = 0; s < KS; ++s) acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[s], b[s], acc, 0, 0, 0);
+    return acc;
+}
+
+// input steps K0 (dims[0] padded to 32 K0) that have kernels of their own
+inline int net256_steps(const NetArgs& na) {
+    if (na.n_layers < 2) return 0;
+    for (int l = 1; l < na.n_layers; ++l)
+        if (na.dims[l] != 256) return 0;
+    const int k0 = na.pdims[0] / 32;
+    if (na.pdims[na.n_layers] > 32 * kMaxKS) return 0;
+    return k0 == 3 || k0 == 5 || k0 == 6 || k0 == 10 ? k0 : 0;
+}
+
+// A wavefront's tile of the first layer, loaded behind the states it is
+// applied to.
+template <int K0>
+struct FirstTile {
+    bf16x8 b[K0];
+    float bias;
+    __device__ __forceinline__ void load(const NetArgs& na, int wave, int lane) {
+        load_steps<0, K0>(b, weight_rsrc(gmem(na.W[0]), 32 * K0, 256), (wave * K0 * 64 + lane) * 16);
+        bias = gmem(na.b[0])[wave * 16 + (lane & 15)];
+    }
+};
+
+// entry j of a five-entry array of the arguments, by selects (indexed by a
+// lane's value the array would be read from memory, a round trip each)
+template <class V>
+__device__ __forceinline__ V pick5(const V* a, int j) {
+    V x = a[0];
+    x = j == 1 ? a[1] : x;
+    x = j == 2 ? a[2] : x;
+    x = j == 3 ? a[3] : x;
+    x = j == 4 ? a[4] : x;
+    return x;
+}
+
+// Gather + normalise + bf16 of a block's sixteen rows (elements e0 ...):
+// wavefront w row w, a lane a node (zero rows beyond E and columns beyond
+// dims[0]).  The first tile of weights (K0 > 0) is asked for when the states
+// are there: all wavefronts' loads go through one queue, and the last one's
+// states would wait for the others' weights.
+template <int K0>
+__device__ __forceinline__ void net_gather(const NetArgs& na, int NP, const NetTarget& T, int e0, uint16_t* bufA, int ld,
+                                           int wave, int lane, FirstTile<K0 ? K0 : 1>& first) {
+    const size_t vs = (size_t)T.E * NP;
+    const int din = na.dims[0], pin = na.pdims[0];
+    const int e = e0 + wave;
+    uint16_t* row = bufA + wave * ld;
+    const bool in = e < T.E;
+    const global_t<const double>* q = gmem(T.q) + (size_t)(in ? e : e0) * NP;
+    size_t var[5];   // beyond n_in: variable 0, read and not used
+#pragma unroll
+    for (int j = 0; j < 5; ++j) var[j] = na.in_var[j] * vs;
+    for (int n0 = 0; n0 < NP; n0 += 64) {
+        const int n = n0 + lane;
+        const int nc = n < NP ? n : NP - 1;
+        double x[5];
+#pragma unroll
+        for (int j = 0; j < 5; ++j) x[j] = q[var[j] + nc];
+        if constexpr (K0 > 0)
+            if (n0 == 0) {
+#pragma unroll
+                for (int j = 0; j < 5; ++j) arrived(x[j]);
+                first.load(na, wave, lane);
+            }
+#pragma unroll
+        for (int j = 0; j < 5; ++j)
+            if (j < na.n_in) {
+                const float v = net_input(na, NP, j, nc, x[j]);
+                if (n < NP) row[j * NP + n] = f2bf(in ? v : 0.0f);
+            }
+    }
+    for (int c = din + lane; c < pin; c += 64) row[c] = f2bf(0.0f);
+}
+
+// The layers of one 16-row block, as net_block_forward below.
+template <int K0, int ACT>
+__device__ __forceinline__ void net256_forward(const NetArgs& na, int NP, const NetTarget& T, int e0, int accumulate,
+                                               uint16_t* bufA, uint16_t* bufB, int ld, int wave, int lane,
+                                               FirstTile<K0>& first) {
+    const size_t vs = (size_t)T.E * NP;
+    const int L = na.n_layers;
+    const int r = lane & 15, g = lane >> 4;
+    const int Np = na.pdims[L], Nd = na.dims[L], nt = Np / 16;
+    // output columns of this wavefront: where they go and their scale
+    bf16x8 b[8];
+    float bn = first.bias;
+    floatx4 acc = mma_steps<K0>(first.b, bufA + r * ld + 8 * g);
+    for (int l = 0; l + 1 < L; ++l) {
+        // layer l's products are in acc; its epilogue with layer l + 1's loads
+        const bool out = l + 2 == L;
+        const __amdgpu_buffer_rsrc_t rs = weight_rsrc(gmem(na.W[l + 1]), 256, out ? Np : 256);
+        const int tile = out && wave >= nt ? nt - 1 : wave;
+        const int vo = (tile * 8 * 64 + lane) * 16;
+        const int n1 = tile * 16 + r;
+        const float bnext = gmem(na.b[l + 1])[out && n1 >= Nd ? Nd - 1 : n1];
+        uint16_t* o = bufB + 4 * g * ld + wave * 16 + r;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            if (i == 0) load_steps<0, 2>(b, rs, vo);
+            if (i == 1) load_steps<2, 4>(b, rs, vo);
+            if (i == 2) load_steps<4, 6>(b, rs, vo);
+            if (i == 3) load_steps<6, 8>(b, rs, vo);
+            net_fence();
+            o[i * ld] = f2bf(act_fwd(acc[i] + bn, ACT));
+            net_fence();
+        }
+        bn = bnext;
+        __syncthreads();
+        uint16_t* tmp = bufA;
+        bufA = bufB;
+        bufB = tmp;
+        acc = mma_steps<8>(b, bufA + r * ld + 8 * g);
+    }
+    // the output layer: its first tile's products are in acc
+    const __amdgpu_buffer_rsrc_t rs = weight_rsrc(gmem(na.W[L - 1]), 256, Np);
+    for (int tile = wave; tile < nt; tile += kRowWaves) {
+        const int n = tile * 16 + r;
+        const bool more = tile + kRowWaves < nt;
+        if (more) load_steps<0, 8>(b, rs, ((tile + kRowWaves) * 8 * 64 + lane) * 16);
+        if (n < Nd) {
+            const int j = (n >= NP) + (n >= 2 * NP) + (n >= 3 * NP) + (n >= 4 * NP), node = n - j * NP;
+            const int vv = pick5(na.out_var, j);
+            double sc, sh;
+            if (na.col) {
+                const int cc = vv * NP + node;
+                sc = pick5(na.mask, vv) * gmem(na.col)[15 * NP + cc];
+                sh = pick5(na.mask, vv) * gmem(na.col)[10 * NP + cc];
+            } else {
+                sc = pick5(na.out_scale, j);
+                sh = pick5(na.out_shift, j);
+            }
+            global_t<double>* o = gmem(T.out) + vv * vs + (size_t)(e0 + 4 * g) * NP + node;
+            double s[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) s[i] = sc * (double)(acc[i] + bn) + sh;
+            if (accumulate) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    if (e0 + 4 * g + i < T.E) s[i] += o[i * NP];
+            }
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                if (e0 + 4 * g + i < T.E) o[i * NP] = s[i];
+        }
+        if (more) {
+            const int n1 = n + 16 * kRowWaves;
+            bn = gmem(na.b[L - 1])[n1 < Nd ? n1 : Nd - 1];
+            acc = mma_steps<8>(b, bufA + r * ld + 8 * g);
+        }
     }
 }
 

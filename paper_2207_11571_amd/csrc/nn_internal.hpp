@@ -39,9 +39,9 @@ int net_forcing_impl(const nn_model* m, const Mesh& mesh, const double* q, doubl
                      hipStream_t st);
 // batched: several solves' fields in one launch (all on meshes of the same order)
 int net_forcing_batch(const nn_model* m, int n_p, const NetTarget* targets, int nt, hipStream_t st);
-// whether the stage's BR1 pass and the network (write mode, out = s(q)) can
-// run as one launch (launch_grad_net) on this mesh
-bool grad_net_fusable(const nn_model* m, const Mesh& mesh);
+// how the stage's BR1 pass and the network (write mode, out = s(q)) run on
+// this mesh; apart without a model or where they cannot share a launch
+GradNetForm grad_net_form(const nn_model* m, const Mesh& mesh);
 // the BR1 pass of the stage described by S and out = s(q) in one launch
 int grad_net_impl(const nn_model* m, const Mesh& mesh, const SolveDesc& S, const double* q, double* out,
                   hipStream_t st);

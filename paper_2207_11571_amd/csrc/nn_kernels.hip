@@ -19,6 +19,7 @@
 namespace dgnn {
 
 int net_rows_per_block() { return kRows; }
+int net_row_pad() { return kLdPad; }
 
 struct NetTargets {
     NetTarget t[16];
@@ -27,11 +28,11 @@ struct NetTargets {
 
 // ------------------------------------------------------------------ inference
 
+// K0 > 0: hidden layers of 256 (net256_forward), K0 steps of input; 0: any
+template <int K0, int ACT>
 __global__ void __launch_bounds__(kRowThreads) k_net_forcing(NetArgs na, int NP, NetTargets tg, int accumulate) {
     extern __shared__ __attribute__((aligned(16))) uint16_t smem[];
-    int pmax = 0;
-    for (int l = 0; l <= na.n_layers; ++l) pmax = pmax > na.pdims[l] ? pmax : na.pdims[l];
-    const int ld = pmax + kLdPad;
+    const int ld = na.ld;
     uint16_t* bufA = smem;
     uint16_t* bufB = smem + kRows * ld;
 
@@ -43,25 +44,15 @@ __global__ void __launch_bounds__(kRowThreads) k_net_forcing(NetArgs na, int NP,
     const int e0 = (b - T.blk_begin) * kRows;
     const int E = T.E;
     const int t = threadIdx.x;
-    const int wave = t >> 6, lane = t & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(t >> 6), lane = t & 63;
     const size_t vs = (size_t)E * NP;
 
-    // gather + normalise + bf16 (zero rows beyond E and columns beyond dims[0])
-    const int din = na.dims[0], pin = na.pdims[0];
-    for (int idx = t; idx < kRows * pin; idx += kRowThreads) {
-        const int r = idx / pin, c = idx - r * pin;
-        const int e = e0 + r;
-        float x = 0.0f;
-        if (e < E && c < din) {
-            const int j = c / NP, n = c - j * NP;
-            const int v = na.in_var[j];
-            x = net_input(na, NP, v, n, gmem(T.q)[v * vs + (size_t)e * NP + n]);
-        }
-        bufA[r * ld + c] = f2bf(x);
-    }
+    FirstTile<K0 ? K0 : 1> first;
+    net_gather<K0>(na, NP, T, e0, bufA, ld, wave, lane, first);
     if (!accumulate) net_zero_unforced(na, NP, T, e0, t);
     __syncthreads();
-    net_block_forward(na, NP, T, e0, accumulate, bufA, bufB, ld, wave, lane);
+    if constexpr (K0 > 0) net256_forward<K0, ACT>(na, NP, T, e0, accumulate, bufA, bufB, ld, wave, lane, first);
+    else net_block_forward(na, NP, T, e0, accumulate, bufA, bufB, ld, wave, lane);
 }
 
 // ------------------------------------------------------------------- weights
@@ -113,9 +104,7 @@ __device__ __forceinline__ void store_transposed(const uint16_t* src, int ld, in
 __global__ void __launch_bounds__(kRowThreads) k_train_rows(NetArgs na, TrainArgs ta) {
     extern __shared__ __attribute__((aligned(16))) uint16_t smem[];
     const int L = na.n_layers;
-    int pmax = 0;
-    for (int l = 0; l <= L; ++l) pmax = pmax > na.pdims[l] ? pmax : na.pdims[l];
-    const int ld = pmax + kLdPad;
+    const int ld = na.ld;
     // act(0..L-1) then two gradient buffers
     auto act = [&](int l) { return smem + l * kRows * ld; };
     uint16_t* g0 = smem + L * kRows * ld;
@@ -124,7 +113,7 @@ __global__ void __launch_bounds__(kRowThreads) k_train_rows(NetArgs na, TrainArg
 
     const int r0 = blockIdx.x * kRows;
     const int t = threadIdx.x;
-    const int wave = t >> 6, lane = t & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(t >> 6), lane = t & 63;
     const int B = ta.B, Bp = ta.Bp;
     const int din = na.dims[0], pin = na.pdims[0];
     const int npv_in = din / na.n_in;
@@ -240,7 +229,7 @@ __global__ void __launch_bounds__(kThreads) k_wgrad(GradArgs ga) {
     int l = 0;
     while (l + 1 < ga.n_layers && (int)blockIdx.x >= ga.tblk[l + 1]) ++l;
     const int t = threadIdx.x;
-    const int wave = t >> 6, lane = t & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(t >> 6), lane = t & 63;
     const int pout = ga.pout[l], pin = ga.pin[l], Bp = ga.Bp;
     const int tiles_i = pin / 32;
     const int tile = ((int)blockIdx.x - ga.tblk[l]) * 4 + wave;
@@ -477,41 +466,40 @@ hipError_t launch_data_stats(const float* x, const float* y, int64_t rows, int n
 }
 
 static size_t net_smem_bytes(const NetArgs& na, int nbuf) {
-    int pmax = 0;
-    for (int l = 0; l <= na.n_layers; ++l) pmax = pmax > na.pdims[l] ? pmax : na.pdims[l];
-    return (size_t)nbuf * kRows * (pmax + kLdPad) * sizeof(uint16_t);
+    return (size_t)nbuf * kRows * na.ld * sizeof(uint16_t);
+}
+
+static hipError_t launch_forcing(const NetArgs& na, int n_p, const NetTarget* targets, int nt, int nblocks,
+                                 int accumulate, hipStream_t st) {
+    if (nt < 1 || nt > 16) return hipErrorInvalidValue;
+    NetTargets tg;
+    for (int i = 0; i < nt; ++i) tg.t[i] = targets[i];
+    tg.n = nt;
+    const size_t smem = net_smem_bytes(na, 2);
+    auto kernel = k_net_forcing<0, 0>;
+    switch (net256_steps(na)) {
+        case 3: kernel = na.act ? k_net_forcing<3, 1> : k_net_forcing<3, 0>; break;
+        case 5: kernel = na.act ? k_net_forcing<5, 1> : k_net_forcing<5, 0>; break;
+        case 6: kernel = na.act ? k_net_forcing<6, 1> : k_net_forcing<6, 0>; break;
+        case 10: kernel = na.act ? k_net_forcing<10, 1> : k_net_forcing<10, 0>; break;
+        default: break;
+    }
+    if (smem > 65536) {
+        hipError_t e = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+        if (e != hipSuccess) return e;
+    }
+    hipLaunchKernelGGL(kernel, dim3(nblocks), dim3(kRowThreads), smem, st, na, n_p, tg, accumulate);
+    return hipGetLastError();
 }
 
 hipError_t launch_net_forcing(const NetArgs& na, int n_p, const NetTarget* targets, int nt, int nblocks,
                               hipStream_t st) {
-    if (nt < 1 || nt > 16) return hipErrorInvalidValue;
-    NetTargets tg;
-    for (int i = 0; i < nt; ++i) tg.t[i] = targets[i];
-    tg.n = nt;
-    const size_t smem = net_smem_bytes(na, 2);
-    if (smem > 65536) {
-        hipError_t e = hipFuncSetAttribute((const void*)k_net_forcing, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                           (int)smem);
-        if (e != hipSuccess) return e;
-    }
-    hipLaunchKernelGGL(k_net_forcing, dim3(nblocks), dim3(kRowThreads), smem, st, na, n_p, tg, 1);
-    return hipGetLastError();
+    return launch_forcing(na, n_p, targets, nt, nblocks, 1, st);
 }
 
 hipError_t launch_net_forcing_write(const NetArgs& na, int n_p, const NetTarget* targets, int nt, int nblocks,
                                     hipStream_t st) {
-    if (nt < 1 || nt > 16) return hipErrorInvalidValue;
-    NetTargets tg;
-    for (int i = 0; i < nt; ++i) tg.t[i] = targets[i];
-    tg.n = nt;
-    const size_t smem = net_smem_bytes(na, 2);
-    if (smem > 65536) {
-        hipError_t e = hipFuncSetAttribute((const void*)k_net_forcing, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                           (int)smem);
-        if (e != hipSuccess) return e;
-    }
-    hipLaunchKernelGGL(k_net_forcing, dim3(nblocks), dim3(kRowThreads), smem, st, na, n_p, tg, 0);
-    return hipGetLastError();
+    return launch_forcing(na, n_p, targets, nt, nblocks, 0, st);
 }
 
 hipError_t launch_net_refresh_layer(const NetArgs& na, const float* params, int64_t woff, int l, uint16_t* wbf,

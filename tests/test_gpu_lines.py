@@ -69,3 +69,28 @@ def test_list_of_solves(B, P):
         torch.cuda.synchronize()
         assert np.array_equal(q.cpu().numpy().ravel(), srv.results(rid)[1])
     srv.close()
+
+
+# sixteen-element blocks: one, not full (1, 8, 27), several (125), and more
+# than half of the CUs (2197: two launches); hidden widths with and without
+# kernels of their own
+@pytest.mark.parametrize("N", [1, 2, 3, 5, 13])
+@pytest.mark.parametrize("hidden,momenta", [((256, 256, 256), False), ((256,), True), ((96, 256), False)])
+def test_network_beside_br1_pass(B, N, hidden, momenta):
+    """Steps with the forcing network, whose BR1 pass may share the network's
+    launch, against the measurement twin, which launches them one after the
+    other: bitwise."""
+    say("network beside BR1 pass", N, hidden, momenta)
+    io = (1, 2, 3) if momenta else (0, 1, 2, 3, 4)
+    dims = [64 * len(io), *hidden, 64 * len(io)]
+    norm = [1.0, 0.0, 0.0, 0.0, synthetic.TGV_ENERGY_LEVEL, 0.01, 1.0, 1.0, 1.0, 1.0] + [0.0] * 5 + [1e-3] * 5
+    model = B.Model(dims, B.pack_params(synthetic.mlp_init(dims, seed=0)), norm, train=False,
+                    activation="relu" if momenta else "tanh", in_vars=io, out_vars=io)
+    m = B.Mesh(N, 3, 200.0)
+    q = torch.from_numpy(synthetic.random_state(N, 3, seed=7, momentum=0.3)).cuda()
+    dt = 0.5 * B.dg_stable_dt(m, q)
+    q2, k, k2 = q.clone(), m.field(0.0), m.field(0.0)
+    B.dg_rk_step(m, q, k, dt, 2, model=model)
+    B.dg_profile_steps(m, q2, k2, dt, 2, model=model)
+    torch.cuda.synchronize()
+    assert torch.isfinite(q).all() and torch.equal(q, q2) and torch.equal(k, k2)
