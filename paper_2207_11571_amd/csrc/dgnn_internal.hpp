@@ -100,6 +100,8 @@ struct NetArgs {
     double in_mu[5], in_isig[5];
     // per output variable: s = out_scale[j] yhat + out_shift[j] (mask applied)
     double out_scale[5], out_shift[5];
+    // and of the targets: mean and 1 / sigma
+    double out_mu[5], out_isig[5];
     // the network reads variables in_var[0..n_in) (input column j n_p + n is
     // node n of variable in_var[j]) and forces out_var[0..n_out) likewise
     int n_in, n_out;

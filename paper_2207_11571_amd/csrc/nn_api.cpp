@@ -68,6 +68,8 @@ NetArgs net_args(const nn_model* m) {
         na.in_mu[v] = m->norm[m->in_var[v]];
         na.in_isig[v] = 1.0 / m->norm[5 + m->in_var[v]];
         const int o = m->out_var[v];
+        na.out_mu[v] = m->norm[10 + o];
+        na.out_isig[v] = 1.0 / m->norm[15 + o];
         na.out_scale[v] = m->mask[o] * m->norm[15 + o];
         na.out_shift[v] = m->mask[o] * m->norm[10 + o];
     }

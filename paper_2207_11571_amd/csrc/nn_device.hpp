@@ -207,7 +207,10 @@ __device__ __forceinline__ void net_zero_unforced(const NetArgs& na, int NP, con
 __device__ __forceinline__ void net_fence() { __builtin_amdgcn_sched_barrier(0); }
 
 // waits until a loaded value is in its register
-__device__ __forceinline__ void arrived(double& x) { asm volatile("" : "+v"(x)); }
+template <class V>
+__device__ __forceinline__ void arrived(V& x) {
+    asm volatile("" : "+v"(x));
+}
 
 // fragments [S0, S1) of the tile whose lane offset is vo
 template <int S0, int S1, int N>
@@ -250,17 +253,17 @@ struct FirstTile {
     }
 };
 
-// entry j of a five-entry array of the arguments, by selects (indexed by a
-// lane's value the array would be read from memory, a round trip each)
+// A five-entry array of the arguments in scalar registers, entry j by selects:
+// indexed by a lane's value the array would be read from memory, a round trip
+// each (and the compiler turns selects of its loads into that).
 template <class V>
-__device__ __forceinline__ V pick5(const V* a, int j) {
-    V x = a[0];
-    x = j == 1 ? a[1] : x;
-    x = j == 2 ? a[2] : x;
-    x = j == 3 ? a[3] : x;
-    x = j == 4 ? a[4] : x;
-    return x;
-}
+struct Five {
+    V a, b, c, d, e;
+    __device__ __forceinline__ explicit Five(const V* p) : a(p[0]), b(p[1]), c(p[2]), d(p[3]), e(p[4]) {
+        asm volatile("" : "+s"(a), "+s"(b), "+s"(c), "+s"(d), "+s"(e));
+    }
+    __device__ __forceinline__ V at(int j) const { return j == 0 ? a : (j == 1 ? b : (j == 2 ? c : (j == 3 ? d : e))); }
+};
 
 // Gather + normalise + bf16 of a block's sixteen rows (elements e0 ...):
 // wavefront w row w, a lane a node (zero rows beyond E and columns beyond
@@ -310,7 +313,6 @@ __device__ __forceinline__ void net256_forward(const NetArgs& na, int NP, const 
     const int L = na.n_layers;
     const int r = lane & 15, g = lane >> 4;
     const int Np = na.pdims[L], Nd = na.dims[L], nt = Np / 16;
-    // output columns of this wavefront: where they go and their scale
     bf16x8 b[8];
     float bn = first.bias;
     floatx4 acc = mma_steps<K0>(first.b, bufA + r * ld + 8 * g);
@@ -341,23 +343,27 @@ __device__ __forceinline__ void net256_forward(const NetArgs& na, int NP, const 
         acc = mma_steps<8>(b, bufA + r * ld + 8 * g);
     }
     // the output layer: its first tile's products are in acc
+    const Five<int> out_var(na.out_var);
+    const Five<double> out_scale(na.out_scale), out_shift(na.out_shift);
     const __amdgpu_buffer_rsrc_t rs = weight_rsrc(gmem(na.W[L - 1]), 256, Np);
     for (int tile = wave; tile < nt; tile += kRowWaves) {
         const int n = tile * 16 + r;
         const bool more = tile + kRowWaves < nt;
+        const int nc = n < Nd ? n : Nd - 1;
+        const int j = (nc >= NP) + (nc >= 2 * NP) + (nc >= 3 * NP) + (nc >= 4 * NP), node = nc - j * NP;
+        const int vv = out_var.at(j);
+        double sc = out_scale.at(j), sh = out_shift.at(j);
+        if (na.col) {
+            const int cc = vv * NP + node;
+            const double mask = na.mask[vv];
+            sc = mask * gmem(na.col)[15 * NP + cc];
+            sh = mask * gmem(na.col)[10 * NP + cc];
+        }
+        arrived(sc);   // ahead of the next tile's loads, which return behind it
+        arrived(sh);
+        arrived(bn);
         if (more) load_steps<0, 8>(b, rs, ((tile + kRowWaves) * 8 * 64 + lane) * 16);
         if (n < Nd) {
-            const int j = (n >= NP) + (n >= 2 * NP) + (n >= 3 * NP) + (n >= 4 * NP), node = n - j * NP;
-            const int vv = pick5(na.out_var, j);
-            double sc, sh;
-            if (na.col) {
-                const int cc = vv * NP + node;
-                sc = pick5(na.mask, vv) * gmem(na.col)[15 * NP + cc];
-                sh = pick5(na.mask, vv) * gmem(na.col)[10 * NP + cc];
-            } else {
-                sc = pick5(na.out_scale, j);
-                sh = pick5(na.out_shift, j);
-            }
             global_t<double>* o = gmem(T.out) + vv * vs + (size_t)(e0 + 4 * g) * NP + node;
             double s[4];
 #pragma unroll

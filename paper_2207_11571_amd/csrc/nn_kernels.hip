@@ -81,6 +81,7 @@ __global__ void __launch_bounds__(256) k_fill_f32(float* p, float v, size_t n) {
 // ------------------------------------------------------------------- training
 
 typedef uint16_t u16x8 __attribute__((ext_vector_type(8)));
+typedef uint16_t u16x4 __attribute__((ext_vector_type(4)));
 
 // Columns c < pd of the block's 16 LDS rows (rows r0 .. r0 + 15 of the
 // batch) to dst in fragment order over the batch (wfrag_index with K = Bp):
@@ -217,6 +218,211 @@ __global__ void __launch_bounds__(kRowThreads) k_train_rows(NetArgs na, TrainArg
         gin = gout;
         gout = tmp;
         __syncthreads();
+    }
+}
+
+// The same for networks with hidden layers of 256 (net256_steps), K0 steps of
+// input and nt column tiles of output.  Each wavefront owns the same column
+// tile of every hidden layer, forward and backward, and the lane that forms
+// rows 4 g .. 4 g + 3 of a column holds four consecutive batch entries of it,
+// so activations and output gradients go to their transposed arrays straight
+// from the epilogues, 8 bytes a lane, and the bias sums of a column are three
+// additions and a butterfly over its four lanes; only the input's transpose
+// goes through LDS.  Weights are loaded ahead as in net256_forward, the
+// targets before the output layer.
+template <int K0, int ACT>
+__global__ void __launch_bounds__(kRowThreads) k_train256(NetArgs na, TrainArgs ta) {
+    extern __shared__ __attribute__((aligned(16))) uint16_t smem[];
+    const int L = na.n_layers, ld = na.ld;
+    auto act = [&](int l) { return smem + l * kRows * ld; };
+    uint16_t* g0 = smem + L * kRows * ld;
+    uint16_t* g1 = g0 + kRows * ld;
+    __shared__ float red[kRowWaves];
+
+    const int t = threadIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(t >> 6), lane = t & 63;
+    const int r = lane & 15, g = lane >> 4;
+    const int r0 = blockIdx.x * kRows, B = ta.B, Bp = ta.Bp;
+    const int Np = na.pdims[L], Nd = na.dims[L], nt = Np / 16;
+    const int npv = na.dims[0] / na.n_in;
+    const size_t rw = (size_t)5 * npv;
+
+    // gather + normalise + bf16: wavefront w row w
+    FirstTile<K0> first;
+    {
+        const int din = na.dims[0];
+        const int row = r0 + wave;
+        const bool in = row < B;
+        const int rc = in ? row : B - 1;
+        const size_t src = ta.idx ? (size_t)gmem(ta.idx)[rc] : (size_t)rc;
+        const global_t<const float>* x = gmem(ta.x) + src * rw;
+        uint16_t* o = act(0) + wave * ld;
+        float xv[5];
+        for (int n0 = 0; n0 < npv; n0 += 64) {
+            const int n = n0 + lane;
+            const int nc = n < npv ? n : npv - 1;
+#pragma unroll
+            for (int j = 0; j < 5; ++j) xv[j] = x[na.in_var[j] * npv + nc];
+            if (n0 == 0) {
+#pragma unroll
+                for (int j = 0; j < 5; ++j) arrived(xv[j]);
+                first.load(na, wave, lane);
+            }
+#pragma unroll
+            for (int j = 0; j < 5; ++j)
+                if (j < na.n_in) {
+                    const float v = net_input(na, npv, j, nc, (double)xv[j]);
+                    if (n < npv) o[j * npv + n] = f2bf(in ? v : 0.0f);
+                }
+        }
+        for (int c = din + lane; c < 32 * K0; c += 64) o[c] = f2bf(0.0f);
+    }
+    // the lane's four rows of the targets
+    size_t ysrc[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int row = r0 + 4 * g + i < B ? r0 + 4 * g + i : B - 1;
+        ysrc[i] = (ta.idx ? (size_t)gmem(ta.idx)[row] : (size_t)row) * rw;
+    }
+    __syncthreads();
+    // its place in the transposed arrays, in column tile 0: batch rows
+    // r0 + 4 g .. + 3 of column r
+    const int64_t tile_step = (int64_t)(Bp >> 5) * 512;
+    const int64_t tr = wfrag_index(r, r0 + 4 * g, Bp);
+
+    bf16x8 b[K0 > 8 ? K0 : 8];
+    float bn = first.bias;
+    floatx4 acc = mma_steps<K0>(first.b, act(0) + r * ld + 8 * g);
+    store_transposed(act(0), ld, 32 * K0, gmem(ta.actT[0]), r0, Bp, t);
+    float yv[2][4];
+    const Five<int> out_var(na.out_var);
+    for (int l = 0; l + 1 < L; ++l) {
+        const bool out = l + 2 == L;
+        const __amdgpu_buffer_rsrc_t rs = weight_rsrc(gmem(na.W[l + 1]), 256, out ? Np : 256);
+        const int tile = out && wave >= nt ? nt - 1 : wave;
+        const int vo = (tile * 8 * 64 + lane) * 16;
+        const int n1 = tile * 16 + r;
+        const float bnext = gmem(na.b[l + 1])[out && n1 >= Nd ? Nd - 1 : n1];
+        uint16_t* o = act(l + 1) + 4 * g * ld + wave * 16 + r;
+        u16x4 h;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            if (i == 0) load_steps<0, 2>(b, rs, vo);
+            if (i == 1) load_steps<2, 4>(b, rs, vo);
+            if (i == 2) load_steps<4, 6>(b, rs, vo);
+            if (i == 3) load_steps<6, 8>(b, rs, vo);
+            net_fence();
+            h[i] = f2bf(act_fwd(acc[i] + bn, ACT));
+            o[i * ld] = h[i];
+            net_fence();
+        }
+        *(global_t<u16x4>*)(gmem(ta.actT[l + 1]) + wave * tile_step + tr) = h;
+        if (out) {
+#pragma unroll
+            for (int s = 0; s < 2; ++s) {
+                const int n = (wave + s * kRowWaves) * 16 + r;
+                const int nc = n < Nd ? n : Nd - 1;
+                const int j = (nc >= npv) + (nc >= 2 * npv) + (nc >= 3 * npv) + (nc >= 4 * npv);
+                const int c = out_var.at(j) * npv + nc - j * npv;
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    yv[s][i] = gmem(ta.y)[ysrc[i] + c];
+            }
+        }
+        bn = bnext;
+        __syncthreads();
+        acc = mma_steps<8>(b, act(l + 1) + r * ld + 8 * g);
+    }
+    // output layer: loss gradient dY = scale (yhat - ytilde); its first tile's
+    // products are in acc
+    float lsum = 0.0f;
+    const Five<double> out_mu(na.out_mu), out_isig(na.out_isig);
+    auto output_tile = [&](int tile, const float (&y)[4]) {
+        const int n = tile * 16 + r;
+        const int nc = n < Nd ? n : Nd - 1;
+        const int j = (nc >= npv) + (nc >= 2 * npv) + (nc >= 3 * npv) + (nc >= 4 * npv);
+        const double mu = out_mu.at(j), isig = out_isig.at(j);
+        u16x4 d;
+        float bsum = 0.0f;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            float dy = 0.0f;
+            if (r0 + 4 * g + i < B && n < Nd) {
+                float yt;
+                if (na.col) {
+                    const int cc = out_var.at(j) * npv + nc - j * npv;
+                    yt = (float)(((double)y[i] - gmem(na.col)[10 * npv + cc]) / gmem(na.col)[15 * npv + cc]);
+                } else {
+                    yt = (float)(((double)y[i] - mu) * isig);
+                }
+                const float diff = acc[i] + bn - yt;
+                lsum += diff * diff;
+                dy = ta.grad_scale * diff;
+            }
+            d[i] = f2bf(dy);
+            g0[(4 * g + i) * ld + n] = d[i];
+            bsum += bf2f(d[i]);
+        }
+        *(global_t<u16x4>*)(gmem(ta.dzT[L - 1]) + tile * tile_step + tr) = d;
+        bsum += __shfl_xor(bsum, 16);
+        bsum += __shfl_xor(bsum, 32);
+        if (g == 0) gmem(ta.bias_part[L - 1])[(size_t)blockIdx.x * Np + n] = bsum;
+    };
+    if (wave + kRowWaves < nt) {
+        const int n1 = (wave + kRowWaves) * 16 + r;
+        load_steps<0, 8>(b, weight_rsrc(gmem(na.W[L - 1]), 256, Np), ((wave + kRowWaves) * 8 * 64 + lane) * 16);
+        const float bnext = gmem(na.b[L - 1])[n1 < Nd ? n1 : Nd - 1];
+        output_tile(wave, yv[0]);
+        bn = bnext;
+        acc = mma_steps<8>(b, act(L - 1) + r * ld + 8 * g);
+        output_tile(wave + kRowWaves, yv[1]);
+    } else if (wave < nt) {
+        output_tile(wave, yv[0]);
+    }
+    // the first backward product's weights: K0 steps, as the input has
+    load_steps<0, K0>(b, weight_rsrc(gmem(na.WT[L - 1]), 32 * K0, 256), (wave * K0 * 64 + lane) * 16);
+    // the block's loss: a fixed butterfly within each wavefront, then
+    // wavefront 0 sums the sixteen partial sums in order
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) lsum += __shfl_xor(lsum, off);
+    if (lane == 0) red[wave] = lsum;
+    __syncthreads();
+    if (t == 0) {
+        float sum = 0.0f;
+        for (int w = 0; w < kRowWaves; ++w) sum += red[w];
+        ta.loss_part[blockIdx.x] = sum;
+    }
+    // backward data chain
+    uint16_t* gin = g0;
+    uint16_t* gout = g1;
+    acc = mma_steps<K0>(b, gin + r * ld + 8 * g);
+    for (int l = L - 1; l >= 1; --l) {
+        const uint16_t* h = act(l) + 4 * g * ld + wave * 16 + r;
+        uint16_t* o = gout + 4 * g * ld + wave * 16 + r;
+        const bool more = l > 1;
+        const __amdgpu_buffer_rsrc_t rs = weight_rsrc(gmem(na.WT[more ? l - 1 : l]), 256, 256);
+        const int vo = (wave * 8 * 64 + lane) * 16;
+        u16x4 d;
+        float bsum = 0.0f;
+        if (more) load_steps<0, 8>(b, rs, vo);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const float v = acc[i] * act_bwd(bf2f(h[i * ld]), ACT);
+            d[i] = f2bf(r0 + 4 * g + i < B ? v : 0.0f);
+            o[i * ld] = d[i];
+            bsum += bf2f(d[i]);
+        }
+        *(global_t<u16x4>*)(gmem(ta.dzT[l - 1]) + wave * tile_step + tr) = d;
+        bsum += __shfl_xor(bsum, 16);
+        bsum += __shfl_xor(bsum, 32);
+        if (g == 0) gmem(ta.bias_part[l - 1])[(size_t)blockIdx.x * 256 + wave * 16 + r] = bsum;
+        if (more) {
+            __syncthreads();
+            uint16_t* tmp = gin;
+            gin = gout;
+            gout = tmp;
+            acc = mma_steps<8>(b, gin + r * ld + 8 * g);
+        }
     }
 }
 
@@ -524,12 +730,21 @@ size_t train_smem_bytes(const NetArgs& na) { return net_smem_bytes(na, na.n_laye
 
 hipError_t launch_train_rows(const NetArgs& na, const TrainArgs& ta, int nblocks, hipStream_t st) {
     const size_t smem = train_smem_bytes(na);
+    auto kernel = k_train_rows;
+    // the backward chain starts with as many steps as the forward one where
+    // the network reads as many columns as it forces
+    if (na.pdims[na.n_layers] == na.pdims[0]) switch (net256_steps(na)) {
+        case 3: kernel = na.act ? k_train256<3, 1> : k_train256<3, 0>; break;
+        case 5: kernel = na.act ? k_train256<5, 1> : k_train256<5, 0>; break;
+        case 6: kernel = na.act ? k_train256<6, 1> : k_train256<6, 0>; break;
+        case 10: kernel = na.act ? k_train256<10, 1> : k_train256<10, 0>; break;
+        default: break;
+    }
     if (smem > 65536) {
-        hipError_t e = hipFuncSetAttribute((const void*)k_train_rows, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                           (int)smem);
+        hipError_t e = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
         if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL(k_train_rows, dim3(nblocks), dim3(kRowThreads), train_smem_bytes(na), st, na, ta);
+    hipLaunchKernelGGL(kernel, dim3(nblocks), dim3(kRowThreads), smem, st, na, ta);
     return hipGetLastError();
 }
 

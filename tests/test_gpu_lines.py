@@ -94,3 +94,42 @@ def test_network_beside_br1_pass(B, N, hidden, momenta):
     B.dg_profile_steps(m, q2, k2, dt, 2, model=model)
     torch.cuda.synchronize()
     assert torch.isfinite(q).all() and torch.equal(q, q2) and torch.equal(k, k2)
+
+
+# row blocks of sixteen: one row, one short, one over, two over; one, two and
+# three hidden layers of 256; the four input widths with kernels of their own
+@pytest.mark.parametrize("batch", [1, 15, 17, 34])
+@pytest.mark.parametrize("n_p,momenta,hidden", [(64, False, 3), (64, True, 1), (27, False, 2), (27, True, 3)])
+def test_training_rows(B, batch, n_p, momenta, hidden):
+    """Loss and gradients of a small batch of indexed rows against the oracle
+    with the same bfloat16 weights and activations.  What is left is the
+    rounding of the output gradients to bfloat16, 2^-9 relative each, once a
+    layer: below 1e-2 relative L2 for the at most four layers here."""
+    from oracle import mlp
+    say("training rows", batch, n_p, momenta, hidden)
+    io = (1, 2, 3) if momenta else (0, 1, 2, 3, 4)
+    kind = "relu" if momenta else "tanh"
+    dims = [n_p * len(io)] + [256] * hidden + [n_p * len(io)]
+    layers = [(W, b + np.float32(0.01)) for W, b in synthetic.mlp_init(dims, seed=4)]
+    mu, sig = np.array([1.0, 0, 0, 0, 178.7]), np.array([0.01, 0.5, 0.5, 0.5, 1.0])
+    norm = [*mu, *sig, *([0.0] * 5), *([1e-3] * 5)]
+    rng = np.random.default_rng(batch)
+    rows = batch + 5
+    x = (np.repeat(mu, n_p) + np.repeat(sig, n_p) * rng.standard_normal((rows, 5 * n_p))).astype(np.float32)
+    y = (1e-3 * rng.standard_normal((rows, 5 * n_p))).astype(np.float32)
+    idx = rng.permutation(rows)[:batch].astype(np.int32)
+    model = B.Model(dims, B.pack_params(layers), norm, activation=kind, in_vars=io, out_vars=io)
+    loss = torch.zeros(1, dtype=torch.float32, device="cuda")
+    B.nn_train_step(model, torch.from_numpy(x).cuda(), torch.from_numpy(y).cuda(), loss=loss,
+                    idx=torch.from_numpy(idx).cuda())
+    torch.cuda.synchronize()
+    cols = np.concatenate([np.arange(v * n_p, (v + 1) * n_p) for v in io])
+    xh = ((x[idx].astype(np.float64) - np.repeat(mu, n_p)) / np.repeat(sig, n_p))[:, cols]
+    yt = (y[idx].astype(np.float64) / 1e-3)[:, cols]
+    params = [(mlp.bf16_round(W), b.astype(np.float64)) for W, b in layers]
+    loss_ref, grads = mlp.mse_loss_and_grads(params, xh, yt, act=kind, quantise=True)
+    assert abs(loss.item() / loss_ref - 1) < 1e-3
+    for (gW, gb), (rW, rb) in zip(B.unpack_params(model.grad.cpu().numpy().astype(np.float64), dims), grads):
+        eW = np.linalg.norm(gW - rW) / np.linalg.norm(rW)
+        eb = np.linalg.norm(gb - rb) / np.linalg.norm(rb)
+        assert eW < 1e-2 and eb < 1e-2, (eW, eb)
