@@ -49,6 +49,7 @@ struct Line {
     // wavefront (P = 6, 7) one wavefront a direction, else packed
     static constexpr bool WD = PP == 7;
     static constexpr int NT = WD ? 192 : 64 * ((EPG * NL + 63) / 64);
+    static constexpr bool XOR = PP == 8 || PP == 4;       // permuted LDS order (lds_index)
     static constexpr int NN = (EPG * NP + NT - 1) / NT;   // nodes of a thread
     static constexpr int FS = EPG * NP;         // stride of the fields in LDS
 };
@@ -227,6 +228,17 @@ __device__ __forceinline__ double strain_square(const double g[3][4]) {
 }
 
 
+// LDS index of node (i, j, k) where PP is a power of two: rows and entries
+// permuted by the coordinates above them, so that the lines of each direction
+// spread over all banks (in node order, lines along x are PP entries apart).
+// 16^3 P=7: BR1 pass 47 -> 41 us, residual 127 -> 110, a step 511 -> 440;
+// 8^3 P=3: a step 29.0 -> 27.9.  Odd PP has no conflicts in node order, and
+// PP = 6 a two-way one along x alone.
+template <int PP>
+__device__ __forceinline__ int lds_index(int i, int j, int k) {
+    return (k * PP + (j ^ k)) * PP + (i ^ j);
+}
+
 // One thread's place in its group: its line and its nodes.  A thread without a
 // line, or without its last node, takes another's, and does everything but
 // the stores: loads under a branch would make the compiler wait for all of
@@ -273,10 +285,18 @@ __device__ __forceinline__ Place<PP> place_of(int group, int t, int N, int E) {
     p.nbp = p.e + (c + 1 == N ? 1 - N : 1) * st;
     p.nbm = p.e + (c == 0 ? N - 1 : -1) * st;
     const int a = p.r % PP, b = p.r / PP;
-    const int base = p.d == 0 ? PP * p.r : (p.d == 1 ? a + L::NF * b : p.r);
-    const int ns = p.d == 0 ? 1 : (p.d == 1 ? PP : L::NF);
+    if constexpr (L::XOR) {
 #pragma unroll
-    for (int m = 0; m < PP; ++m) p.at[m] = el * L::NP + base + m * ns;
+        for (int m = 0; m < PP; ++m) {
+            const int i = p.d == 0 ? m : a, j = p.d == 0 ? a : (p.d == 1 ? m : b), k = p.d == 2 ? m : b;
+            p.at[m] = lds_index<PP>(i, j, k);
+        }
+    } else {
+        const int base = p.d == 0 ? PP * p.r : (p.d == 1 ? a + L::NF * b : p.r);
+        const int ns = p.d == 0 ? 1 : (p.d == 1 ? PP : L::NF);
+#pragma unroll
+        for (int m = 0; m < PP; ++m) p.at[m] = el * L::NP + base + m * ns;
+    }
     return p;
 }
 
@@ -290,6 +310,13 @@ __device__ __forceinline__ bool node_of(const Place<PP>& p, int i, int& n) {
     const bool in = n <= last;
     n = in ? n : last;
     return in;
+}
+
+// LDS index of node n of the group
+template <int PP>
+__device__ __forceinline__ int node_lds(int n) {
+    if constexpr (Line<PP>::XOR) return lds_index<PP>(n % PP, (n / PP) % PP, n / (PP * PP));
+    else return n;
 }
 
 // the traces that the two ends of a line need: own and neighbour's
@@ -339,6 +366,7 @@ __device__ __forceinline__ void nodes_to_w(const Place<PP>& p, const double (&q)
         const double T = a.p * a.ir;
         int n;
         if (node_of<PP>(p, i, n)) {
+            n = node_lds<PP>(n);
             sh[n] = a.v[0];
             sh[FS + n] = a.v[1];
             sh[2 * FS + n] = a.v[2];
@@ -389,6 +417,7 @@ __device__ __forceinline__ void nodes_to_traces(const Place<PP>& p, Tab B, const
     for (int i = 0; i < L::NN; ++i) {
         int n;
         if (node_of<PP>(p, i, n)) {
+            n = node_lds<PP>(n);
             sh[n] = q[i][0];
             sh[FS + n] = q[i][4];
             sh[2 * FS + n] = q[i][1];
@@ -660,6 +689,7 @@ __device__ __forceinline__ void resid_group(const SolveDesc& S, int group, int t
     for (int i = 0; i < NN; ++i) {
         int n;
         const bool in = node_of<PP>(p, i, n);
+        n = node_lds<PP>(n);
         // the primitive values are formed again: kept from above they would
         // not fit the registers beside the faces' data
         pin(q[i][0]);
@@ -719,6 +749,7 @@ __device__ __forceinline__ void resid_group(const SolveDesc& S, int group, int t
     for (int i = 0; i < NN; ++i) {
         int n;
         node_of<PP>(p, i, n);
+        n = node_lds<PP>(n);
         R[i][0] = sh[n] + sh[4 * FS + n] + sh[8 * FS + n];
 #pragma unroll
         for (int a = 0; a < 3; ++a)
@@ -731,6 +762,7 @@ __device__ __forceinline__ void resid_group(const SolveDesc& S, int group, int t
     for (int i = 0; i < NN; ++i) {
         int n;
         node_of<PP>(p, i, n);
+        n = node_lds<PP>(n);
         R[i][4] = sh[n] + sh[FS + n] + sh[2 * FS + n];
 #pragma unroll
         for (int v = 0; v < 5; ++v) R[i][v] *= -ph.s;
