@@ -177,20 +177,24 @@ __global__ void __launch_bounds__(kRowThreads) k_grad_beside_net(SolveDesc S, Ne
     net256_forward<K0, ACT>(na, L::NP, T, e0, 0, bufA, bufB, ld, wave, lane, first);
 }
 
-template <int PP, int UPDATE, int VISC>
+// STREAM (see streams()): the groups in reverse, so that the launch begins
+// with what the BR1 pass left in the cache, and ends where the next begins.
+template <int PP, int UPDATE, int VISC, bool STREAM>
 __global__ void __launch_bounds__(Line<PP>::NT) __attribute__((amdgpu_waves_per_eu(line_waves<ResidLds<PP>, Line<PP>::NT>())))
 k_resid1(SolveDesc S, double rkA, double rkB, int first_stage) {
     __shared__ double sh[ResidLds<PP>::N];
-    resid_group<PP, UPDATE, VISC>(S, blockIdx.x, threadIdx.x, sh, rkA, rkB, first_stage);
+    const int group = STREAM ? gridDim.x - 1 - blockIdx.x : blockIdx.x;
+    resid_group<PP, UPDATE, VISC, STREAM>(S, group, threadIdx.x, sh, rkA, rkB, first_stage);
 }
 
 // the stage update of a list of solves, all with viscous fluxes
-template <int PP>
+template <int PP, bool STREAM>
 __global__ void __launch_bounds__(Line<PP>::NT) __attribute__((amdgpu_waves_per_eu(line_waves<ResidLds<PP>, Line<PP>::NT>())))
 k_resid(DescList dl, double rkA, double rkB, int first_stage) {
     __shared__ double sh[ResidLds<PP>::N];
-    const int si = find_solve(dl, blockIdx.x);
-    resid_group<PP, 1, 1>(*dl.d[si], blockIdx.x - dl.blk[si], threadIdx.x, sh, rkA, rkB, first_stage);
+    const int block = STREAM ? gridDim.x - 1 - blockIdx.x : blockIdx.x;
+    const int si = find_solve(dl, block);
+    resid_group<PP, 1, 1, STREAM>(*dl.d[si], block - dl.blk[si], threadIdx.x, sh, rkA, rkB, first_stage);
 }
 
 // Taylor-Green vortex initial condition, Eq. (11), on [0, L]^3.
@@ -575,11 +579,30 @@ hipError_t launch_grad_net(int PPv, const SolveDesc& S, const NetArgs& na, const
     return hipGetLastError();
 }
 
-template <int PP, int UPDATE>
+// Whether what a stage goes through (state, register, two sets of traces,
+// viscous fluxes) exceeds the 256 MB of the memory-side cache: then the
+// register is kept out of it, and the stage update takes the groups in
+// reverse.  A step, us, without -> with: 16^3 P=7 (356 MB) 446 -> 424, 16^3
+// P=8 605 -> 565, 20^3 P=5 392 -> 372, 24^3 P=6 1030 -> 974, 32^3 P=6 2389 ->
+// 2266; below, 24^3 P=3 (230 MB) 223 -> 234, 16^3 P=6 (253 MB) 298 -> 304.
+template <int PP>
+static bool streams(int E) {
+    using L = Line<PP>;
+    return (size_t)E * (2 * 5 * L::NP + 6 * (5 + 5 + 4) * L::NF) * sizeof(double) > ((size_t)256 << 20);
+}
+
+template <int PP, int UPDATE, int VISC>
 static void launch_resid1(const SolveDesc& S, double rkA, double rkB, int first_stage, hipStream_t st) {
     const dim3 grid(groups<PP>(S.E)), block(Line<PP>::NT);
-    if (S.ph.viscous) hipLaunchKernelGGL((k_resid1<PP, UPDATE, 1>), grid, block, 0, st, S, rkA, rkB, first_stage);
-    else hipLaunchKernelGGL((k_resid1<PP, UPDATE, 0>), grid, block, 0, st, S, rkA, rkB, first_stage);
+    if (UPDATE && streams<PP>(S.E))
+        hipLaunchKernelGGL((k_resid1<PP, UPDATE, VISC, UPDATE == 1>), grid, block, 0, st, S, rkA, rkB, first_stage);
+    else hipLaunchKernelGGL((k_resid1<PP, UPDATE, VISC, false>), grid, block, 0, st, S, rkA, rkB, first_stage);
+}
+
+template <int PP, int UPDATE>
+static void launch_resid1(const SolveDesc& S, double rkA, double rkB, int first_stage, hipStream_t st) {
+    if (S.ph.viscous) launch_resid1<PP, UPDATE, 1>(S, rkA, rkB, first_stage, st);
+    else launch_resid1<PP, UPDATE, 0>(S, rkA, rkB, first_stage, st);
 }
 
 hipError_t launch_resid(int PPv, int update, const SolveDesc& S, double rkA, double rkB, int first_stage,
@@ -594,8 +617,8 @@ hipError_t launch_resid(int PPv, int update, const SolveDesc& S, double rkA, dou
 
 hipError_t launch_resid(int PPv, const DescList& dl, double rkA, double rkB, int first_stage, hipStream_t st) {
     DG_DISPATCH_PP(PPv, const DescList g = in_groups<PP>(dl);
-                   hipLaunchKernelGGL(k_resid<PP>, dim3(g.blk[g.n]), dim3(Line<PP>::NT), 0, st, g, rkA, rkB,
-                                      first_stage));
+                   hipLaunchKernelGGL((streams<PP>(dl.blk[dl.n]) ? k_resid<PP, true> : k_resid<PP, false>),
+                                      dim3(g.blk[g.n]), dim3(Line<PP>::NT), 0, st, g, rkA, rkB, first_stage));
     return hipGetLastError();
 }
 

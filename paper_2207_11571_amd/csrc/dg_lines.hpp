@@ -342,7 +342,7 @@ __device__ __forceinline__ void load_ends(const Place<PP>& p, const double* tr, 
 // state of the thread's nodes: load, and w = (u, v, w, T) into the fields
 // 0 .. 7 of LDS as u, v, w, u, v, T, T, T (a line of axis d finds the velocity
 // of its frame at fields d .. d + 2, T at d + 5)
-template <int PP>
+template <int PP, bool STREAM = false>
 __device__ __forceinline__ void load_nodes(const Place<PP>& p, const double* f, size_t vs, double (&q)[Line<PP>::NN][5]) {
     using L = Line<PP>;
 #pragma unroll
@@ -351,7 +351,7 @@ __device__ __forceinline__ void load_nodes(const Place<PP>& p, const double* f, 
         node_of<PP>(p, i, n);
         const gdouble* g = gmem(f) + ((size_t)p.e0 * L::NP + n);
 #pragma unroll
-        for (int v = 0; v < 5; ++v) q[i][v] = g[v * vs];
+        for (int v = 0; v < 5; ++v) q[i][v] = STREAM ? __builtin_nontemporal_load(g + v * vs) : g[v * vs];
     }
 }
 
@@ -618,7 +618,9 @@ __device__ __forceinline__ NodeFlux node_flux(const double q[5], const double g[
 
 // Residual (out = p(q) + forcing), or Runge-Kutta stage (UPDATE: k <- A k +
 // dt R, q <- q + B k, the traces of the new q), of a group's elements.
-template <int PP, int UPDATE, int VISC>
+// STREAM: the register, which nothing else of a step reads, passes by the
+// caches.
+template <int PP, int UPDATE, int VISC, bool STREAM = false>
 __device__ __forceinline__ void resid_group(const SolveDesc& S, int group, int t, double* sh, double rkA, double rkB,
                                             int first_stage) {
     using L = Line<PP>;
@@ -717,7 +719,7 @@ __device__ __forceinline__ void resid_group(const SolveDesc& S, int group, int t
         }
     }
     // the Runge-Kutta register, in flight until the update
-    if (UPDATE && !first_stage) load_nodes<PP>(p, S.k, vs, k);
+    if (UPDATE && !first_stage) load_nodes<PP, STREAM>(p, S.k, vs, k);
     sched_fence();
     group_sync<PP>();
     double o[5][PP];
@@ -810,7 +812,8 @@ __device__ __forceinline__ void resid_group(const SolveDesc& S, int group, int t
                 const size_t at = (size_t)p.e0 * L::NP + n;
 #pragma unroll
                 for (int v = 0; v < 5; ++v) {
-                    kg[at + v * vs] = k[i][v];
+                    if constexpr (STREAM) __builtin_nontemporal_store(k[i][v], kg + at + v * vs);
+                    else kg[at + v * vs] = k[i][v];
                     qg[at + v * vs] = q[i][v];
                 }
             }

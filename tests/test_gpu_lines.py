@@ -133,3 +133,27 @@ def test_training_rows(B, batch, n_p, momenta, hidden):
         eW = np.linalg.norm(gW - rW) / np.linalg.norm(rW)
         eb = np.linalg.norm(gb - rb) / np.linalg.norm(rb)
         assert eW < 1e-2 and eb < 1e-2, (eW, eb)
+
+
+@pytest.mark.parametrize("N,P,viscous", [(13, 8, True), (14, 8, True), (27, 3, False)])
+def test_stage_update_past_the_cache(B, N, P, viscous):
+    """A step on both sides of 256 MB of stage data (236, 295 and 298 MB)
+    against the same stages put together from the residual, on the GPU.
+    Float64 on both sides in other rounding orders: 32 eps of what the
+    divergence sums, fluxes of up to 2 E times the derivative's (N / pi) PP^2."""
+    say("stage update past the cache", N, P, viscous)
+    m = B.Mesh(N, P, 200.0, viscous=viscous)
+    q, k, r = m.field(), m.field(0.0), m.field()
+    B.dg_init_tgv(m, q)
+    ref, reg = q.clone(), torch.zeros_like(q)
+    dt = 1e-4
+    for A, w in ((0.0, 1 / 3), (-5 / 9, 15 / 16), (-153 / 128, 8 / 15)):
+        B.dg_residual(m, ref, r)
+        reg = A * reg + dt * r
+        ref += w * reg
+    B.dg_rk_step(m, q, k, dt, 1)
+    eps = np.finfo(float).eps
+    tol = 32 * eps * dt * 2 * float(ref[4].abs().max()) * (N / np.pi) * (P + 1) ** 2
+    for v in range(5):
+        assert float((k[v] - reg[v]).abs().max()) <= tol
+        assert float((q[v] - ref[v]).abs().max()) <= tol + 8 * eps * float(ref[v].abs().max())
