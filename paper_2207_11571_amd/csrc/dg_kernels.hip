@@ -223,24 +223,55 @@ __global__ void __launch_bounds__(768) k_tgv(Phys ph, int N, double* __restrict_
     q[4 * vs + n] = p / ph.gm1 + 0.5 * (u * u + v * v);
 }
 
-// Per-element partial diagnostics: KE integrand sum, max(|v| + c), min rho,
-// integrals of the five conserved variables (quadrature-weighted).  Fixed
-// reduction order, so the result is bitwise reproducible.
+// Reduction of eight values over 256 threads, in an order that depends on
+// nothing but the thread numbers: value 1 by maximum, 2 by minimum, the others
+// by sum.  In LDS red[c][x]; thread 32 c returns value c.
+constexpr int kReduceRow = 257;   // row stride of red: the writers of one x use different banks
+__device__ __forceinline__ double diag_join(int c, double a, double b) {
+    return c == 1 ? fmax(a, b) : (c == 2 ? fmin(a, b) : a + b);
+}
+template <int COUNT>
+__device__ __forceinline__ double reduce_rows(const double (&red)[8][kReduceRow], int t) {
+    const int c = t >> 5, x = t & 31;
+    double r = red[c][x];
+#pragma unroll
+    for (int i = 1; i < COUNT / 32; ++i) r = diag_join(c, r, red[c][x + 32 * i]);
+#pragma unroll
+    for (int w = 16; w > 0; w >>= 1) r = diag_join(c, r, __shfl_xor(r, w));
+    return r;
+}
+
+// Diagnostics, first launch: per block the kinetic-energy integrand's sum,
+// max(|v| + c), min rho, and the integrals of the five conserved variables
+// (quadrature-weighted) of the nodes it strides over.  Bound by its launch on
+// small meshes and by reading the state on large ones; a fixed number of
+// blocks, at most kDiagBlocks, so that the second launch stays short.  The
+// launches take, with a block per element and a third launch for the mean ->
+// so: 4^3 P=3 8.4 -> 6.5 us, 8^3 P=6 10.0 -> 9.8 and a launch gap, 16^3 P=6
+// 25 -> 17.5, 32^3 P=6 160 -> 86 (450 MB).
+constexpr int kDiagBlocks = 512;
+static int diag_blocks(int E, int NP) {
+    const size_t b = ((size_t)E * NP + 255) / 256;
+    const size_t most = E < kDiagBlocks ? E : kDiagBlocks;   // the workspace holds a row an element
+    return (int)(b < most ? b : most);
+}
+
 template <int PP>
 __global__ void __launch_bounds__(256) k_diag_partial(Phys ph, int E, const double* __restrict__ q,
                                                      double* __restrict__ part) {
     constexpr int NP = PP * PP * PP;
-    __shared__ double red[8][256];
-    const int e = blockIdx.x;
+    __shared__ double red[8][kReduceRow];
     const int t = threadIdx.x;
     const BasisTab& B = c_basis[PP - 2];
     double val[8] = {0.0, 0.0, 1e300, 0.0, 0.0, 0.0, 0.0, 0.0};
-    const size_t vs = (size_t)E * NP;
-    for (int n = t; n < NP; n += 256) {
-        const int i = n % PP, j = (n / PP) % PP, k = n / (PP * PP);
+    const size_t vs = (size_t)E * NP, step = (size_t)gridDim.x * 256;
+    const int advance = (int)(step % NP);
+    int m = (int)(((size_t)blockIdx.x * 256 + t) % NP);   // node of the element
+    for (size_t n = (size_t)blockIdx.x * 256 + t; n < vs; n += step, m = m + advance < NP ? m + advance : m + advance - NP) {
+        const int i = m % PP, j = (m / PP) % PP, k = m / (PP * PP);
         const double wq = B.w[i] * B.w[j] * B.w[k];
         double qq[5];
-        for (int v = 0; v < 5; ++v) qq[v] = q[v * vs + (size_t)e * NP + n];
+        for (int v = 0; v < 5; ++v) qq[v] = q[v * vs + n];
         const double ir = 1.0 / qq[0];
         const double m2 = qq[1] * qq[1] + qq[2] * qq[2] + qq[3] * qq[3];
         val[0] += wq * 0.5 * m2 * ir;
@@ -251,91 +282,66 @@ __global__ void __launch_bounds__(256) k_diag_partial(Phys ph, int E, const doub
     }
     for (int c = 0; c < 8; ++c) red[c][t] = val[c];
     __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if (t < w) {
-            red[0][t] += red[0][t + w];
-            red[1][t] = fmax(red[1][t], red[1][t + w]);
-            red[2][t] = fmin(red[2][t], red[2][t + w]);
-            for (int c = 3; c < 8; ++c) red[c][t] += red[c][t + w];
-        }
-        __syncthreads();
-    }
-    if (t < 8) part[(size_t)e * 8 + t] = red[t][0];
+    const double r = reduce_rows<256>(red, t);
+    if ((t & 31) == 0) part[(size_t)blockIdx.x * 8 + (t >> 5)] = r;
 }
 
-__global__ void __launch_bounds__(256) k_diag_final(int E, double vol_factor, const double* __restrict__ part,
-                                                   double* __restrict__ out) {
-    __shared__ double red[8][256];
-    const int t = threadIdx.x;
-    double val[8] = {0.0, 0.0, 1e300, 0.0, 0.0, 0.0, 0.0, 0.0};
-    for (int e = t; e < E; e += 256) {
-        const double* p = part + (size_t)e * 8;
-        val[0] += p[0];
-        val[1] = fmax(val[1], p[1]);
-        val[2] = fmin(val[2], p[2]);
-        for (int c = 3; c < 8; ++c) val[c] += p[c];
+// Second launch, one block: the rows of the first, times the Jacobian
+// (integrals) or its share of the volume (the mean kinetic energy).
+__global__ void __launch_bounds__(256) k_diag_final(int rows, double mean_factor, double vol_factor,
+                                                   const double* __restrict__ part, double* __restrict__ out) {
+    __shared__ double red[8][kReduceRow];
+    const int t = threadIdx.x, c = t & 7;
+    // eight loads in flight; past the last row, the last once more, not joined
+    double r = c == 2 ? 1e300 : 0.0;
+    for (int x0 = t >> 3; x0 < rows; x0 += 256) {
+        double v[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const int x = x0 + 32 * i;
+            v[i] = part[(x < rows ? x : rows - 1) * 8 + c];
+        }
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+            if (x0 + 32 * i < rows) r = diag_join(c, r, v[i]);
     }
-    for (int c = 0; c < 8; ++c) red[c][t] = val[c];
+    red[c][t >> 3] = r;
     __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if (t < w) {
-            red[0][t] += red[0][t + w];
-            red[1][t] = fmax(red[1][t], red[1][t + w]);
-            red[2][t] = fmin(red[2][t], red[2][t + w]);
-            for (int c = 3; c < 8; ++c) red[c][t] += red[c][t + w];
-        }
-        __syncthreads();
-    }
-    if (t == 0) {
-        // vol_factor = J: integrals; KE is the volume mean, J / L^3 folded in by the caller
-        out[0] = red[0][0];
-        out[1] = red[1][0];
-        out[2] = red[2][0];
-        for (int c = 3; c < 8; ++c) out[c] = red[c][0] * vol_factor;
-    }
+    r = reduce_rows<32>(red, t);
+    const int o = t >> 5;
+    if ((t & 31) == 0) out[o] = o == 0 ? r * mean_factor : (o < 3 ? r : r * vol_factor);
 }
 
-__global__ void k_scale(double* p, double f) {
-    if (threadIdx.x == 0) p[0] *= f;
-}
-
-// Eq. (9): per-element max |q_v - qref_v| for the three momenta
-__global__ void __launch_bounds__(256) k_err_partial(int E, int NP, const double* __restrict__ q,
+// Eq. (9): max |q_v - qref_v| of the three momenta, per block (rows of four)
+__global__ void __launch_bounds__(256) k_err_partial(size_t vs, const double* __restrict__ q,
                                                     const double* __restrict__ qr, double* __restrict__ part) {
-    __shared__ double red[3][256];
-    const int e = blockIdx.x;
+    __shared__ double red[4][3];
     const int t = threadIdx.x;
     double m[3] = {0.0, 0.0, 0.0};
-    const size_t vs = (size_t)E * NP;
-    for (int n = t; n < NP; n += 256)
+    const size_t step = (size_t)gridDim.x * 256;
+    for (size_t n = (size_t)blockIdx.x * 256 + t; n < vs; n += step)
         for (int c = 0; c < 3; ++c) {
-            const size_t idx = (1 + c) * vs + (size_t)e * NP + n;
+            const size_t idx = (1 + c) * vs + n;
             m[c] = fmax(m[c], fabs(q[idx] - qr[idx]));
         }
-    for (int c = 0; c < 3; ++c) red[c][t] = m[c];
+    for (int c = 0; c < 3; ++c)
+        for (int w = 32; w > 0; w >>= 1) m[c] = fmax(m[c], __shfl_xor(m[c], w));
+    if ((t & 63) == 0)
+        for (int c = 0; c < 3; ++c) red[t >> 6][c] = m[c];
     __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if (t < w)
-            for (int c = 0; c < 3; ++c) red[c][t] = fmax(red[c][t], red[c][t + w]);
-        __syncthreads();
-    }
-    if (t < 3) part[(size_t)e * 3 + t] = red[t][0];
+    if (t < 3) part[(size_t)blockIdx.x * 4 + t] = fmax(fmax(red[0][t], red[1][t]), fmax(red[2][t], red[3][t]));
 }
 
-__global__ void __launch_bounds__(256) k_err_final(int E, const double* __restrict__ part, double* __restrict__ out) {
-    __shared__ double red[3][256];
+__global__ void __launch_bounds__(256) k_err_final(int rows, const double* __restrict__ part, double* __restrict__ out) {
+    __shared__ double red[4][4];
     const int t = threadIdx.x;
-    double m[3] = {0.0, 0.0, 0.0};
-    for (int e = t; e < E; e += 256)
-        for (int c = 0; c < 3; ++c) m[c] = fmax(m[c], part[(size_t)e * 3 + c]);
-    for (int c = 0; c < 3; ++c) red[c][t] = m[c];
+    double m = 0.0;
+    if ((t & 3) < 3)
+        for (int x = t; x < rows * 4; x += 256) m = fmax(m, part[x]);
+    for (int w = 32; w > 3; w >>= 1) m = fmax(m, __shfl_xor(m, w));
+    if ((t & 63) < 4) red[t >> 6][t & 3] = m;
     __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if (t < w)
-            for (int c = 0; c < 3; ++c) red[c][t] = fmax(red[c][t], red[c][t + w]);
-        __syncthreads();
-    }
-    if (t < 3) out[t] = red[t][0];
+    if (t < 3) out[t] = fmax(fmax(red[0][t], red[1][t]), fmax(red[2][t], red[3][t]));
 }
 
 // Filter G: tensor-product 1D projection, one element per block, five variables.
@@ -630,18 +636,19 @@ hipError_t launch_tgv(int PPv, const Phys& ph, int N, double* q, hipStream_t st)
 hipError_t launch_diag(int PPv, const Phys& ph, int N, const double* q, double* partial, double* out,
                        hipStream_t st) {
     const int E = N * N * N;
-    DG_DISPATCH_PP(PPv, hipLaunchKernelGGL(k_diag_partial<PP>, dim3(E), dim3(256), 0, st, ph, E, q, partial));
+    const int blocks = diag_blocks(E, PPv * PPv * PPv);
+    DG_DISPATCH_PP(PPv, hipLaunchKernelGGL(k_diag_partial<PP>, dim3(blocks), dim3(256), 0, st, ph, E, q, partial));
     const double J = (ph.h * 0.5) * (ph.h * 0.5) * (ph.h * 0.5);
-    hipLaunchKernelGGL(k_diag_final, dim3(1), dim3(256), 0, st, E, J, partial, out);
-    hipLaunchKernelGGL(k_scale, dim3(1), dim3(64), 0, st, out, J / (ph.L * ph.L * ph.L));
+    hipLaunchKernelGGL(k_diag_final, dim3(1), dim3(256), 0, st, blocks, J / (ph.L * ph.L * ph.L), J, partial, out);
     return hipGetLastError();
 }
 
 hipError_t launch_err_inf(int PPv, int E, const double* q, const double* qref, double* partial, double* out,
                           hipStream_t st) {
     const int NP = PPv * PPv * PPv;
-    hipLaunchKernelGGL(k_err_partial, dim3(E), dim3(256), 0, st, E, NP, q, qref, partial);
-    hipLaunchKernelGGL(k_err_final, dim3(1), dim3(256), 0, st, E, partial, out);
+    const int blocks = diag_blocks(E, NP);
+    hipLaunchKernelGGL(k_err_partial, dim3(blocks), dim3(256), 0, st, (size_t)E * NP, q, qref, partial);
+    hipLaunchKernelGGL(k_err_final, dim3(1), dim3(256), 0, st, blocks, partial, out);
     return hipGetLastError();
 }
 

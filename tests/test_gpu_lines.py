@@ -157,3 +157,35 @@ def test_stage_update_past_the_cache(B, N, P, viscous):
     for v in range(5):
         assert float((k[v] - reg[v]).abs().max()) <= tol
         assert float((q[v] - ref[v]).abs().max()) <= tol + 8 * eps * float(ref[v].abs().max())
+
+
+# one block and fewer nodes than it has threads, as many blocks as elements,
+# several nodes a thread with an element's node count that does not divide
+# the stride
+@pytest.mark.parametrize("N,P", [(1, 1), (2, 8), (3, 2), (9, 6), (15, 7)])
+def test_diagnostics_over_blocks(B, N, P):
+    """Diagnostics and error norm against torch in float64: sums of up to
+    1.7 million terms in another order (1e-12 relative; momenta, which
+    cancel, relative to the sum of their absolute values), maxima of the
+    same numbers, a reciprocal in place of quotients (8 eps)."""
+    from oracle import basis
+    say("diagnostics over blocks", N, P)
+    m = B.Mesh(N, P, 100.0)
+    q0 = synthetic.random_state(N, P, seed=70 + P, momentum=0.3)
+    q1 = synthetic.random_state(N, P, seed=71 + P, momentum=0.3)
+    q, r = (torch.from_numpy(x).cuda() for x in (q0, q1))
+    d = B.dg_diagnostics(m, q).cpu().numpy()
+    err = torch.full((3,), float("nan"), dtype=torch.float64, device="cuda")
+    B.dg_error_inf(m, q, r, err)
+    _, w = basis.gauss_legendre(P)
+    x = q0.reshape(5, N ** 3, -1)
+    wq = np.einsum("k,j,i->kji", w, w, w).ravel() * (np.pi / N) ** 3
+    m2 = x[1] ** 2 + x[2] ** 2 + x[3] ** 2
+    pr = 0.4 * (x[4] - 0.5 * m2 / x[0])
+    eps = np.finfo(float).eps
+    assert abs(d[0] - (wq * 0.5 * m2 / x[0]).sum() / (2 * np.pi) ** 3) <= 1e-12 * d[0]
+    assert abs(d[1] - (np.sqrt(m2) / x[0] + np.sqrt(1.4 * pr / x[0])).max()) <= 8 * eps * d[1]
+    assert d[2] == x[0].min()
+    for v in range(5):
+        assert abs(d[3 + v] - (wq * x[v]).sum()) <= 1e-12 * (wq * np.abs(x[v])).sum()
+    assert np.array_equal(err.cpu().numpy(), np.abs(x - q1.reshape(5, N ** 3, -1))[1:4].reshape(3, -1).max(axis=1))
