@@ -234,16 +234,6 @@ static int check_ws(const Mesh& m, const void* ws, size_t ws_bytes) {
 
 static bool aligned8(const void* p) { return (((uintptr_t)p) & 7) == 0; }
 
-DescList single_list(const SolveDesc* d, int E) {
-    DescList dl;
-    std::memset(&dl, 0, sizeof(dl));
-    dl.d[0] = d;
-    dl.blk[0] = 0;
-    dl.blk[1] = E;
-    dl.n = 1;
-    return dl;
-}
-
 // ----------------------------------------------------------------- internal API used by server/nn
 
 int residual_impl(const Mesh& m, const double* q, double* dqdt, char* ws, hipStream_t st) {

@@ -74,21 +74,14 @@ namespace dgnn {
 
 // ---------------------------------------------------------------- kernels
 //
-// Each stage kernel exists twice: for one solve with its descriptor in the
+// k_grad and k_resid exist twice: for one solve with its descriptor in the
 // kernel arguments (two dependent loads fewer before a block's first data
 // load), and for a list of solves whose descriptors are in device memory.
 
 template <int PP>
-__global__ void __launch_bounds__(Line<PP>::NT) k_traces1(SolveDesc S) {
+__global__ void __launch_bounds__(Line<PP>::NT) k_traces(SolveDesc S) {
     __shared__ double sh[7 * Line<PP>::FS];
     traces_group<PP>(S, blockIdx.x, threadIdx.x, sh);
-}
-
-template <int PP>
-__global__ void __launch_bounds__(Line<PP>::NT) k_traces(DescList dl) {
-    __shared__ double sh[7 * Line<PP>::FS];
-    const int si = find_solve(dl, blockIdx.x);
-    traces_group<PP>(*dl.d[si], blockIdx.x - dl.blk[si], threadIdx.x, sh);
 }
 
 template <int PP>
@@ -488,13 +481,7 @@ static DescList in_groups(const DescList& dl) {
 }
 
 hipError_t launch_traces(int PPv, const SolveDesc& S, hipStream_t st) {
-    DG_DISPATCH_PP(PPv, hipLaunchKernelGGL(k_traces1<PP>, dim3(groups<PP>(S.E)), dim3(Line<PP>::NT), 0, st, S));
-    return hipGetLastError();
-}
-
-hipError_t launch_traces(int PPv, const DescList& dl, hipStream_t st) {
-    DG_DISPATCH_PP(PPv, const DescList g = in_groups<PP>(dl);
-                   hipLaunchKernelGGL(k_traces<PP>, dim3(g.blk[g.n]), dim3(Line<PP>::NT), 0, st, g));
+    DG_DISPATCH_PP(PPv, hipLaunchKernelGGL(k_traces<PP>, dim3(groups<PP>(S.E)), dim3(Line<PP>::NT), 0, st, S));
     return hipGetLastError();
 }
 

@@ -154,7 +154,6 @@ hipError_t scratch_setup(int dev);
 void* scratch_device_ptr(int dev);
 hipError_t launch_write_descs(const SolveDesc* host, int n, SolveDesc* dev, hipStream_t st);
 hipError_t launch_traces(int PP, const SolveDesc& S, hipStream_t st);
-hipError_t launch_traces(int PP, const DescList& dl, hipStream_t st);
 // compute units of the current device
 int cu_count();
 hipError_t launch_grad(int PP, const SolveDesc& S, hipStream_t st);
@@ -260,7 +259,6 @@ int set_error(int code, const char* fmt, ...);
 extern const double kRkA[3];
 extern const double kRkB[3];
 int make_mesh(const dg_params* prm, Mesh& M);
-DescList single_list(const SolveDesc* d, int E);
 int residual_impl(const Mesh& m, const double* q, double* dqdt, char* ws, hipStream_t st);
 int diag_impl(const Mesh& m, const double* q, double* out_dev, char* ws, hipStream_t st);
 int project_impl(const Mesh& src, const Mesh& dst, const double* f_src, double* f_dst, hipStream_t st);

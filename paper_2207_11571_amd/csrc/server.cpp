@@ -5,18 +5,22 @@
 // face-trace / interface-flux / forcing workspace, descriptors, a device ring
 // of kinetic-energy records).  Admitted solves stay resident until done.
 //
-// Execution: one host thread, one stream per polynomial order.  Each round it
-// admits what fits, then advances every running solve by a number of
-// Runge-Kutta steps sized to its order group's cost; within a step, the
-// stages of all running solves of the same order run in shared launches (one
-// k_grad, one batched network launch for the corrected solves, one k_resid
-// per stage) on that order's stream, and the groups of different orders
-// overlap on the device.  Requests that arrive while others run join them at
-// the next round.  Per-solve time steps and step counts are independent;
-// nothing is reduced across solves, so each result is what the solve computes
-// alone.  After each round the stream is synchronised once: kinetic-energy
-// records are collected, non-finite solves are failed, finished solves are
-// copied out and their arena blocks released.
+// Execution: one host thread and one stream per polynomial order, started with
+// the first request of the order.  Each round a thread sets up the admitted
+// solves of its order, then advances all it runs by a number of Runge-Kutta
+// steps; within a step, the stages of all its solves run in shared launches
+// (one k_grad, one batched network launch for the corrected solves, one
+// k_resid per stage).  Orders neither wait for each other's rounds nor for
+// each other's launches, and overlap on the device.  Requests that arrive
+// while others run join them at their order's next round.  Per-solve time
+// steps and step counts are independent; nothing is reduced across solves, so
+// each result is what the solve computes alone.  After each round the stream
+// is synchronised once: kinetic-energy records are collected, non-finite
+// solves are failed.  Finished solves are copied out, and their arena blocks
+// released, while the next round runs.
+// (Two corrected P=3, two P=6 and two P=8 solves on 4^3, one of each on 8^3:
+// 9.0 ms with one thread for all orders, whose rounds waited for the slowest
+// order and for the copies, 3.9 so.)
 //
 // Fallback of the learned part: a corrected solve (network forcing, Eq. (4),
 // or Algorithm 1's correction) keeps a copy of its state from the start of
@@ -35,6 +39,7 @@
 #include <condition_variable>
 #include <cstring>
 #include <deque>
+#include <future>
 #include <map>
 #include <memory>
 #include <mutex>
@@ -46,9 +51,14 @@
 namespace dgnn {
 
 constexpr int kHist = 64;    // device KE records per solve between synchronisations
-constexpr int kChunk = 16;   // steps per round of the costliest order group
-constexpr int kChunkMax = 256;  // steps per round of any group
+constexpr int kChunk = 16;   // steps per round of the costliest solve of an order
+constexpr int kChunkMax = 256;  // steps per round of any solve
 constexpr size_t kDiagDoubles = 8;
+// finished states go out in chunks, by way of pinned memory: a copy straight
+// to pageable memory goes through the runtime's own, one piece after the
+// other (15 MB: 0.97 ms to memory that was written before, 1.9 ms to new)
+constexpr size_t kStageChunk = 2 << 20;
+constexpr int kStageSlots = 4;
 constexpr double kFallbackKeRise = 1e-3;   // relative kinetic-energy rise that ends the correction
 
 static double now_s() {
@@ -164,6 +174,25 @@ class Arena {
 
 using namespace dgnn;
 
+namespace dgnn {
+
+// the thread of one order
+struct Worker {
+    int PP = 0;
+    std::thread th;
+    std::vector<Solve*> inbox;   // admitted, not yet set up (under the server's lock)
+    hipStream_t st = nullptr;
+    double* records = nullptr;   // pinned: records read back at the end of a round
+    size_t records_for = 0;      // solves it has room for
+    char* stage = nullptr;       // pinned: kStageSlots chunks of states on their way out
+};
+
+// per solve in Worker::records: a round's kinetic-energy records, then the
+// health record
+constexpr size_t kRecords = (kHist + 1) * kDiagDoubles;
+
+}  // namespace dgnn
+
 struct solve_server {
     char* base = nullptr;
     size_t bytes = 0;
@@ -173,32 +202,75 @@ struct solve_server {
     std::condition_variable cv;
     std::map<uint64_t, std::unique_ptr<Solve>> solves;
     std::deque<Solve*> queue;
-    std::vector<Solve*> running;
+    int running = 0;             // admitted, not done
     uint64_t next_id = 1;
     bool stop = false;
-    std::thread th;
-    hipStream_t st = nullptr;                 // admission work
-    hipStream_t gst[dgnn::kMaxPP + 1] = {};   // one stream per order group
+    Worker workers[dgnn::kMaxPP + 1];
     Arena arena;
-    double busy = 0.0;
+    double busy = 0.0;           // time in which some order had a round running
+    int in_round = 0;
+    double round_t0 = 0.0;
     int64_t batches = 0;
-    double* pinned = nullptr;
 };
 
 namespace dgnn {
 
-static void fail(solve_server* S, Solve* s, int code) {
-    std::lock_guard<std::mutex> lk(S->mu);
-    s->state = SOLVE_FAILED;
-    s->error = code;
-    s->t_done = now_s();
-    S->arena.release(s->off, s->bytes);
+// hands queued requests, in their order, to the threads of their orders while
+// slots are free; one that finds no room in the arena lets later ones pass
+// (lock held)
+static void admit_waiting(solve_server* S) {
+    for (auto it = S->queue.begin(); it != S->queue.end() && S->running < S->max_slots;) {
+        Solve* s = *it;
+        size_t off;
+        if (!S->arena.alloc(s->bytes, off)) {
+            ++it;
+            continue;
+        }
+        s->off = off;
+        s->state = SOLVE_RUNNING;
+        s->t_admit = now_s();
+        ++S->running;
+        S->workers[s->mesh.PP].inbox.push_back(s);
+        it = S->queue.erase(it);
+    }
 }
 
-static int write_descs(solve_server* S, Solve* s);
+// ends a solve: its state, and its room for others
+static void leave(solve_server* S, Solve* s, int state, int code) {
+    {
+        std::lock_guard<std::mutex> lk(S->mu);
+        s->state = state;
+        s->error = code;
+        s->t_done = now_s();
+        S->arena.release(s->off, s->bytes);
+        --S->running;
+        admit_waiting(S);
+    }
+    S->cv.notify_all();
+}
 
-// set up one admitted solve: pointers, TGV state, dt, descriptors, traces
-static int admit_one(solve_server* S, Solve* s) {
+static void fail(solve_server* S, Solve* s, int code) { leave(S, s, SOLVE_FAILED, code); }
+
+static int reserve_records(Worker& W, size_t solves) {
+    if (solves <= W.records_for) return DG_OK;
+    if (W.records) (void)hipHostFree(W.records);
+    W.records = nullptr;
+    W.records_for = 0;
+    const size_t n = std::max<size_t>(16, 2 * solves);
+    if (hipHostMalloc((void**)&W.records, n * kRecords * sizeof(double), hipHostMallocDefault) != hipSuccess) {
+        W.records = nullptr;
+        return set_error(DG_EHIP, "pinned buffer allocation failed");
+    }
+    W.records_for = n;
+    return DG_OK;
+}
+
+static int write_descs(Solve* s, hipStream_t st);
+static void stage_desc(const Solve* s, int par, SolveDesc& d);
+
+// admitted solves, first half: pointers, TGV state, its traces and
+// diagnostics (which are also the record at t = 0), on their way back
+static int admit_begin(solve_server* S, Worker& W, Solve* s, double* rec) {
     const dg_params prm = request_params(s->req);
     int rc = make_mesh(&prm, s->mesh);
     if (rc) return rc;
@@ -212,61 +284,85 @@ static int admit_one(solve_server* S, Solve* s) {
     s->health = (double*)(p + f.health);
     s->ckpt = s->req.use_nn ? (double*)(p + f.ckpt) : nullptr;
     s->nn_active = s->req.use_nn != 0;
-    if ((rc = init_tgv_impl(s->mesh, s->q, S->st))) return rc;
-    double* dout = s->hist;   // scratch for the time-step diagnostics
-    if ((rc = diag_impl(s->mesh, s->q, dout, s->ws, S->st))) return rc;
-    double h[kDiagDoubles];
-    if (hipMemcpyAsync(h, dout, sizeof(h), hipMemcpyDeviceToHost, S->st) != hipSuccess ||
-        hipStreamSynchronize(S->st) != hipSuccess)
+    if ((rc = init_tgv_impl(s->mesh, s->q, W.st))) return rc;
+    if ((rc = diag_impl(s->mesh, s->q, s->hist, s->ws, W.st))) return rc;
+    if (hipMemcpyAsync(rec, s->hist, kDiagDoubles * sizeof(double), hipMemcpyDeviceToHost, W.st) != hipSuccess)
         return set_error(DG_EHIP, "admission readback failed");
-    const double dt0 = stable_dt_from_diag(s->mesh, h, 0.4);
+    SolveDesc d;
+    stage_desc(s, 1, d);
+    if (launch_traces(s->mesh.PP, d, W.st) != hipSuccess) return set_error(DG_EHIP, "trace launch failed");
+    return DG_OK;
+}
+
+// second half, with the diagnostics: time step and stage descriptors
+static int admit_end(solve_server* S, Worker& W, Solve* s, const double* rec) {
+    const double dt0 = stable_dt_from_diag(s->mesh, rec, 0.4);
     if (!(dt0 > 0) || !std::isfinite(dt0)) return set_error(DG_ENONFINITE, "bad initial state");
-    s->ke0 = h[0];
-    s->n_steps = (int64_t)std::ceil(s->req.t_end / dt0 - 1e-12);
-    if (s->n_steps < 1) s->n_steps = 1;
-    s->dt = s->req.t_end / s->n_steps;
-    if ((rc = write_descs(S, s))) return rc;
-    if (launch_traces(s->mesh.PP, single_list(s->ddesc + 1, s->mesh.E), S->st) != hipSuccess)
-        return set_error(DG_EHIP, "trace launch failed");
-    // record KE(0)
-    if ((rc = diag_impl(s->mesh, s->q, s->hist, s->ws, S->st))) return rc;
-    if (hipStreamSynchronize(S->st) != hipSuccess) return set_error(DG_EHIP, "admission synchronise failed");
+    s->ke0 = rec[0];
+    {
+        std::lock_guard<std::mutex> lk(S->mu);
+        s->n_steps = (int64_t)std::ceil(s->req.t_end / dt0 - 1e-12);
+        if (s->n_steps < 1) s->n_steps = 1;
+        s->dt = s->req.t_end / s->n_steps;
+    }
     s->pending_t.push_back(0.0);
     s->par = 0;
     s->steps = 0;
-    return DG_OK;
+    return write_descs(s, W.st);
+}
+
+// sets up the admitted solves, with one wait for all of them, and moves those
+// that can run to `run`
+static void admit(solve_server* S, Worker& W, std::vector<Solve*>& admitted, std::vector<Solve*>& run) {
+    if (admitted.empty()) return;
+    std::vector<int> rc(admitted.size(), DG_OK);
+    const int all = reserve_records(W, admitted.size());
+    for (size_t i = 0; i < admitted.size(); ++i)
+        rc[i] = all ? all : admit_begin(S, W, admitted[i], W.records + i * kRecords);
+    const bool back = hipStreamSynchronize(W.st) == hipSuccess;
+    for (size_t i = 0; i < admitted.size(); ++i) {
+        if (!rc[i] && !back) rc[i] = set_error(DG_EHIP, "admission synchronise failed");
+        if (!rc[i]) rc[i] = admit_end(S, W, admitted[i], W.records + i * kRecords);
+        if (rc[i]) fail(S, admitted[i], rc[i]);
+        else run.push_back(admitted[i]);
+    }
+    admitted.clear();
+}
+
+// the stage descriptor of a solve that reads traces `par`
+static void stage_desc(const Solve* s, int par, SolveDesc& d) {
+    const WsLayout L = ws_layout(s->mesh);
+    std::memset(&d, 0, sizeof(SolveDesc));
+    d.q = s->q;
+    d.k = s->k;
+    d.qtr_in = (const double*)(s->ws + (par == 0 ? L.qtr0 : L.qtr1));
+    d.qtr_out = (double*)(s->ws + (par == 0 ? L.qtr1 : L.qtr0));
+    d.fv = (double*)(s->ws + L.fv);
+    d.N = s->mesh.N;
+    d.E = s->mesh.E;
+    d.dt = s->dt;
+    d.ph = s->mesh.ph;
 }
 
 // the four stage descriptors of a solve, with the correction while it is
 // active: d[par] the stages, d[2 + par] the last stage of a step corrected
 // after the step (Algorithm 1), whose update adds dt s(q^n)
-static int write_descs(solve_server* S, Solve* s) {
-    const WsLayout L = ws_layout(s->mesh);
+static int write_descs(Solve* s, hipStream_t st) {
     const bool post = s->nn_active && s->req.nn_after_step;
-    const double* fbuf = s->nn_active ? (const double*)(s->ws + L.forcing) : nullptr;
+    const double* fbuf = s->nn_active ? (const double*)(s->ws + ws_layout(s->mesh).forcing) : nullptr;
     SolveDesc d[4];
     for (int p = 0; p < 4; ++p) {
-        const int par = p & 1;
-        std::memset(&d[p], 0, sizeof(SolveDesc));
-        d[p].q = s->q;
-        d[p].k = s->k;
+        stage_desc(s, p & 1, d[p]);
         d[p].forcing = post ? nullptr : fbuf;
         d[p].post = (post && p >= 2) ? fbuf : nullptr;
-        d[p].qtr_in = (const double*)(s->ws + (par == 0 ? L.qtr0 : L.qtr1));
-        d[p].qtr_out = (double*)(s->ws + (par == 0 ? L.qtr1 : L.qtr0));
-        d[p].fv = (double*)(s->ws + L.fv);
-        d[p].N = s->mesh.N;
-        d[p].E = s->mesh.E;
-        d[p].dt = s->dt;
-        d[p].ph = s->mesh.ph;
     }
-    if (launch_write_descs(d, 4, s->ddesc, S->st) != hipSuccess) return set_error(DG_EHIP, "descriptor upload failed");
+    if (launch_write_descs(d, 4, s->ddesc, st) != hipSuccess) return set_error(DG_EHIP, "descriptor upload failed");
     return DG_OK;
 }
 
-// one Runge-Kutta step of every solve of one order group, stages batched,
-// enqueued on the group's stream
-static int step_group(solve_server* S, int PP, std::vector<Solve*>& v, hipStream_t st) {
+// one Runge-Kutta step of solves of one order, stages batched, enqueued on the
+// order's stream
+static int step_group(int PP, std::vector<Solve*>& v, hipStream_t st) {
     for (Solve* s : v)
         if (s->inject) {
             static const double nan_val = std::nan("");
@@ -331,38 +427,22 @@ static double step_cost(const Solve* s) {
     return (double)s->mesh.E * s->mesh.n_p * (s->nn_active ? (s->req.nn_after_step ? 1.3 : 2.0) : 1.0);
 }
 
-// Steps of one round for each running solve.  Per order group, the group's
-// costliest solve takes n_g steps, where the costliest group (by summed cost
-// per step) takes kChunk and cheaper groups proportionally more, up to
-// kChunkMax, so that a round takes about the same time on every stream.
-// Within a group every solve gets about the same device time as that
-// costliest one: a solve whose steps cost a k-th as much takes k times the
-// steps (up to kChunkMax), so that a small solve batched with large ones of
-// its order does not wait for as many of their steps as it needs of its own.
-// Never past a solve's last step or its KE-record capacity.
-static std::map<const Solve*, int64_t> round_plan(const std::map<int, std::vector<Solve*>>& groups) {
-    std::map<int, double> cost;
-    double cmax = 0.0;
-    for (auto& g : groups) {
-        double c = 0.0;
-        for (Solve* s : g.second) c += step_cost(s);
-        cost[g.first] = c;
-        cmax = std::max(cmax, c);
-    }
-    std::map<const Solve*, int64_t> plan;
-    for (auto& g : groups) {
-        const double ng = std::max(1.0, std::min((double)kChunkMax,
-                                                 std::floor(kChunk * cmax / std::max(1.0, cost[g.first]))));
-        double cbig = 0.0;
-        for (Solve* s : g.second) cbig = std::max(cbig, step_cost(s));
-        for (Solve* s : g.second) {
-            double n = std::floor(ng * cbig / std::max(1.0, step_cost(s)));
-            n = std::min(n, std::max(ng, (double)kChunkMax));
-            int64_t k = std::max<int64_t>((int64_t)n, 1);
-            k = std::min<int64_t>(k, s->n_steps - s->steps);
-            k = std::min<int64_t>(k, (int64_t)(kHist - 1 - (int)s->pending_t.size()) * s->req.ke_every);
-            plan[s] = std::max<int64_t>(k, 1);
-        }
+// Steps of one round for each running solve of an order: the costliest takes
+// kChunk, and every solve gets about the same device time as that one: a solve
+// whose steps cost a k-th as much takes k times the steps (up to kChunkMax),
+// so that a small solve batched with large ones does not wait for as many of
+// their steps as it needs of its own.  Never past a solve's last step or its
+// KE-record capacity.
+static std::vector<int64_t> round_plan(const std::vector<Solve*>& run) {
+    double cbig = 0.0;
+    for (Solve* s : run) cbig = std::max(cbig, step_cost(s));
+    std::vector<int64_t> plan;
+    for (Solve* s : run) {
+        const double n = std::floor(kChunk * cbig / std::max(1.0, step_cost(s)));
+        int64_t k = std::max<int64_t>((int64_t)std::min(n, (double)kChunkMax), 1);
+        k = std::min<int64_t>(k, s->n_steps - s->steps);
+        k = std::min<int64_t>(k, (int64_t)(kHist - 1 - (int)s->pending_t.size()) * s->req.ke_every);
+        plan.push_back(std::max<int64_t>(k, 1));
     }
     return plan;
 }
@@ -378,30 +458,19 @@ static bool record_healthy(const Solve* s, const double* rec) {
     return record_finite(rec) && rec[0] <= s->ke0 * (1.0 + kFallbackKeRise);
 }
 
-// Reads the round's kinetic-energy records (and, for a corrected solve, the
-// end-of-round health record).  Returns true when a corrected solve must
-// fall back: its pending records are then dropped, except those at or
-// before the state copy it returns to.
-static bool collect(solve_server* S, Solve* s) {
+// Takes over the round's kinetic-energy records (and, for a corrected solve,
+// the end-of-round health record) that the round read back.  Returns true when
+// a corrected solve must fall back: its pending records are then dropped,
+// except those at or before the state copy it returns to.
+static bool collect(solve_server* S, Solve* s, const double* records) {
     const size_t n = s->pending_t.size();
-    double health[kDiagDoubles];
     const bool check = s->nn_active;
-    if (n > 0 && hipMemcpy(S->pinned, s->hist, n * kDiagDoubles * sizeof(double), hipMemcpyDeviceToHost) != hipSuccess) {
-        std::lock_guard<std::mutex> lk(S->mu);
-        s->error = DG_EHIP;
-        return false;
-    }
-    if (check && hipMemcpy(health, s->health, sizeof(health), hipMemcpyDeviceToHost) != hipSuccess) {
-        std::lock_guard<std::mutex> lk(S->mu);
-        s->error = DG_EHIP;
-        return false;
-    }
     std::lock_guard<std::mutex> lk(S->mu);
-    bool bad = check && !record_healthy(s, health);
-    for (size_t r = 0; r < n && check && !bad; ++r) bad = !record_healthy(s, S->pinned + r * kDiagDoubles);
+    bool bad = check && !record_healthy(s, records + kHist * kDiagDoubles);
+    for (size_t r = 0; r < n && check && !bad; ++r) bad = !record_healthy(s, records + r * kDiagDoubles);
     const double t_ckpt = s->ckpt_steps * s->dt;
     for (size_t r = 0; r < n; ++r) {
-        const double* rec = S->pinned + r * kDiagDoubles;
+        const double* rec = records + r * kDiagDoubles;
         if (bad && s->pending_t[r] > t_ckpt + 0.5 * s->dt) continue;
         if (!bad && !record_finite(rec)) s->error = DG_ENONFINITE;
         s->ke.push_back(s->pending_t[r]);
@@ -413,17 +482,17 @@ static bool collect(solve_server* S, Solve* s) {
 
 // return a corrected solve to the state copy of the round start and continue
 // it uncorrected from there
-static int fall_back(solve_server* S, Solve* s) {
+static int fall_back(solve_server* S, Worker& W, Solve* s) {
     s->nn_active = false;
     if (hipMemcpyAsync(s->q, s->ckpt, (size_t)5 * s->mesh.E * s->mesh.n_p * sizeof(double), hipMemcpyDeviceToDevice,
-                       S->st) != hipSuccess)
+                       W.st) != hipSuccess)
         return set_error(DG_EHIP, "fallback restore failed");
-    int rc = write_descs(S, s);
+    int rc = write_descs(s, W.st);
     if (rc) return rc;
     s->par = 0;
-    if (launch_traces(s->mesh.PP, single_list(s->ddesc + 1, s->mesh.E), S->st) != hipSuccess)
-        return set_error(DG_EHIP, "trace launch failed");
-    if (hipStreamSynchronize(S->st) != hipSuccess) return set_error(DG_EHIP, "fallback synchronise failed");
+    SolveDesc d;
+    stage_desc(s, 1, d);
+    if (launch_traces(s->mesh.PP, d, W.st) != hipSuccess) return set_error(DG_EHIP, "trace launch failed");
     std::lock_guard<std::mutex> lk(S->mu);
     s->steps = s->ckpt_steps;
     s->fell_back = true;
@@ -431,113 +500,144 @@ static int fall_back(solve_server* S, Solve* s) {
     return DG_OK;
 }
 
-static void finish(solve_server* S, Solve* s) {
+// Device to pageable host memory, a chunk on its way to pinned memory while
+// others go on from there, each in a thread of its own (new pages are what
+// takes long: 15 MB in four threads 0.8 ms, in one 1.4).
+static hipError_t copy_out(Worker& W, char* dst, const char* src, size_t bytes) {
+    if (bytes > kStageChunk && !W.stage &&
+        hipHostMalloc((void**)&W.stage, kStageSlots * kStageChunk, hipHostMallocDefault) != hipSuccess)
+        W.stage = nullptr;
+    if (bytes <= kStageChunk || !W.stage) return hipMemcpy(dst, src, bytes, hipMemcpyDeviceToHost);
+    std::future<void> going[kStageSlots];   // their destructors wait
+    for (size_t at = 0, i = 0; at < bytes; at += kStageChunk, ++i) {
+        const size_t slot = i % kStageSlots, n = std::min(kStageChunk, bytes - at);
+        char* const piece = W.stage + slot * kStageChunk;
+        if (going[slot].valid()) going[slot].wait();
+        const hipError_t e = hipMemcpy(piece, src + at, n, hipMemcpyDeviceToHost);
+        if (e != hipSuccess) return e;
+        const auto move = [=] { std::memcpy(dst + at, piece, n); };
+        try {
+            going[slot] = std::async(std::launch::async, move);
+        } catch (const std::exception&) {
+            move();
+        }
+    }
+    return hipSuccess;
+}
+
+static void finish(solve_server* S, Worker& W, Solve* s) {
     if (s->req.q_out_host)
-        (void)hipMemcpy(s->req.q_out_host, s->q, (size_t)5 * s->mesh.E * s->mesh.n_p * sizeof(double), hipMemcpyDeviceToHost);
+        (void)copy_out(W, (char*)s->req.q_out_host, (const char*)s->q,
+                       (size_t)5 * s->mesh.E * s->mesh.n_p * sizeof(double));
     if (s->req.ke_host) {
         const size_t pairs = std::min((size_t)s->req.ke_capacity, s->ke.size() / 2);
         std::memcpy(s->req.ke_host, s->ke.data(), pairs * 2 * sizeof(double));
     }
-    std::lock_guard<std::mutex> lk(S->mu);
-    s->state = SOLVE_DONE;
-    s->t_done = now_s();
-    S->arena.release(s->off, s->bytes);
+    leave(S, s, SOLVE_DONE, s->error);
 }
 
-static void server_loop(solve_server* S) {
-    (void)hipSetDevice(S->device);
-    std::vector<Solve*> run;
+// enqueues one round of the running solves, up to the read-back of its records
+static int enqueue_round(solve_server* S, Worker& W, const std::vector<Solve*>& run) {
+    int rc = reserve_records(W, run.size());
+    if (rc) return rc;
+    const std::vector<int64_t> plan = round_plan(run);
+    const int64_t steps = *std::max_element(plan.begin(), plan.end());
+    // corrected solves: copy of the (already checked) state the round starts from
+    for (Solve* s : run)
+        if (s->nn_active) {
+            s->ckpt_steps = s->steps;
+            if (hipMemcpyAsync(s->ckpt, s->q, (size_t)5 * s->mesh.E * s->mesh.n_p * sizeof(double),
+                               hipMemcpyDeviceToDevice, W.st) != hipSuccess)
+                return set_error(DG_EHIP, "state copy failed");
+        }
+    // step n batches every solve that still has steps in this round
+    std::vector<Solve*> active;
+    for (int64_t n = 0; n < steps; ++n) {
+        active.clear();
+        for (size_t i = 0; i < run.size(); ++i)
+            if (plan[i] > n) active.push_back(run[i]);
+        if ((rc = step_group(W.PP, active, W.st))) return rc;
+    }
+    for (size_t i = 0; i < run.size(); ++i) {
+        Solve* s = run[i];
+        double* rec = W.records + i * kRecords;
+        if (s->nn_active && (rc = diag_impl(s->mesh, s->q, s->health, s->ws, W.st))) return rc;
+        if ((!s->pending_t.empty() &&
+             hipMemcpyAsync(rec, s->hist, s->pending_t.size() * kDiagDoubles * sizeof(double), hipMemcpyDeviceToHost,
+                            W.st) != hipSuccess) ||
+            (s->nn_active && hipMemcpyAsync(rec + kHist * kDiagDoubles, s->health, kDiagDoubles * sizeof(double),
+                                            hipMemcpyDeviceToHost, W.st) != hipSuccess))
+            return set_error(DG_EHIP, "record readback failed");
+    }
+    std::lock_guard<std::mutex> lk(S->mu);
+    S->batches += steps;
+    return DG_OK;
+}
+
+static void mark_round(solve_server* S, bool begin) {
+    std::lock_guard<std::mutex> lk(S->mu);
+    const double t = now_s();
+    if (begin && S->in_round++ == 0) S->round_t0 = t;
+    if (!begin && --S->in_round == 0) S->busy += t - S->round_t0;
+}
+
+static void worker_loop(solve_server* S, Worker& W) {
+    int broken = DG_OK;
+    if (hipSetDevice(S->device) != hipSuccess ||
+        hipStreamCreateWithFlags(&W.st, hipStreamNonBlocking) != hipSuccess) {
+        W.st = nullptr;
+        broken = set_error(DG_EHIP, "stream creation failed");
+    }
+    std::vector<Solve*> admitted, run, keep, done;
     while (true) {
-        std::vector<Solve*> admitted;
+        bool stop;
         {
             std::unique_lock<std::mutex> lk(S->mu);
-            S->cv.wait(lk, [&] { return S->stop || !S->queue.empty() || !run.empty(); });
-            if (S->stop) break;
-            for (auto it = S->queue.begin(); it != S->queue.end();) {
-                Solve* s = *it;
-                if ((int)(run.size() + admitted.size()) >= S->max_slots) break;
-                size_t off;
-                if (S->arena.alloc(s->bytes, off)) {
-                    s->off = off;
-                    s->state = SOLVE_RUNNING;
-                    s->t_admit = now_s();
-                    admitted.push_back(s);
-                    it = S->queue.erase(it);
-                } else {
-                    ++it;
-                }
-            }
+            S->cv.wait(lk, [&] { return S->stop || !W.inbox.empty() || !run.empty() || !done.empty(); });
+            stop = S->stop;
+            if (!stop) admitted.swap(W.inbox);
         }
-        for (Solve* s : admitted) {
-            int rc = admit_one(S, s);
-            if (rc) fail(S, s, rc);
-            else run.push_back(s);
+        if (broken) {
+            for (Solve* s : admitted) fail(S, s, broken);
+            admitted.clear();
         }
-        if (run.empty()) {
-            S->cv.notify_all();
-            continue;
-        }
-        std::map<int, std::vector<Solve*>> groups;
-        for (Solve* s : run) groups[s->mesh.PP].push_back(s);
-        const std::map<const Solve*, int64_t> plan = round_plan(groups);
-        const double t0 = now_s();
+        if (!stop) admit(S, W, admitted, run);
         int rc = DG_OK;
-        int64_t steps_done = 0;
-        for (auto& g : groups) {
-            hipStream_t gst = S->gst[g.first];
-            int64_t n_g = 0;
-            for (Solve* s : g.second) n_g = std::max(n_g, plan.at(s));
-            // corrected solves: copy of the (already checked) state the round starts from
-            for (Solve* s : g.second)
-                if (s->nn_active && rc == DG_OK) {
-                    s->ckpt_steps = s->steps;
-                    if (hipMemcpyAsync(s->ckpt, s->q, (size_t)5 * s->mesh.E * s->mesh.n_p * sizeof(double),
-                                       hipMemcpyDeviceToDevice, gst) != hipSuccess)
-                        rc = set_error(DG_EHIP, "state copy failed");
-                }
-            // step n batches every solve that still has steps in this round
-            std::vector<Solve*> active;
-            for (int64_t n = 0; n < n_g && rc == DG_OK; ++n) {
-                active.clear();
-                for (Solve* s : g.second)
-                    if (plan.at(s) > n) active.push_back(s);
-                rc = step_group(S, g.first, active, gst);
-            }
-            for (Solve* s : g.second)
-                if (s->nn_active && rc == DG_OK) rc = diag_impl(s->mesh, s->q, s->health, s->ws, gst);
-            steps_done = std::max(steps_done, n_g);
+        const bool round = !stop && !run.empty();
+        if (round) {
+            mark_round(S, true);
+            rc = enqueue_round(S, W, run);
         }
-        for (auto& g : groups) (void)hipStreamSynchronize(S->gst[g.first]);
-        const double t1 = now_s();
-        {
-            std::lock_guard<std::mutex> lk(S->mu);
-            S->busy += t1 - t0;
-            S->batches += steps_done;
-        }
-        std::vector<Solve*> keep;
-        for (Solve* s : run) {
-            const bool back = collect(S, s);
-            if (back && rc == DG_OK) {
-                const int frc = fall_back(S, s);
-                if (frc) {
+        for (Solve* s : done) finish(S, W, s);   // beside the round on the device
+        done.clear();
+        if (stop) break;
+        if (!round) continue;
+        const bool synced = hipStreamSynchronize(W.st) == hipSuccess;
+        mark_round(S, false);
+        if (!synced && rc == DG_OK) rc = set_error(DG_EHIP, "round synchronise failed");
+        keep.clear();
+        for (size_t i = 0; i < run.size(); ++i) {
+            Solve* s = run[i];
+            int err = rc;
+            if (err == DG_OK) {
+                if (collect(S, s, W.records + i * kRecords)) err = fall_back(S, W, s);
+                else {
                     std::lock_guard<std::mutex> lk(S->mu);
-                    s->error = frc;
+                    err = s->error;
                 }
-            }
-            int err;
-            {
-                std::lock_guard<std::mutex> lk(S->mu);
-                if (rc != DG_OK) s->error = rc;
-                err = s->error;
             }
             if (err) fail(S, s, err);
-            else if (s->steps >= s->n_steps) finish(S, s);
+            else if (s->steps >= s->n_steps) done.push_back(s);
             else keep.push_back(s);
         }
         run.swap(keep);
-        S->cv.notify_all();
     }
-    S->cv.notify_all();
+    if (W.st) {
+        (void)hipStreamSynchronize(W.st);
+        (void)hipStreamDestroy(W.st);
+    }
+    if (W.records) (void)hipHostFree(W.records);
+    if (W.stage) (void)hipHostFree(W.stage);
 }
 
 }  // namespace dgnn
@@ -571,24 +671,7 @@ int solve_server_create(void* arena, size_t arena_bytes, int32_t max_slots, solv
         delete S;
         return set_error(DG_EHIP, "hipGetDevice failed");
     }
-    if (hipStreamCreateWithFlags(&S->st, hipStreamNonBlocking) != hipSuccess) {
-        delete S;
-        return set_error(DG_EHIP, "stream creation failed");
-    }
-    for (int pp = DG_MIN_ORDER + 1; pp <= kMaxPP; ++pp)
-        if (hipStreamCreateWithFlags(&S->gst[pp], hipStreamNonBlocking) != hipSuccess) {
-            for (int q = DG_MIN_ORDER + 1; q < pp; ++q) (void)hipStreamDestroy(S->gst[q]);
-            (void)hipStreamDestroy(S->st);
-            delete S;
-            return set_error(DG_EHIP, "stream creation failed");
-        }
-    if (hipHostMalloc((void**)&S->pinned, kHist * kDiagDoubles * sizeof(double), hipHostMallocDefault) != hipSuccess) {
-        (void)hipStreamDestroy(S->st);
-        for (int pp = DG_MIN_ORDER + 1; pp <= kMaxPP; ++pp) (void)hipStreamDestroy(S->gst[pp]);
-        delete S;
-        return set_error(DG_EHIP, "pinned buffer allocation failed");
-    }
-    S->th = std::thread(server_loop, S);
+    for (int pp = 0; pp <= kMaxPP; ++pp) S->workers[pp].PP = pp;
     *out = S;
     return DG_OK;
 }
@@ -617,10 +700,19 @@ int solve_submit(solve_server* S, const solve_request* r, uint64_t* id) {
     {
         std::lock_guard<std::mutex> lk(S->mu);
         if (S->stop) return set_error(DG_EINVAL, "server is shutting down");
+        Worker& W = S->workers[m.PP];
+        if (!W.th.joinable()) {
+            try {
+                W.th = std::thread(worker_loop, S, std::ref(W));
+            } catch (const std::exception&) {
+                return set_error(DG_EHIP, "thread creation failed");
+            }
+        }
         s->id = S->next_id++;
         *id = s->id;
         S->queue.push_back(s.get());
         S->solves[s->id] = std::move(s);
+        admit_waiting(S);
     }
     S->cv.notify_all();
     return DG_OK;
@@ -672,7 +764,7 @@ int solve_inject_nan(solve_server* S, uint64_t id) {
 int solve_server_stats(solve_server* S, double* busy_s, int64_t* batches) {
     if (!S) return set_error(DG_EINVAL, "null server");
     std::lock_guard<std::mutex> lk(S->mu);
-    if (busy_s) *busy_s = S->busy;
+    if (busy_s) *busy_s = S->busy + (S->in_round > 0 ? now_s() - S->round_t0 : 0.0);
     if (batches) *batches = S->batches;
     return DG_OK;
 }
@@ -684,14 +776,8 @@ void solve_server_free(solve_server* S) {
         S->stop = true;
     }
     S->cv.notify_all();
-    if (S->th.joinable()) S->th.join();
-    (void)hipStreamSynchronize(S->st);
-    (void)hipStreamDestroy(S->st);
-    for (int pp = DG_MIN_ORDER + 1; pp <= kMaxPP; ++pp) {
-        (void)hipStreamSynchronize(S->gst[pp]);
-        (void)hipStreamDestroy(S->gst[pp]);
-    }
-    (void)hipHostFree(S->pinned);
+    for (Worker& W : S->workers)
+        if (W.th.joinable()) W.th.join();
     delete S;
 }
 
