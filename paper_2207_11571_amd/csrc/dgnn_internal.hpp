@@ -206,27 +206,23 @@ struct TrainArgs {
     float* loss_part;                 // [Bp / 16]
 };
 
-// All layers' weight and bias gradients of one training step: split-K
-// partial products, then one fixed-order reduction.
+// All layers' weight and bias gradients of one training step.
 struct GradArgs {
     const uint16_t* dzT[kMaxLayers];
     const uint16_t* actT[kMaxLayers];
-    float* part[kMaxLayers];          // [nks][pout][pin]
     const float* bias_part[kMaxLayers];
     float* gW[kMaxLayers];
     float* gb[kMaxLayers];
     int pout[kMaxLayers], pin[kMaxLayers], dout[kMaxLayers], din[kMaxLayers];
-    int tblk[kMaxLayers + 1];         // product blocks before layer l (four 16x16 tiles each)
-    int rblk[kMaxLayers + 1];         // reduction blocks before layer l (256 outputs each)
-    int n_layers, Bp, kchunk, nks, nrb;
+    int tblk[kMaxLayers + 1];         // 32 x 32 tiles before layer l
+    int gtiles;                       // blocks for all tiles: their number, a multiple of eight
+    int n_layers, Bp, nrb;
 };
 
 // Adam on the float32 master weights with the bf16 copies W_l, W_l^T written
 // in the same pass.
 struct ParamMap {
     int64_t woff[kMaxLayers], boff[kMaxLayers], wbo[kMaxLayers], wtbo[kMaxLayers];
-    int din[kMaxLayers], dout[kMaxLayers], pin[kMaxLayers], pout[kMaxLayers];
-    int n_layers;
 };
 // Adam step of the whole parameter vector (and the loss output, when loss is
 // not null), for the fused end-of-step launch
@@ -243,10 +239,8 @@ struct AdamArgs {
 };
 size_t train_smem_bytes(const NetArgs& na);
 hipError_t launch_train_rows(const NetArgs& na, const TrainArgs& ta, int nblocks, hipStream_t st);
-// the split-K weight-gradient products alone, and then the gradient
-// reductions, the Adam update and the loss in one launch
-hipError_t launch_wgrad(const GradArgs& ga, hipStream_t st);
-hipError_t launch_reduce_adam(const GradArgs& ga, const ParamMap& pm, const AdamArgs& aa, hipStream_t st);
+// gradients, Adam update and loss, in one launch
+hipError_t launch_grad_adam(const GradArgs& ga, const ParamMap& pm, const AdamArgs& aa, hipStream_t st);
 hipError_t launch_data_stats(const float* x, const float* y, int64_t rows, int n_p, double* part, int nblocks,
                              double* out_dev, hipStream_t st);
 hipError_t launch_column_stats(const float* x, const float* y, int64_t rows, int ncols, double* part, int nblocks,

@@ -151,21 +151,19 @@ static int refresh(nn_model* m, hipStream_t st) {
 }
 
 struct TrainLayout {
-    size_t actT[kMaxLayers], dzT[kMaxLayers], part[kMaxLayers], bpart[kMaxLayers], loss, total;
-    int Bp, nks, nrb;
+    size_t actT[kMaxLayers], dzT[kMaxLayers], bpart[kMaxLayers], loss, total;
+    int Bp, nrb;
 };
 
 static TrainLayout train_layout(const nn_model* m, int batch) {
     TrainLayout T;
     std::memset(&T, 0, sizeof(T));
     T.Bp = pad32(batch);
-    // the weight-gradient products split the batch into nks slices of at
-    // least 256 rows, at most eight (batch 4096: 0.0675 ms per Adam step
-    // against 0.071 with sixteen slices, whose partial sums double the
-    // traffic of the reduction; 0.0705 with four)
-    T.nks = T.Bp / 256;
-    if (T.nks < 1) T.nks = 1;
-    if (T.nks > 8) T.nks = 8;
+    // the size that callers know includes an area for the weight gradients
+    // of up to eight slices of the batch, which are summed on the chip now
+    int slices = T.Bp / 256;
+    if (slices < 1) slices = 1;
+    if (slices > 8) slices = 8;
     T.nrb = T.Bp / 16;
     size_t off = 0;
     for (int l = 0; l < m->n_layers; ++l) {
@@ -173,8 +171,7 @@ static TrainLayout train_layout(const nn_model* m, int batch) {
         off += align256((size_t)m->pdims[l] * T.Bp * sizeof(uint16_t));
         T.dzT[l] = off;
         off += align256((size_t)m->pdims[l + 1] * T.Bp * sizeof(uint16_t));
-        T.part[l] = off;
-        off += align256((size_t)T.nks * m->pdims[l] * m->pdims[l + 1] * sizeof(float));
+        off += align256((size_t)slices * m->pdims[l] * m->pdims[l + 1] * sizeof(float));
         T.bpart[l] = off;
         off += align256((size_t)T.nrb * m->pdims[l + 1] * sizeof(float));
     }
@@ -353,13 +350,10 @@ int nn_train_step(nn_model* m, const float* x, const float* y, const int32_t* id
     std::memset(&ga, 0, sizeof(ga));
     ga.n_layers = m->n_layers;
     ga.Bp = T.Bp;
-    ga.nks = T.nks;
     ga.nrb = T.nrb;
-    ga.kchunk = ((T.Bp + T.nks - 1) / T.nks + 31) / 32 * 32;
     for (int l = 0; l < m->n_layers; ++l) {
         ga.dzT[l] = ta.dzT[l];
         ga.actT[l] = ta.actT[l];
-        ga.part[l] = (float*)(base + T.part[l]);
         ga.bias_part[l] = ta.bias_part[l];
         ga.gW[l] = m->grad + m->woff[l];
         ga.gb[l] = m->grad + m->boff[l];
@@ -367,26 +361,19 @@ int nn_train_step(nn_model* m, const float* x, const float* y, const int32_t* id
         ga.pin[l] = m->pdims[l];
         ga.dout[l] = m->dims[l + 1];
         ga.din[l] = m->dims[l];
-        const int ntiles = (ga.pout[l] / 32) * (ga.pin[l] / 32);
-        ga.tblk[l + 1] = ga.tblk[l] + (ntiles + 3) / 4;
-        ga.rblk[l + 1] = ga.rblk[l] + (ga.dout[l] * ga.din[l] + 255) / 256;
+        ga.tblk[l + 1] = ga.tblk[l] + (ga.pout[l] / 32) * (ga.pin[l] / 32);
     }
-    NN_HIP(launch_wgrad(ga, st));
+    ga.gtiles = (ga.tblk[ga.n_layers] + 7) / 8 * 8;
     m->step += 1;
     const double bc1 = 1.0 - std::pow(0.9, (double)m->step);
     const double bc2 = 1.0 - std::pow(0.999, (double)m->step);
     ParamMap pm;
     std::memset(&pm, 0, sizeof(pm));
-    pm.n_layers = m->n_layers;
     for (int l = 0; l < m->n_layers; ++l) {
         pm.woff[l] = m->woff[l];
         pm.boff[l] = m->boff[l];
         pm.wbo[l] = m->wbf_off[l];
         pm.wtbo[l] = m->wtbf_off[l];
-        pm.din[l] = m->dims[l];
-        pm.dout[l] = m->dims[l + 1];
-        pm.pin[l] = m->pdims[l];
-        pm.pout[l] = m->pdims[l + 1];
     }
     AdamArgs aa;
     aa.p = m->params;
@@ -403,7 +390,7 @@ int nn_train_step(nn_model* m, const float* x, const float* y, const int32_t* id
     aa.n_loss = nblocks;
     aa.inv_count = (float)(1.0 / ((double)batch * m->dims[m->n_layers]));
     aa.loss = loss_dev;
-    NN_HIP(launch_reduce_adam(ga, pm, aa, st));
+    NN_HIP(launch_grad_adam(ga, pm, aa, st));
     return DG_OK;
 }
 

@@ -22,7 +22,6 @@ template <class T>
 __device__ __forceinline__ global_t<T>* gmem(T* p) { return (global_t<T>*)p; }
 
 constexpr int kRows = 16;      // rows (elements / samples) per block
-constexpr int kThreads = 256;     // weight-gradient blocks: four wavefronts, one tile each
 constexpr int kRowWaves = 16;     // row-block kernels: sixteen wavefronts share the column tiles
 constexpr int kRowThreads = 64 * kRowWaves;
 constexpr int kLdPad = 8;      // LDS row padding (bf16 elements)

@@ -13,7 +13,7 @@
 // backward data chain with all activations LDS-resident, and write the
 // transposed activations and output gradients needed by the weight-gradient
 // products dW_l = dz_l^T h_l, which reduce over the batch in a second kernel
-// (split over the batch, then a fixed-order sum).
+// that also updates the weights.
 #include "nn_device.hpp"
 
 namespace dgnn {
@@ -426,136 +426,169 @@ __global__ void __launch_bounds__(kRowThreads) k_train256(NetArgs na, TrainArgs 
     }
 }
 
-// Weight-gradient partials of every layer in one launch: part_l[ks][o][i] =
-// sum over the batch slice ks of dzT_l[o][b] actT_l[i][b].  Each wave computes
-// one 32 x 32 tile as 2 x 2 MFMA tiles, so every fragment it loads feeds two
-// products; block x (four tiles) belongs to the layer whose block range
-// holds it.
-__global__ void __launch_bounds__(kThreads) k_wgrad(GradArgs ga) {
+// Adam update of parameter i (flat index) with gradient gi and its old moments
+// and value, loaded by the caller; returns the new value
+struct AdamState {
+    float m, v, p;
+};
+__device__ __forceinline__ AdamState adam_load(const AdamArgs& aa, int64_t i) {
+    return {gmem(aa.m)[i], gmem(aa.v)[i], gmem(aa.p)[i]};
+}
+__device__ __forceinline__ float adam_one(const AdamArgs& aa, int64_t i, float gi, const AdamState& s) {
+    const float mi = aa.b1 * s.m + (1.0f - aa.b1) * gi;
+    const float vi = aa.b2 * s.v + (1.0f - aa.b2) * gi * gi;
+    gmem(aa.m)[i] = mi;
+    gmem(aa.v)[i] = vi;
+    const float pi = s.p - aa.lr * (mi / aa.bc1) / (sqrtf(vi / aa.bc2) + aa.eps);
+    gmem(aa.p)[i] = pi;
+    return pi;
+}
+
+// layer of entry x of a list whose layers end at end[l + 1] (one load of the
+// ends, where a search would wait for one after the other)
+__device__ __forceinline__ int layer_of(const int (&end)[kMaxLayers + 1], int n_layers, int x) {
     int l = 0;
-    while (l + 1 < ga.n_layers && (int)blockIdx.x >= ga.tblk[l + 1]) ++l;
+#pragma unroll
+    for (int i = 1; i < kMaxLayers; ++i) l += i < n_layers && x >= end[i];
+    return l;
+}
+
+// The end of a training step in one launch.  Blocks [0, gtiles) take one
+// 32 x 32 tile of a layer's weights each: gradient dz^T h over the whole
+// batch, Adam, and the tile's share of the bf16 copies W_l [pout][pin] and
+// W_l^T [pin][pout].  Eight wavefronts split the batch; each computes 2 x 2
+// MFMA tiles (every fragment it loads feeds two products), and their sums are
+// added in LDS in a fixed order.  Then bias blocks (32 biases each: the sums
+// of the row blocks), then, with a loss output, one block for the loss.
+// Bound by the reads of h and dz: tiles that share rows go to one XCD (the
+// hardware deals blocks out to the eight in turn), whose L2 then takes 3.5 of
+// the 19 MB at a batch of 4096 instead of all of them (21.2 -> 14.5 us;
+// 64 x 32 tiles, which read a quarter less from L2, 15.8).
+// With the split over blocks, the partial sums in memory and Adam in a launch
+// of its own: 320-256-256-256-320, batch 512 6.2 + 6.6 us, 4096 13.0 + 9.3;
+// so 6.6 and 14.4.
+constexpr int kGradWaves = 8;
+__global__ void __launch_bounds__(64 * kGradWaves) k_grad_adam(GradArgs ga, ParamMap pm, AdamArgs aa, int nbias) {
+    constexpr int LDR = 36;    // floats a row of a partial tile: the four row groups of a store use other banks
+    constexpr int LDH = 40;    // bf16 a row of the new weights, rows 16 bytes aligned
+    constexpr int T = 64 * kGradWaves, NE = 1024 / T;
+    __shared__ float red[kGradWaves][32 * LDR];
+    __shared__ __attribute__((aligned(16))) uint16_t hw[2][32 * LDH];
     const int t = threadIdx.x;
-    const int wave = __builtin_amdgcn_readfirstlane(t >> 6), lane = t & 63;
-    const int pout = ga.pout[l], pin = ga.pin[l], Bp = ga.Bp;
-    const int tiles_i = pin / 32;
-    const int tile = ((int)blockIdx.x - ga.tblk[l]) * 4 + wave;
-    const int ntiles = (pout / 32) * tiles_i;
-    if (tile >= ntiles) return;
-    const int to = tile / tiles_i, tii = tile - to * tiles_i;
-    const int ks = blockIdx.y;
-    const int kb = ks * ga.kchunk;
-    const int ke = kb + ga.kchunk < Bp ? kb + ga.kchunk : Bp;
-    const int r = lane & 15;
-    // dzT and actT are in fragment order over the batch (wfrag_index with
-    // K = Bp): the 32-batch step s of 16-row tile t is the 1 KB block
-    // t * Bp / 32 + s, lane-major
-    const int ksteps = Bp / 32;
-    const global_t<uint16_t>* arow0 = gmem(ga.dzT[l]) + ((int64_t)(2 * to) * ksteps * 64 + lane) * 8;
-    const global_t<uint16_t>* arow1 = arow0 + (int64_t)ksteps * 512;
-    const global_t<uint16_t>* brow0 = gmem(ga.actT[l]) + ((int64_t)(2 * tii) * ksteps * 64 + lane) * 8;
-    const global_t<uint16_t>* brow1 = brow0 + (int64_t)ksteps * 512;
-    floatx4 acc[2][2];
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j) acc[i][j] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
-    for (int k0 = kb; k0 < ke; k0 += 32) {
-        const int64_t o = (int64_t)(k0 / 32) * 512;
-        const bf16x8 a0 = *(const global_t<bf16x8>*)(arow0 + o);
-        const bf16x8 a1 = *(const global_t<bf16x8>*)(arow1 + o);
-        const bf16x8 b0 = *(const global_t<bf16x8>*)(brow0 + o);
-        const bf16x8 b1 = *(const global_t<bf16x8>*)(brow1 + o);
-        acc[0][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a0, b0, acc[0][0], 0, 0, 0);
-        acc[0][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a0, b1, acc[0][1], 0, 0, 0);
-        acc[1][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a1, b0, acc[1][0], 0, 0, 0);
-        acc[1][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a1, b1, acc[1][1], 0, 0, 0);
-    }
-    float* o = ga.part[l] + (size_t)ks * pout * pin;
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-#pragma unroll
-            for (int v = 0; v < 4; ++v)
-                o[(size_t)(to * 32 + 16 * i + 4 * (lane >> 4) + v) * pin + tii * 32 + 16 * j + r] = acc[i][j][v];
-}
-
-// Adam update of parameter i (flat index) with gradient gi; weights also go
-// to their bf16 copies W_l [pout][pin] and W_l^T [pin][pout] (fragment order)
-__device__ __forceinline__ void adam_one(const AdamArgs& aa, const ParamMap& pm, int64_t i, float gi) {
-    const float mi = aa.b1 * aa.m[i] + (1.0f - aa.b1) * gi;
-    const float vi = aa.b2 * aa.v[i] + (1.0f - aa.b2) * gi * gi;
-    aa.m[i] = mi;
-    aa.v[i] = vi;
-    const float pi = aa.p[i] - aa.lr * (mi / aa.bc1) / (sqrtf(vi / aa.bc2) + aa.eps);
-    aa.p[i] = pi;
-    int l = 0;
-    while (l + 1 < pm.n_layers && i >= pm.woff[l + 1]) ++l;
-    if (i < pm.boff[l]) {
-        const int64_t w = i - pm.woff[l];
-        const int o = (int)(w / pm.din[l]), ii = (int)(w - (int64_t)o * pm.din[l]);
-        const uint16_t h = f2bf(pi);
-        aa.wbf[pm.wbo[l] + wfrag_index(o, ii, pm.pin[l])] = h;
-        aa.wbf[pm.wtbo[l] + wfrag_index(ii, o, pm.pout[l])] = h;
-    }
-}
-
-// The end of a training step in one launch: blocks [0, rblk[L]) sum the
-// split-K weight-gradient partials, one thread per weight in a fixed order,
-// write the gradient and update that weight (Adam); the next ceil(nbias / 4)
-// blocks sum the bias row-block sums, one wavefront per bias (lane-strided
-// sums, then a fixed butterfly), and lane 0 updates that bias; with a loss
-// output, one more block sums the loss partials.  The same sums in the same
-// order as separate reduction launches would make, one launch instead of four.
-__global__ void __launch_bounds__(256) k_reduce_adam(GradArgs ga, ParamMap pm, AdamArgs aa, int nbias) {
-    const int wblk = ga.rblk[ga.n_layers];
-    const int bblk = (nbias + 3) / 4;
     const int b = blockIdx.x;
-    if (b < wblk) {
-        int l = 0;
-        while (l + 1 < ga.n_layers && b >= ga.rblk[l + 1]) ++l;
-        const int idx = (b - ga.rblk[l]) * 256 + threadIdx.x;
-        const int dout = ga.dout[l], din = ga.din[l], pout = ga.pout[l], pin = ga.pin[l];
-        if (idx < dout * din) {
-            const int o = idx / din, i = idx - o * din;
-            float s = 0.0f;
-            for (int k = 0; k < ga.nks; ++k) s += gmem(ga.part[l])[(size_t)k * pout * pin + (size_t)o * pin + i];
-            gmem(ga.gW[l])[idx] = s;
-            adam_one(aa, pm, pm.woff[l] + idx, s);
+    if (b < ga.gtiles) {
+        const int tile = (b % 8) * (ga.gtiles / 8) + b / 8;
+        if (tile >= ga.tblk[ga.n_layers]) return;
+        const int l = layer_of(ga.tblk, ga.n_layers, tile);
+        const int wave = __builtin_amdgcn_readfirstlane(t >> 6), lane = t & 63;
+        const int pout = ga.pout[l], pin = ga.pin[l], dout = ga.dout[l], din = ga.din[l];
+        const int tiles_i = pin / 32;
+        const int to = (tile - ga.tblk[l]) / tiles_i, ti = (tile - ga.tblk[l]) - to * tiles_i;
+        // the weights of this thread
+        int64_t at[NE];
+        bool in[NE];
+        AdamState old[NE];
+#pragma unroll
+        for (int j = 0; j < NE; ++j) {
+            const int o = to * 32 + t / 32 + j * (T / 32), i = ti * 32 + (t & 31);
+            in[j] = o < dout && i < din;
+            at[j] = in[j] ? (int64_t)o * din + i : 0;
+            old[j] = adam_load(aa, pm.woff[l] + at[j]);
+        }
+        // dzT and actT are in fragment order over the batch (wfrag_index with
+        // K = Bp): the 32-batch step s of 16-row tile t is the 1 KB block
+        // t * Bp / 32 + s, lane-major
+        const int ksteps = ga.Bp / 32;
+        const int kn = (ksteps + kGradWaves - 1) / kGradWaves;
+        const int kb = wave * kn, ke = kb + kn < ksteps ? kb + kn : ksteps;
+        const global_t<bf16x8>* a0 = (const global_t<bf16x8>*)gmem(ga.dzT[l]) + (int64_t)2 * to * ksteps * 64 + lane;
+        const global_t<bf16x8>* a1 = a0 + (int64_t)ksteps * 64;
+        const global_t<bf16x8>* b0 = (const global_t<bf16x8>*)gmem(ga.actT[l]) + (int64_t)2 * ti * ksteps * 64 + lane;
+        const global_t<bf16x8>* b1 = b0 + (int64_t)ksteps * 64;
+        floatx4 acc[2][2];
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int j = 0; j < 2; ++j) acc[i][j] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll 4
+        for (int k = kb; k < ke; ++k) {
+            const bf16x8 x0 = a0[k * 64], x1 = a1[k * 64], y0 = b0[k * 64], y1 = b1[k * 64];
+            acc[0][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x0, y0, acc[0][0], 0, 0, 0);
+            acc[0][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x0, y1, acc[0][1], 0, 0, 0);
+            acc[1][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x1, y0, acc[1][0], 0, 0, 0);
+            acc[1][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x1, y1, acc[1][1], 0, 0, 0);
+        }
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+#pragma unroll
+                for (int v = 0; v < 4; ++v)
+                    red[wave][(16 * i + 4 * (lane >> 4) + v) * LDR + 16 * j + (lane & 15)] = acc[i][j][v];
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < NE; ++j) {
+            const int o = t / 32 + j * (T / 32), i = t & 31;
+            float g = red[0][o * LDR + i];
+#pragma unroll
+            for (int w = 1; w < kGradWaves; ++w) g += red[w][o * LDR + i];
+            uint16_t h = 0;   // past the true sizes the copies hold zeros
+            if (in[j]) {
+                gmem(ga.gW[l])[at[j]] = g;
+                h = f2bf(adam_one(aa, pm.woff[l] + at[j], g, old[j]));
+            }
+            hw[0][o * LDH + i] = h;
+            hw[1][i * LDH + o] = h;
+        }
+        __syncthreads();
+        // two 1 KB fragments (16 rows, 32 columns) of each copy
+        if (wave < 4) {
+            const int c = wave >> 1, half = wave & 1;   // W or W^T
+            const int64_t frag = c ? (int64_t)(2 * ti + half) * (pout / 32) + to : (int64_t)(2 * to + half) * (pin / 32) + ti;
+            ((global_t<bf16x8>*)(gmem(aa.wbf) + (c ? pm.wtbo[l] : pm.wbo[l])))[frag * 64 + lane] =
+                *(const bf16x8*)(hw[c] + (16 * half + (lane & 15)) * LDH + 8 * (lane >> 4));
         }
         return;
     }
-    if (b < wblk + bblk) {
-        const int w = (b - wblk) * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
-        if (w >= nbias) return;
-        int l = 0, o = w;
+    float(*sum)[33] = (float(*)[33])red;
+    const int bblk = (nbias + 31) / 32;
+    if (b < ga.gtiles + bblk) {
+        const int n = (b - ga.gtiles) * 32 + (t & 31);   // bias n of all layers'
+        int l = 0, o = n;
         while (l + 1 < ga.n_layers && o >= ga.dout[l]) {
             o -= ga.dout[l];
             ++l;
         }
-        const int pout = ga.pout[l];
+        const bool in = n < nbias;
+        AdamState old{};
+        if (in && t < 32) old = adam_load(aa, pm.boff[l] + o);
         float s = 0.0f;
-        for (int k = lane; k < ga.nrb; k += 64) s += gmem(ga.bias_part[l])[(size_t)k * pout + o];
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
-        if (lane == 0) {
+        if (in) {
+            const global_t<float>* part = gmem(ga.bias_part[l]) + o;
+            const int pout = ga.pout[l];
+#pragma unroll 8
+            for (int k = t / 32; k < ga.nrb; k += T / 32) s += part[(size_t)k * pout];
+        }
+        sum[t / 32][t & 31] = s;
+        __syncthreads();
+        if (in && t < 32) {
+            s = sum[0][t];
+            for (int w = 1; w < T / 32; ++w) s += sum[w][t];
             gmem(ga.gb[l])[o] = s;
-            adam_one(aa, pm, pm.boff[l] + o, s);
+            adam_one(aa, pm.boff[l] + o, s, old);
         }
         return;
     }
     // the loss: sum of the row-block partials
-    __shared__ float red[256];
-    const int t = threadIdx.x;
     float s = 0.0f;
-    for (int i = t; i < aa.n_loss; i += 256) s += aa.loss_part[i];
-    red[t] = s;
+    for (int i = t; i < aa.n_loss; i += T) s += aa.loss_part[i];
+    red[0][t] = s;
     __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if (t < w) red[t] += red[t + w];
+    for (int w = T / 2; w > 0; w >>= 1) {
+        if (t < w) red[0][t] += red[0][t + w];
         __syncthreads();
     }
-    if (t == 0) aa.loss[0] = red[0] * aa.inv_count;
+    if (t == 0) aa.loss[0] = red[0][0] * aa.inv_count;
 }
 
 // Per-variable statistics of a training set (rows of 5 n_p floats).  Pass 0
@@ -748,16 +781,11 @@ hipError_t launch_train_rows(const NetArgs& na, const TrainArgs& ta, int nblocks
     return hipGetLastError();
 }
 
-hipError_t launch_wgrad(const GradArgs& ga, hipStream_t st) {
-    hipLaunchKernelGGL(k_wgrad, dim3(ga.tblk[ga.n_layers], ga.nks), dim3(kThreads), 0, st, ga);
-    return hipGetLastError();
-}
-
-hipError_t launch_reduce_adam(const GradArgs& ga, const ParamMap& pm, const AdamArgs& aa, hipStream_t st) {
+hipError_t launch_grad_adam(const GradArgs& ga, const ParamMap& pm, const AdamArgs& aa, hipStream_t st) {
     int nbias = 0;
     for (int l = 0; l < ga.n_layers; ++l) nbias += ga.dout[l];
-    const int blocks = ga.rblk[ga.n_layers] + (nbias + 3) / 4 + (aa.loss ? 1 : 0);
-    hipLaunchKernelGGL(k_reduce_adam, dim3(blocks), dim3(256), 0, st, ga, pm, aa, nbias);
+    const int blocks = ga.gtiles + (nbias + 31) / 32 + (aa.loss ? 1 : 0);
+    hipLaunchKernelGGL(k_grad_adam, dim3(blocks), dim3(64 * kGradWaves), 0, st, ga, pm, aa, nbias);
     return hipGetLastError();
 }
 

@@ -19,7 +19,7 @@
 // solves are failed.  Finished solves are copied out, and their arena blocks
 // released, while the next round runs.
 // (Two corrected P=3, two P=6 and two P=8 solves on 4^3, one of each on 8^3:
-// 9.0 ms with one thread for all orders, whose rounds waited for the slowest
+// 7.6 ms with one thread for all orders, whose rounds waited for the slowest
 // order and for the copies, 3.9 so.)
 //
 // Fallback of the learned part: a corrected solve (network forcing, Eq. (4),

@@ -189,3 +189,37 @@ def test_diagnostics_over_blocks(B, N, P):
     for v in range(5):
         assert abs(d[3 + v] - (wq * x[v]).sum()) <= 1e-12 * (wq * np.abs(x[v])).sum()
     assert np.array_equal(err.cpu().numpy(), np.abs(x - q1.reshape(5, N ** 3, -1))[1:4].reshape(3, -1).max(axis=1))
+
+
+# 32-row steps over eight wavefronts: one, a few, ten, more than eight each;
+# a width that is no multiple of 32
+@pytest.mark.parametrize("rows", [16, 80, 160, 1100])
+@pytest.mark.parametrize("dims", [(320, 256, 256, 320), (320, 40, 96, 320)])
+def test_gradient_of_a_batch(B, rows, dims):
+    """The gradient of a batch is the mean of its halves' gradients.  Each
+    row's share is the same number in both (its scale differs by a power of
+    two), so they differ by the order of float32 sums only: 1e-5 relative L2.
+    With a vanishing learning rate the weights and their bf16 copies stay, so
+    the whole batch gives the same bits once more."""
+    say("gradient of a batch", rows, dims)
+    layers = [(W, b + 0.01) for W, b in synthetic.mlp_init(list(dims), seed=9)]
+    norm = [1.0, 0.0, 0.0, 0.0, 178.0, 0.01, 1.0, 1.0, 1.0, 1.0] + [0.0] * 5 + [1e-3] * 5
+    model = B.Model(list(dims), B.pack_params(layers), norm)
+    rng = np.random.default_rng(rows)
+    x = rng.standard_normal((2 * rows, 320)).astype(np.float32)
+    y = (1e-3 * rng.standard_normal((2 * rows, 320))).astype(np.float32)
+    x, y = torch.from_numpy(x).cuda(), torch.from_numpy(y).cuda()
+    p0 = model.params.clone()
+
+    def grad(a, b):
+        loss = torch.zeros(1, dtype=torch.float32, device="cuda")
+        B.nn_train_step(model, x[a:b], y[a:b], lr=1e-30, loss=loss)
+        return model.grad.clone(), loss.item()
+
+    whole, loss = grad(0, 2 * rows)
+    (first, l0), (second, l1) = grad(0, rows), grad(rows, 2 * rows)
+    again, _ = grad(0, 2 * rows)
+    assert torch.equal(model.params, p0) and torch.equal(again, whole)
+    mean = 0.5 * (first.double() + second.double())
+    assert float((whole - mean).norm() / mean.norm()) < 1e-5
+    assert abs(loss - 0.5 * (l0 + l1)) < 1e-5 * loss
