@@ -74,29 +74,54 @@ namespace dgnn {
 
 // ---------------------------------------------------------------- kernels
 //
+// Order in which a launch takes the groups of a solve.  The hardware deals
+// workgroups out to the eight XCDs in turn, and each XCD has an L2 of its own.
+// kRange gives each XCD a contiguous range of the groups, the same in every
+// launch: most neighbours' traces and fluxes, and what the launch before left,
+// are in its own L2.  kTurn follows the workgroups, kBack in reverse.
+enum Order { kTurn, kRange, kBack };
+
+// groups of the elements of one solve
+template <int PP>
+__host__ __device__ __forceinline__ int groups(int E) {
+    return (E + Line<PP>::EPG - 1) / Line<PP>::EPG;
+}
+
+__device__ __forceinline__ int xcd_range(int b, int n) {
+    const int x = b & 7, each = n >> 3, more = n & 7;
+    return x * each + (x < more ? x : more) + (b >> 3);
+}
+template <int PP, Order ORDER>
+__device__ __forceinline__ int group_of_block(int E) {
+    return ORDER == kRange  ? xcd_range(blockIdx.x, groups<PP>(E))
+           : ORDER == kBack ? (int)(gridDim.x - 1 - blockIdx.x)
+                            : (int)blockIdx.x;
+}
+
 // k_grad and k_resid exist twice: for one solve with its descriptor in the
 // kernel arguments (two dependent loads fewer before a block's first data
 // load), and for a list of solves whose descriptors are in device memory.
 
-template <int PP>
+template <int PP, Order ORDER>
 __global__ void __launch_bounds__(Line<PP>::NT) k_traces(SolveDesc S) {
     __shared__ double sh[7 * Line<PP>::FS];
-    traces_group<PP>(S, blockIdx.x, threadIdx.x, sh);
+    traces_group<PP>(S, group_of_block<PP, ORDER>(S.E), threadIdx.x, sh);
 }
 
-template <int PP>
+template <int PP, Order ORDER>
 __global__ void __launch_bounds__(Line<PP>::NT) __attribute__((amdgpu_waves_per_eu(line_waves<GradLds<PP>, Line<PP>::NT>()))) k_grad1(SolveDesc S) {
     __shared__ double sh[GradLds<PP>::N];
     double q[Line<PP>::NN][5];
-    grad_group<PP>(S, blockIdx.x, threadIdx.x, sh, q);
+    grad_group<PP>(S, group_of_block<PP, ORDER>(S.E), threadIdx.x, sh, q);
 }
 
 template <int PP>
 __global__ void __launch_bounds__(Line<PP>::NT) __attribute__((amdgpu_waves_per_eu(line_waves<GradLds<PP>, Line<PP>::NT>()))) k_grad(DescList dl) {
     __shared__ double sh[GradLds<PP>::N];
-    const int si = find_solve(dl, blockIdx.x);
+    const int block = blockIdx.x;
+    const int si = find_solve(dl, block);
     double q[Line<PP>::NN][5];
-    grad_group<PP>(*dl.d[si], blockIdx.x - dl.blk[si], threadIdx.x, sh, q);
+    grad_group<PP>(*dl.d[si], block - dl.blk[si], threadIdx.x, sh, q);
 }
 
 // P = 3 with the forcing network at every stage (Eq. (4)): the BR1 pass of
@@ -120,7 +145,7 @@ __global__ void __launch_bounds__(kRowThreads) k_grad_net(SolveDesc S, NetArgs n
     const int ld = na.ld;
     uint16_t* bufA = (uint16_t*)(gsm + kRowWaves * GradLds<PP>::N);
     uint16_t* bufB = bufA + kRows * ld;
-    const int e0 = blockIdx.x * kRows;
+    const int e0 = xcd_range(blockIdx.x, S.E / kRows) * kRows;
 
     double q[1][5];
     grad_group<PP>(S, __builtin_amdgcn_readfirstlane(e0 + wave), lane, gsm + wave * GradLds<PP>::N, q);
@@ -155,12 +180,12 @@ __global__ void __launch_bounds__(kRowThreads) k_grad_beside_net(SolveDesc S, Ne
     extern __shared__ __attribute__((aligned(16))) double gsm[];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     if ((int)blockIdx.x >= net_blocks) {
-        const int e = ((int)blockIdx.x - net_blocks) * kRowWaves + wave;
+        const int e = xcd_range((int)blockIdx.x - net_blocks, net_blocks) * kRowWaves + wave;
         double q[1][5];
         if (e < S.E) grad_group<PP>(S, e, lane, gsm + wave * GradLds<PP>::N, q);
         return;
     }
-    const int ld = na.ld, e0 = blockIdx.x * kRows;
+    const int ld = na.ld, e0 = xcd_range(blockIdx.x, net_blocks) * kRows;
     uint16_t* bufA = (uint16_t*)gsm;
     uint16_t* bufB = bufA + kRows * ld;
     FirstTile<K0> first;
@@ -170,14 +195,13 @@ __global__ void __launch_bounds__(kRowThreads) k_grad_beside_net(SolveDesc S, Ne
     net256_forward<K0, ACT>(na, L::NP, T, e0, 0, bufA, bufB, ld, wave, lane, first);
 }
 
-// STREAM (see streams()): the groups in reverse, so that the launch begins
-// with what the BR1 pass left in the cache, and ends where the next begins.
-template <int PP, int UPDATE, int VISC, bool STREAM>
+// kBack (see streams()): the launch begins with what the BR1 pass left in the
+// cache, and ends where the next begins; the register passes by the caches.
+template <int PP, int UPDATE, int VISC, Order ORDER>
 __global__ void __launch_bounds__(Line<PP>::NT) __attribute__((amdgpu_waves_per_eu(line_waves<ResidLds<PP>, Line<PP>::NT>())))
 k_resid1(SolveDesc S, double rkA, double rkB, int first_stage) {
     __shared__ double sh[ResidLds<PP>::N];
-    const int group = STREAM ? gridDim.x - 1 - blockIdx.x : blockIdx.x;
-    resid_group<PP, UPDATE, VISC, STREAM>(S, group, threadIdx.x, sh, rkA, rkB, first_stage);
+    resid_group<PP, UPDATE, VISC, ORDER == kBack>(S, group_of_block<PP, ORDER>(S.E), threadIdx.x, sh, rkA, rkB, first_stage);
 }
 
 // the stage update of a list of solves, all with viscous fluxes
@@ -466,12 +490,6 @@ hipError_t launch_write_descs(const SolveDesc* host, int n, SolveDesc* dev, hipS
         default: return hipErrorInvalidValue;          \
     }
 
-// groups of the elements of one solve
-template <int PP>
-static int groups(int E) {
-    return (E + Line<PP>::EPG - 1) / Line<PP>::EPG;
-}
-
 // the list's first blocks (given in elements) in groups
 template <int PP>
 static DescList in_groups(const DescList& dl) {
@@ -480,13 +498,40 @@ static DescList in_groups(const DescList& dl) {
     return g;
 }
 
+// Whether what a stage goes through (state, register, two sets of traces,
+// viscous fluxes) exceeds the 256 MB of the memory-side cache: then the
+// register is kept out of it, and the stage update takes the groups in
+// reverse.  A step, us, without -> with: 16^3 P=7 (356 MB) 446 -> 424, 16^3
+// P=8 605 -> 565, 20^3 P=5 392 -> 372, 24^3 P=6 1030 -> 974, 32^3 P=6 2389 ->
+// 2266; below, 24^3 P=3 (230 MB) 223 -> 234, 16^3 P=6 (253 MB) 298 -> 304.
+template <int PP>
+static bool streams(int E) {
+    using L = Line<PP>;
+    return (size_t)E * (2 * 5 * L::NP + 6 * (5 + 5 + 4) * L::NF) * sizeof(double) > ((size_t)256 << 20);
+}
+
+// Where the single solves' launches take the groups in ranges: while the data
+// fit the memory-side cache, a step, us: 11^3 P=5 91.5 -> 83.3, 12^3 P=6 143 ->
+// 136, 14^3 P=7 302 -> 286, two of 8^3 P=3 with the network (whose blocks take
+// sixteen elements in a row) 111 -> 100.  With N a multiple of eight, groups in
+// turn have their y and z neighbours on the same XCD already, and ranges gain
+// nothing (16^3 P=6 300.5 -> 301.0, three of 8^3 P=8 324 -> 326): there only
+// P = 3 takes them.  Beyond the cache, eight ranges far apart cost more than
+// they save (24^3 P=6 962 -> 1120, 32^3 P=6 2310 -> 2540).
+template <int PP>
+static bool in_ranges(const SolveDesc& S) {
+    return !streams<PP>(S.E) && (PP == 4 || S.N % 8 != 0);
+}
+
 hipError_t launch_traces(int PPv, const SolveDesc& S, hipStream_t st) {
-    DG_DISPATCH_PP(PPv, hipLaunchKernelGGL(k_traces<PP>, dim3(groups<PP>(S.E)), dim3(Line<PP>::NT), 0, st, S));
+    DG_DISPATCH_PP(PPv, hipLaunchKernelGGL((in_ranges<PP>(S) ? k_traces<PP, kRange> : k_traces<PP, kTurn>),
+                                           dim3(groups<PP>(S.E)), dim3(Line<PP>::NT), 0, st, S));
     return hipGetLastError();
 }
 
 hipError_t launch_grad(int PPv, const SolveDesc& S, hipStream_t st) {
-    DG_DISPATCH_PP(PPv, hipLaunchKernelGGL(k_grad1<PP>, dim3(groups<PP>(S.E)), dim3(Line<PP>::NT), 0, st, S));
+    DG_DISPATCH_PP(PPv, hipLaunchKernelGGL((in_ranges<PP>(S) ? k_grad1<PP, kRange> : k_grad1<PP, kTurn>),
+                                           dim3(groups<PP>(S.E)), dim3(Line<PP>::NT), 0, st, S));
     return hipGetLastError();
 }
 
@@ -572,24 +617,12 @@ hipError_t launch_grad_net(int PPv, const SolveDesc& S, const NetArgs& na, const
     return hipGetLastError();
 }
 
-// Whether what a stage goes through (state, register, two sets of traces,
-// viscous fluxes) exceeds the 256 MB of the memory-side cache: then the
-// register is kept out of it, and the stage update takes the groups in
-// reverse.  A step, us, without -> with: 16^3 P=7 (356 MB) 446 -> 424, 16^3
-// P=8 605 -> 565, 20^3 P=5 392 -> 372, 24^3 P=6 1030 -> 974, 32^3 P=6 2389 ->
-// 2266; below, 24^3 P=3 (230 MB) 223 -> 234, 16^3 P=6 (253 MB) 298 -> 304.
-template <int PP>
-static bool streams(int E) {
-    using L = Line<PP>;
-    return (size_t)E * (2 * 5 * L::NP + 6 * (5 + 5 + 4) * L::NF) * sizeof(double) > ((size_t)256 << 20);
-}
-
 template <int PP, int UPDATE, int VISC>
 static void launch_resid1(const SolveDesc& S, double rkA, double rkB, int first_stage, hipStream_t st) {
-    const dim3 grid(groups<PP>(S.E)), block(Line<PP>::NT);
-    if (UPDATE && streams<PP>(S.E))
-        hipLaunchKernelGGL((k_resid1<PP, UPDATE, VISC, UPDATE == 1>), grid, block, 0, st, S, rkA, rkB, first_stage);
-    else hipLaunchKernelGGL((k_resid1<PP, UPDATE, VISC, false>), grid, block, 0, st, S, rkA, rkB, first_stage);
+    const auto kernel = UPDATE && streams<PP>(S.E) ? k_resid1<PP, UPDATE, VISC, UPDATE ? kBack : kTurn>
+                        : in_ranges<PP>(S)         ? k_resid1<PP, UPDATE, VISC, kRange>
+                                                   : k_resid1<PP, UPDATE, VISC, kTurn>;
+    hipLaunchKernelGGL(kernel, dim3(groups<PP>(S.E)), dim3(Line<PP>::NT), 0, st, S, rkA, rkB, first_stage);
 }
 
 template <int PP, int UPDATE>
