@@ -85,39 +85,13 @@ static void host_basis(int P, BasisTab& T) {
         }
         D[i][i] = diag;
     }
-    long double bp[kMaxPP], bm[kMaxPP];
-    for (int side = 0; side < 2; ++side) {
-        const long double t = side ? 1.0L : -1.0L;
-        long double den = 0.0L;
-        for (int k = 0; k < n; ++k) den += lam[k] / (t - x[k]);
-        for (int j = 0; j < n; ++j) (side ? bp : bm)[j] = (lam[j] / (t - x[j])) / den;
-    }
-    for (int side = 0; side < 2; ++side) {
-        const long double* b = side ? bp : bm;
-        long double lp = 0.0L, lm = 0.0L;
-        for (int m = 0; m < n; ++m) {
-            lp += b[m] * bp[m] / w[m];
-            lm += b[m] * bm[m] / w[m];
-        }
-        T.lface_p[side] = (double)lp;
-        T.lface_m[side] = (double)lm;
-        for (int l = 0; l < n; ++l) {
-            long double acc = 0.0L;
-            for (int m = 0; m < n; ++m) acc += b[m] * (D[l][m] * w[l] / w[m]);
-            T.dface[side][l] = (double)acc;
-        }
-    }
+    // values at the line's plus end
+    long double bp[kMaxPP], den = 0.0L;
+    for (int k = 0; k < n; ++k) den += lam[k] / (1.0L - x[k]);
+    for (int j = 0; j < n; ++j) bp[j] = (lam[j] / (1.0L - x[j])) / den;
     for (int i = 0; i < n; ++i) {
         T.nodes[i] = (double)x[i];
         T.w[i] = (double)w[i];
-        T.bp[i] = (double)bp[i];
-        T.bm[i] = (double)bm[i];
-        T.bpw[i] = (double)(bp[i] / w[i]);
-        T.bmw[i] = (double)(bm[i] / w[i]);
-        for (int j = 0; j < n; ++j) {
-            T.D[i * n + j] = (double)D[i][j];
-            T.Dhat[i * n + j] = (double)(D[j][i] * w[j] / w[i]);
-        }
     }
     // parity halves
     const int H = n / 2, M = (n + 1) / 2;
@@ -137,10 +111,7 @@ static void host_basis(int P, BasisTab& T) {
 }
 
 // 1D filter G1[a][j] from P_src to P_dst nodes (Sec. 2: nodal -> modal -> truncate -> nodal)
-static void host_filter(int Ps, int Pd, double* G1) {
-    BasisTab S, Dt;
-    host_basis(Ps, S);
-    host_basis(Pd, Dt);
+static void host_filter(int Ps, const BasisTab& S, int Pd, const BasisTab& Dt, double* G1) {
     const int ns = Ps + 1, nd = Pd + 1;
     for (int a = 0; a < nd; ++a)
         for (int j = 0; j < ns; ++j) {
@@ -166,7 +137,11 @@ static int ensure_tables(int dev) {
     if (g_tab_done[dev]) return DG_OK;
     std::vector<BasisTab> tabs(DG_MAX_ORDER);
     for (int P = 1; P <= DG_MAX_ORDER; ++P) host_basis(P, tabs[P - 1]);
-    DG_HIP(upload_basis_tables(tabs.data()));
+    std::vector<FilterTab> filters(DG_MAX_ORDER * DG_MAX_ORDER);
+    for (int Ps = 1; Ps <= DG_MAX_ORDER; ++Ps)
+        for (int Pd = 1; Pd <= Ps; ++Pd)
+            host_filter(Ps, tabs[Ps - 1], Pd, tabs[Pd - 1], filters[(Ps - 1) * DG_MAX_ORDER + Pd - 1].G);
+    DG_HIP(upload_basis_tables(tabs.data(), filters.data()));
     DG_HIP(scratch_setup(dev));
     g_tab_done[dev] = true;
     return DG_OK;
@@ -307,10 +282,24 @@ int diag_impl(const Mesh& m, const double* q, double* out_dev, char* ws, hipStre
     return DG_OK;
 }
 
-int project_impl(const Mesh& src, const Mesh& dst, const double* f_src, double* f_dst, hipStream_t st) {
-    double G1[kMaxPP * kMaxPP];
-    host_filter(src.P, dst.P, G1);
-    DG_HIP(launch_project(src.PP, dst.PP, src.E, G1, f_src, f_dst, st));
+int project_impl(const Mesh& src, const Mesh& dst, const double* f_src, double* f_dst, hipStream_t st, double* f_dst2) {
+    ProjectOut out{};
+    out.dst = f_dst;
+    out.dst2 = f_dst2;
+    DG_HIP(launch_project(src.PP, dst.PP, src.E, f_src, out, st));
+    return DG_OK;
+}
+
+// training pairs: rows of `first`, and of (G f_src - minus) / div
+static int project_pairs(const Mesh& src, const Mesh& dst, const double* f_src, const double* first, const double* minus,
+                         double div, float* x, float* y, hipStream_t st) {
+    ProjectOut out{};
+    out.first = first;
+    out.minus = minus;
+    out.div = div;
+    out.x = x;
+    out.y = y;
+    DG_HIP(launch_project(src.PP, dst.PP, src.E, f_src, out, st));
     return DG_OK;
 }
 
@@ -589,7 +578,7 @@ size_t dg_forcing_target_ws(const dg_mesh* hi, const dg_mesh* lo) {
     const size_t E = hi->m.E;
     size_t b = 0;
     b += align256(E * 5 * hi->m.n_p * sizeof(double));   // R_hi
-    b += 3 * align256(E * 5 * lo->m.n_p * sizeof(double)); // Gq, GR, R_lo
+    b += 3 * align256(E * 5 * lo->m.n_p * sizeof(double)); // Gq, one not used, R_lo
     b += ws_layout(hi->m).total;                           // residual workspaces (reused)
     b += ws_layout(lo->m).total;
     return b;
@@ -610,16 +599,14 @@ int dg_forcing_target(const dg_mesh* hi, const dg_mesh* lo, const double* q_hi, 
     char* p = (char*)ws;
     double* R_hi = (double*)p;  p += align256(E * 5 * hi->m.n_p * sizeof(double));
     double* Gq = (double*)p;    p += align256(E * 5 * lo->m.n_p * sizeof(double));
-    double* GR = (double*)p;    p += align256(E * 5 * lo->m.n_p * sizeof(double));
+    p += align256(E * 5 * lo->m.n_p * sizeof(double));   // of the size that callers know; not used
     double* R_lo = (double*)p;  p += align256(E * 5 * lo->m.n_p * sizeof(double));
     char* ws_hi = p;            p += ws_layout(hi->m).total;
     char* ws_lo = p;
     if ((rc = residual_impl(hi->m, q_hi, R_hi, ws_hi, st))) return rc;
     if ((rc = project_impl(hi->m, lo->m, q_hi, Gq, st))) return rc;
-    if ((rc = project_impl(hi->m, lo->m, R_hi, GR, st))) return rc;
     if ((rc = residual_impl(lo->m, Gq, R_lo, ws_lo, st))) return rc;
-    DG_HIP(launch_pack_pairs(lo->m.E, lo->m.n_p, 1.0, Gq, GR, R_lo, x_out, y_out, st));
-    return DG_OK;
+    return project_pairs(hi->m, lo->m, R_hi, Gq, R_lo, 1.0, x_out, y_out, st);
 }
 
 }  // extern "C"
@@ -651,16 +638,13 @@ int dg_increment_target(const dg_mesh* hi, const dg_mesh* lo, double* q_hi, doub
     double* q_nn = (double*)p;   p += fb;   // q_NN^n = G q_HO^n
     double* q_nn1 = (double*)p;  p += fb;   // its uncorrected low-order step
     double* k_lo = (double*)p;   p += fb;
-    double* qbar = (double*)p;   p += fb;   // G q_HO^{n+1}
+    p += fb;                                // of the size that callers know; not used
     char* ws_hi = p;             p += ws_layout(hi->m).total;
     char* ws_lo = p;
-    if ((rc = project_impl(hi->m, lo->m, q_hi, q_nn, st))) return rc;
-    if ((rc = project_impl(hi->m, lo->m, q_hi, q_nn1, st))) return rc;
+    if ((rc = project_impl(hi->m, lo->m, q_hi, q_nn, st, q_nn1))) return rc;
     if ((rc = rk_impl(lo->m, q_nn1, k_lo, dt_lo, 1, nullptr, 0, ws_lo, st))) return rc;
     if ((rc = rk_impl(hi->m, q_hi, k_hi, dt_lo / m_sub, m_sub, nullptr, 0, ws_hi, st))) return rc;
-    if ((rc = project_impl(hi->m, lo->m, q_hi, qbar, st))) return rc;
-    DG_HIP(launch_pack_pairs(lo->m.E, lo->m.n_p, dt_lo, q_nn, qbar, q_nn1, x_out, y_out, st));
-    return DG_OK;
+    return project_pairs(hi->m, lo->m, q_hi, q_nn, q_nn1, dt_lo, x_out, y_out, st);
 }
 
 }  // extern "C"

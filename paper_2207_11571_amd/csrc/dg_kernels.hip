@@ -23,6 +23,7 @@
 namespace dgnn {
 
 __constant__ BasisTab c_basis[DG_MAX_ORDER];
+__constant__ FilterTab c_filter[DG_MAX_ORDER * DG_MAX_ORDER];
 
 // The arrays a solve descriptor points to are addressed through gmem()
 // (global memory): read from a descriptor in memory they are generic
@@ -361,66 +362,70 @@ __global__ void __launch_bounds__(256) k_err_final(int rows, const double* __res
     if (t < 3) out[t] = fmax(fmax(red[0][t], red[1][t]), fmax(red[2][t], red[3][t]));
 }
 
-// Filter G: tensor-product 1D projection, one element per block, five variables.
-struct ProjArg {
-    double G[kMaxPP * kMaxPP];   // [PPd][PPs]
-};
+// Filter G: tensor-product 1D projection, one element per block, five
+// variables.  A thread takes a line along x (straight from memory), then along
+// y, then along z, each line's PPS entries to its PPD; the matrix is the same
+// for all threads, in scalar registers.  Latency-bound on small meshes: 8^3
+// elements, P = 8 to 3, with the matrix in the kernel's arguments (so in
+// memory of the host) and a thread per result 7.7 us, 5.5 so.  Pairs are packed
+// in the same launch (5 us, and the projection in memory, less).
+template <int PPS>
+constexpr int kProjectThreads = (5 * PPS * PPS + 63) / 64 * 64;
 
 template <int PPS, int PPD>
-__global__ void __launch_bounds__(256) k_project(ProjArg pa, int E, const double* __restrict__ src,
-                                                double* __restrict__ dst) {
-    constexpr int NS = PPS * PPS * PPS;
-    constexpr int ND = PPD * PPD * PPD;
-    __shared__ double G[PPD * PPS];
-    __shared__ double a[5 * NS];
-    __shared__ double b1[5 * PPD * PPS * PPS];
-    __shared__ double b2[5 * PPD * PPD * PPS];
-    const int e = blockIdx.x;
-    const int t = threadIdx.x;
-    for (int x = t; x < PPD * PPS; x += 256) G[x] = pa.G[x];
-    const size_t vss = (size_t)E * NS, vsd = (size_t)E * ND;
-    for (int x = t; x < 5 * NS; x += 256) {
-        const int v = x / NS, n = x - v * NS;
-        a[x] = src[v * vss + (size_t)e * NS + n];
+__global__ void __launch_bounds__(kProjectThreads<PPS>) k_project(int E, const double* __restrict__ src, ProjectOut out) {
+    constexpr int NS = PPS * PPS * PPS, ND = PPD * PPD * PPD;
+    __shared__ double b1[5 * PPS * PPS * PPD];   // [v][k][j][i']
+    __shared__ double b2[5 * PPS * PPD * PPD];   // [v][k][j'][i']
+    const int e = blockIdx.x, t = threadIdx.x;
+    const double* G = c_filter[(PPS - 2) * DG_MAX_ORDER + PPD - 2].G;
+    const auto line = [&](const double (&a)[PPS], double (&r)[PPD]) {
+#pragma unroll
+        for (int o = 0; o < PPD; ++o) {
+            double acc = 0.0;
+#pragma unroll
+            for (int i = 0; i < PPS; ++i) acc += G[o * PPS + i] * a[i];
+            r[o] = acc;
+        }
+    };
+    double a[PPS], r[PPD];
+    if (t < 5 * PPS * PPS) {
+        const int v = t / (PPS * PPS), kj = t - v * PPS * PPS;
+        const double* s = src + (size_t)v * E * NS + (size_t)e * NS + kj * PPS;
+#pragma unroll
+        for (int i = 0; i < PPS; ++i) a[i] = s[i];
+        line(a, r);
+#pragma unroll
+        for (int o = 0; o < PPD; ++o) b1[t * PPD + o] = r[o];
     }
     __syncthreads();
-    // along x: b1[v][k][j][i'] = sum_i G[i'][i] a[v][k][j][i]
-    for (int x = t; x < 5 * PPS * PPS * PPD; x += 256) {
-        const int ip = x % PPD, r = x / PPD;        // r = (v, k, j)
-        double acc = 0.0;
-        for (int i = 0; i < PPS; ++i) acc += G[ip * PPS + i] * a[r * PPS + i];
-        b1[x] = acc;
+    if (t < 5 * PPS * PPD) {
+        const int vk = t / PPD, ip = t - vk * PPD;
+#pragma unroll
+        for (int j = 0; j < PPS; ++j) a[j] = b1[(vk * PPS + j) * PPD + ip];
+        line(a, r);
+#pragma unroll
+        for (int o = 0; o < PPD; ++o) b2[(vk * PPD + o) * PPD + ip] = r[o];
     }
     __syncthreads();
-    // along y: b2[v][k][j'][i'] = sum_j G[j'][j] b1[v][k][j][i']
-    for (int x = t; x < 5 * PPS * PPD * PPD; x += 256) {
-        const int ip = x % PPD, jp = (x / PPD) % PPD, r = x / (PPD * PPD);   // r = (v, k)
-        double acc = 0.0;
-        for (int j = 0; j < PPS; ++j) acc += G[jp * PPS + j] * b1[(r * PPS + j) * PPD + ip];
-        b2[x] = acc;
-    }
-    __syncthreads();
-    // along z
-    for (int x = t; x < 5 * ND; x += 256) {
-        const int ip = x % PPD, jp = (x / PPD) % PPD, kp = (x / (PPD * PPD)) % PPD, v = x / ND;
-        double acc = 0.0;
-        for (int k = 0; k < PPS; ++k) acc += G[kp * PPS + k] * b2[((v * PPS + k) * PPD + jp) * PPD + ip];
-        dst[v * vsd + (size_t)e * ND + (x - v * ND)] = acc;
-    }
-}
-
-__global__ void __launch_bounds__(256) k_pack_pairs(int E, int NP, double div, const double* __restrict__ Gq,
-                                                   const double* __restrict__ GR, const double* __restrict__ R3,
-                                                   float* __restrict__ x, float* __restrict__ y) {
-    const size_t total = (size_t)5 * E * NP;
-    const size_t vs = (size_t)E * NP;
-    for (size_t idx = (size_t)blockIdx.x * 256 + threadIdx.x; idx < total; idx += (size_t)gridDim.x * 256) {
-        const int v = (int)(idx / vs);
-        const size_t rem = idx - v * vs;
-        const size_t e = rem / NP, n = rem - e * NP;
-        const size_t o = e * (5 * NP) + (size_t)v * NP + n;
-        x[o] = (float)Gq[idx];
-        y[o] = (float)((GR[idx] - R3[idx]) / div);
+    if (t < 5 * PPD * PPD) {
+        const int v = t / (PPD * PPD), ji = t - v * PPD * PPD;
+#pragma unroll
+        for (int k = 0; k < PPS; ++k) a[k] = b2[(v * PPS + k) * PPD * PPD + ji];
+        line(a, r);
+        const size_t at = (size_t)v * E * ND + (size_t)e * ND + ji;
+        const size_t row = (size_t)e * (5 * ND) + v * ND + ji;
+#pragma unroll
+        for (int o = 0; o < PPD; ++o) {
+            const size_t n = o * PPD * PPD;
+            if (out.y) {
+                out.x[row + n] = (float)out.first[at + n];
+                out.y[row + n] = (float)((r[o] - out.minus[at + n]) / out.div);
+            } else {
+                out.dst[at + n] = r[o];
+                if (out.dst2) out.dst2[at + n] = r[o];
+            }
+        }
     }
 }
 
@@ -465,7 +470,9 @@ void* scratch_device_ptr(int dev) {
 
 // ------------------------------------------------------------ host launchers
 
-hipError_t upload_basis_tables(const BasisTab* host_tabs) {
+hipError_t upload_basis_tables(const BasisTab* host_tabs, const FilterTab* host_filters) {
+    const hipError_t e = hipMemcpyToSymbol(HIP_SYMBOL(c_filter), host_filters, sizeof(c_filter));
+    if (e != hipSuccess) return e;
     return hipMemcpyToSymbol(HIP_SYMBOL(c_basis), host_tabs, sizeof(BasisTab) * DG_MAX_ORDER);
 }
 
@@ -673,14 +680,14 @@ hipError_t launch_err_inf(int PPv, int E, const double* q, const double* qref, d
 }
 
 template <int PPS>
-static hipError_t launch_project_s(int PPd, const ProjArg& pa, int E, const double* src, double* dst, hipStream_t st) {
+static hipError_t launch_project_s(int PPd, int E, const double* src, const ProjectOut& out, hipStream_t st) {
     switch (PPd) {
-#define DG_PROJ_CASE(V)                                                                                    \
-    case V:                                                                                                \
-        if constexpr (V <= PPS)                                                                            \
-            hipLaunchKernelGGL((k_project<PPS, V>), dim3(E), dim3(256), 0, st, pa, E, src, dst);           \
-        else                                                                                               \
-            return hipErrorInvalidValue;                                                                   \
+#define DG_PROJ_CASE(V)                                                                                      \
+    case V:                                                                                                  \
+        if constexpr (V <= PPS)                                                                              \
+            hipLaunchKernelGGL((k_project<PPS, V>), dim3(E), dim3(kProjectThreads<PPS>), 0, st, E, src, out); \
+        else                                                                                                 \
+            return hipErrorInvalidValue;                                                                     \
         break;
         DG_PROJ_CASE(2) DG_PROJ_CASE(3) DG_PROJ_CASE(4) DG_PROJ_CASE(5) DG_PROJ_CASE(6) DG_PROJ_CASE(7)
         DG_PROJ_CASE(8) DG_PROJ_CASE(9)
@@ -690,30 +697,9 @@ static hipError_t launch_project_s(int PPd, const ProjArg& pa, int E, const doub
     return hipGetLastError();
 }
 
-hipError_t launch_project(int PPs, int PPd, int E, const double* G1, const double* src, double* dst,
-                          hipStream_t st) {
-    ProjArg pa;
-    for (int x = 0; x < PPd * PPs; ++x) pa.G[x] = G1[x];
-    switch (PPs) {
-        case 2: return launch_project_s<2>(PPd, pa, E, src, dst, st);
-        case 3: return launch_project_s<3>(PPd, pa, E, src, dst, st);
-        case 4: return launch_project_s<4>(PPd, pa, E, src, dst, st);
-        case 5: return launch_project_s<5>(PPd, pa, E, src, dst, st);
-        case 6: return launch_project_s<6>(PPd, pa, E, src, dst, st);
-        case 7: return launch_project_s<7>(PPd, pa, E, src, dst, st);
-        case 8: return launch_project_s<8>(PPd, pa, E, src, dst, st);
-        case 9: return launch_project_s<9>(PPd, pa, E, src, dst, st);
-        default: return hipErrorInvalidValue;
-    }
-}
-
-hipError_t launch_pack_pairs(int E, int n_p, double div, const double* Gq, const double* GR, const double* R3,
-                             float* x, float* y, hipStream_t st) {
-    const size_t total = (size_t)5 * E * n_p;
-    int blocks = (int)((total + 255) / 256);
-    if (blocks > 65535) blocks = 65535;
-    hipLaunchKernelGGL(k_pack_pairs, dim3(blocks), dim3(256), 0, st, E, n_p, div, Gq, GR, R3, x, y);
-    return hipGetLastError();
+hipError_t launch_project(int PPs, int PPd, int E, const double* src, const ProjectOut& out, hipStream_t st) {
+    DG_DISPATCH_PP(PPs, return launch_project_s<PP>(PPd, E, src, out, st));
+    return hipErrorInvalidValue;
 }
 
 }  // namespace dgnn

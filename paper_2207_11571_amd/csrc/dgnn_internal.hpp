@@ -23,21 +23,9 @@ constexpr int kMaxDevices = 64;             // GPUs a process can build meshes o
 struct BasisTab {
     double nodes[kMaxPP];
     double w[kMaxPP];
-    double D[kMaxPP * kMaxPP];
-    double Dhat[kMaxPP * kMaxPP];
-    double bp[kMaxPP];
-    double bm[kMaxPP];
-    double bpw[kMaxPP];
-    double bmw[kMaxPP];
-    // the weak derivative along a line evaluated at the line's minus (0) and
-    // plus (1) end: dface[s][l] = sum_m b_s(m) Dhat[m][l] and the lifting
-    // weights lface_p[s] = sum_m b_s(m) b+_m/w_m, lface_m[s] = sum_m b_s(m) b-_m/w_m
-    double dface[2][kMaxPP];
-    double lface_p[2];
-    double lface_m[2];
-    // The same operators split by parity about the middle of the line (the
-    // nodes are symmetric), for lines held in registers: with H = PP / 2
-    // pairs, M = (PP + 1) / 2, mirrored index i' = P - i,
+    // The weak derivative Dhat[i][m] = D[m][i] w[m] / w[i], its lifting weights
+    // bpw[i] = bp[i] / w[i] and the end values' weights bp, split by parity about
+    // the middle of the line (the nodes are symmetric): with H = PP / 2 pairs, M = (PP + 1) / 2, mirrored index i' = P - i,
     //   nS[i*H + m] = -(Dhat[i][m] - Dhat[i][m']) / 2,  nT[i*M + m] = -(Dhat[i][m] + Dhat[i][m']) / 2
     // (-Dhat[i][m] at the middle m), lS[i] = (bpw[i] + bpw[i']) / 2, lT[i] = (bpw[i] - bpw[i']) / 2
     // (lS = bpw at the middle i), iE[m] = (bp[m] + bp[m']) / 2 (bp at the middle), iO[m] = (bp[m] - bp[m']) / 2
@@ -147,7 +135,11 @@ void fill_phys(const dg_params& p, Phys& ph);
 
 // ----------------------------------------------------------- host launchers
 // All return hipSuccess or the launch error.  `descs` is device memory.
-hipError_t upload_basis_tables(const BasisTab* host_tabs /* index P-1 */);
+// filter matrices G1 [PPd][PPs], at (Ps - 1) * DG_MAX_ORDER + Pd - 1, Pd <= Ps
+struct FilterTab {
+    double G[kMaxPP * kMaxPP];
+};
+hipError_t upload_basis_tables(const BasisTab* host_tabs /* index P-1 */, const FilterTab* host_filters);
 // address of the no-alloc stepper's scratch on device dev (looked up once, by
 // scratch_setup with dev current); null before the set-up
 hipError_t scratch_setup(int dev);
@@ -177,10 +169,18 @@ hipError_t launch_diag(int PP, const Phys& ph, int N, const double* q, double* p
                        double* out, hipStream_t st);
 hipError_t launch_err_inf(int PP, int E, const double* q, const double* qref, double* partial,
                           double* out, hipStream_t st);
-hipError_t launch_project(int PPs, int PPd, int E, const double* G1 /* host [PPd][PPs] */,
-                          const double* src, double* dst, hipStream_t st);
-hipError_t launch_pack_pairs(int E, int n_p, double div, const double* Gq, const double* GR, const double* R3,
-                             float* x, float* y, hipStream_t st);
+// filter G of a field: into dst (and dst2, if given), or, with y given, its
+// row of the pair (first, (G field - minus) / div) as float rows x, y
+struct ProjectOut {
+    double* dst;
+    double* dst2;
+    const double* first;
+    const double* minus;
+    double div;
+    float* x;
+    float* y;
+};
+hipError_t launch_project(int PPs, int PPd, int E, const double* src, const ProjectOut& out, hipStream_t st);
 
 hipError_t launch_net_forcing(const NetArgs& na, int n_p, const NetTarget* targets, int nt,
                               int nblocks, hipStream_t st);             // out += s(q)
@@ -255,7 +255,8 @@ extern const double kRkB[3];
 int make_mesh(const dg_params* prm, Mesh& M);
 int residual_impl(const Mesh& m, const double* q, double* dqdt, char* ws, hipStream_t st);
 int diag_impl(const Mesh& m, const double* q, double* out_dev, char* ws, hipStream_t st);
-int project_impl(const Mesh& src, const Mesh& dst, const double* f_src, double* f_dst, hipStream_t st);
+int project_impl(const Mesh& src, const Mesh& dst, const double* f_src, double* f_dst, hipStream_t st,
+                 double* f_dst2 = nullptr);
 int init_tgv_impl(const Mesh& m, double* q, hipStream_t st);
 double stable_dt_from_diag(const Mesh& m, const double* diag_host, double cfl);
 

@@ -223,3 +223,19 @@ def test_gradient_of_a_batch(B, rows, dims):
     mean = 0.5 * (first.double() + second.double())
     assert float((whole - mean).norm() / mean.norm()) < 1e-5
     assert abs(loss - 0.5 * (l0 + l1)) < 1e-5 * loss
+
+
+# blocks smaller than a wavefront, equal orders, the widest
+@pytest.mark.parametrize("Ps,Pd", [(1, 1), (2, 1), (5, 4), (7, 2), (8, 1), (8, 8)])
+def test_filter_orders(B, Ps, Pd):
+    """Filter G against the oracle: two roundings per product in up to 27
+    sums of order-one terms, 1e-13 of the largest value."""
+    from oracle import dg, projection
+    say("filter orders", Ps, Pd)
+    N = 3
+    src = np.random.default_rng(Ps * 10 + Pd).standard_normal((5, N ** 3, (Ps + 1) ** 3))
+    ms, md = B.Mesh(N, Ps, 100.0), B.Mesh(N, Pd, 100.0)
+    out = md.field(float("nan"))
+    B.dg_project(ms, md, torch.from_numpy(src).cuda(), out)
+    ref = dg.to_flat(projection.project(dg.to_blocks(src, N, Ps), Ps, Pd))
+    assert np.max(np.abs(out.cpu().numpy() - ref)) < 1e-13 * np.max(np.abs(ref))
