@@ -103,14 +103,32 @@ __device__ __forceinline__ int group_of_block(int E) {
 // kernel arguments (two dependent loads fewer before a block's first data
 // load), and for a list of solves whose descriptors are in device memory.
 
+// What a block's first loads need comes as arguments of its own ahead of the
+// descriptor: the first sixteen words of a kernel's arguments are in scalar
+// registers when its wavefronts start (the build asks for that), where a load
+// of them would be the first of three dependent ones.  A step: 4^3 P=3 24.3 ->
+// 21.5 us, 8^3 P=3 27.9 -> 25.9, 8^3 P=6 57.0 -> 55.0, 16^3 P=3 76.8 -> 73.1.
+__device__ __forceinline__ SolveDesc with_head(const SolveDesc& D, const double* state, const double* qtr_in, double* fv, int N,
+                                               int E) {
+    SolveDesc S = D;
+    S.q = const_cast<double*>(state);
+    S.qtr_in = qtr_in;
+    S.fv = fv;
+    S.N = N;
+    S.E = E;
+    return S;
+}
+
 template <int PP, Order ORDER>
-__global__ void __launch_bounds__(Line<PP>::NT) k_traces(SolveDesc S) {
+__global__ void __launch_bounds__(Line<PP>::NT) k_traces(const double* state, int N, int E, SolveDesc D) {
     __shared__ double sh[7 * Line<PP>::FS];
+    const SolveDesc S = with_head(D, state, nullptr, nullptr, N, E);
     traces_group<PP>(S, group_of_block<PP, ORDER>(S.E), threadIdx.x, sh);
 }
 
 template <int PP, Order ORDER>
-__global__ void __launch_bounds__(Line<PP>::NT) __attribute__((amdgpu_waves_per_eu(line_waves<GradLds<PP>, Line<PP>::NT>()))) k_grad1(SolveDesc S) {
+__global__ void __launch_bounds__(Line<PP>::NT) __attribute__((amdgpu_waves_per_eu(line_waves<GradLds<PP>, Line<PP>::NT>()))) k_grad1(const double* state, const double* qtr_in, double* fv, int N, int E, SolveDesc D) {
+    const SolveDesc S = with_head(D, state, qtr_in, fv, N, E);
     __shared__ double sh[GradLds<PP>::N];
     double q[Line<PP>::NN][5];
     grad_group<PP>(S, group_of_block<PP, ORDER>(S.E), threadIdx.x, sh, q);
@@ -137,7 +155,8 @@ __global__ void __launch_bounds__(Line<PP>::NT) __attribute__((amdgpu_waves_per_
 // numbers.  One solve per launch (its descriptor in the kernel arguments),
 // E a multiple of 16.
 template <int PP, int K0, int ACT>
-__global__ void __launch_bounds__(kRowThreads) k_grad_net(SolveDesc S, NetArgs na, NetTarget T) {
+__global__ void __launch_bounds__(kRowThreads) k_grad_net(const double* state, const double* qtr_in, double* fv, int N, int E, SolveDesc D, NetArgs na, NetTarget T) {
+    const SolveDesc S = with_head(D, state, qtr_in, fv, N, E);
     using L = Line<PP>;
     static_assert(L::NT == 64 && L::NP == 64 && L::EPG == 1, "one element per wavefront, one node per lane");
     constexpr int NP = L::NP;
@@ -175,7 +194,10 @@ __global__ void __launch_bounds__(kRowThreads) k_grad_net(SolveDesc S, NetArgs n
 // (512 elements: 12.3 us, against 12.3 us for the network and 4.0 us for the
 // BR1 pass).
 template <int PP, int K0, int ACT>
-__global__ void __launch_bounds__(kRowThreads) k_grad_beside_net(SolveDesc S, NetArgs na, NetTarget T, int net_blocks) {
+__global__ void __launch_bounds__(kRowThreads) k_grad_beside_net(const double* state, const double* qtr_in, double* fv, int N, int E, int v0, int v1, int v2, int v3, int v4,
+                  int net_blocks, SolveDesc D, NetArgs na, double* forcing) {
+    const SolveDesc S = with_head(D, state, qtr_in, fv, N, E);
+    const NetTarget T = {state, forcing, E, 0};
     using L = Line<PP>;
     static_assert(L::NT == 64 && L::EPG == 1, "one element per wavefront");
     extern __shared__ __attribute__((aligned(16))) double gsm[];
@@ -190,7 +212,8 @@ __global__ void __launch_bounds__(kRowThreads) k_grad_beside_net(SolveDesc S, Ne
     uint16_t* bufA = (uint16_t*)gsm;
     uint16_t* bufB = bufA + kRows * ld;
     FirstTile<K0> first;
-    net_gather<K0>(na, L::NP, T, e0, bufA, ld, wave, lane, first);
+    const int in_var[5] = {v0, v1, v2, v3, v4};
+    net_gather<K0>(na, in_var, L::NP, T, e0, bufA, ld, wave, lane, first);
     net_zero_unforced(na, L::NP, T, e0, threadIdx.x);
     __syncthreads();
     net256_forward<K0, ACT>(na, L::NP, T, e0, 0, bufA, bufB, ld, wave, lane, first);
@@ -200,7 +223,9 @@ __global__ void __launch_bounds__(kRowThreads) k_grad_beside_net(SolveDesc S, Ne
 // cache, and ends where the next begins; the register passes by the caches.
 template <int PP, int UPDATE, int VISC, Order ORDER>
 __global__ void __launch_bounds__(Line<PP>::NT) __attribute__((amdgpu_waves_per_eu(line_waves<ResidLds<PP>, Line<PP>::NT>())))
-k_resid1(SolveDesc S, double rkA, double rkB, int first_stage) {
+k_resid1(const double* state, const double* qtr_in, double* fv, int N, int E, int first_stage, SolveDesc D, double rkA,
+         double rkB) {
+    const SolveDesc S = with_head(D, state, qtr_in, fv, N, E);
     __shared__ double sh[ResidLds<PP>::N];
     resid_group<PP, UPDATE, VISC, ORDER == kBack>(S, group_of_block<PP, ORDER>(S.E), threadIdx.x, sh, rkA, rkB, first_stage);
 }
@@ -366,8 +391,8 @@ __global__ void __launch_bounds__(256) k_err_final(int rows, const double* __res
 // variables.  A thread takes a line along x (straight from memory), then along
 // y, then along z, each line's PPS entries to its PPD; the matrix is the same
 // for all threads, in scalar registers.  Latency-bound on small meshes: 8^3
-// elements, P = 8 to 3, with the matrix in the kernel's arguments (so in
-// memory of the host) and a thread per result 7.7 us, 5.5 so.  Pairs are packed
+// elements, P = 8 to 3, with the matrix in the kernel's arguments, read lane by
+// lane, and a thread per result 7.7 us, 5.5 so.  Pairs are packed
 // in the same launch (5 us, and the projection in memory, less).
 template <int PPS>
 constexpr int kProjectThreads = (5 * PPS * PPS + 63) / 64 * 64;
@@ -532,13 +557,14 @@ static bool in_ranges(const SolveDesc& S) {
 
 hipError_t launch_traces(int PPv, const SolveDesc& S, hipStream_t st) {
     DG_DISPATCH_PP(PPv, hipLaunchKernelGGL((in_ranges<PP>(S) ? k_traces<PP, kRange> : k_traces<PP, kTurn>),
-                                           dim3(groups<PP>(S.E)), dim3(Line<PP>::NT), 0, st, S));
+                                           dim3(groups<PP>(S.E)), dim3(Line<PP>::NT), 0, st, S.q, S.N, S.E, S));
     return hipGetLastError();
 }
 
 hipError_t launch_grad(int PPv, const SolveDesc& S, hipStream_t st) {
     DG_DISPATCH_PP(PPv, hipLaunchKernelGGL((in_ranges<PP>(S) ? k_grad1<PP, kRange> : k_grad1<PP, kTurn>),
-                                           dim3(groups<PP>(S.E)), dim3(Line<PP>::NT), 0, st, S));
+                                           dim3(groups<PP>(S.E)), dim3(Line<PP>::NT), 0, st, S.q, S.qtr_in,
+                                           S.fv, S.N, S.E, S));
     return hipGetLastError();
 }
 
@@ -609,7 +635,9 @@ hipError_t launch_grad_net(int PPv, const SolveDesc& S, const NetArgs& na, const
         const hipError_t e = allow_lds((const void*)kernel, 4 + nw, smem);
         if (e != hipSuccess) return e;
         const int blocks = (T.E + kRows - 1) / kRows;
-        hipLaunchKernelGGL(kernel, dim3(2 * blocks), dim3(kRowThreads), smem, st, S, na, T, blocks);
+        const int* v = na.in_var;
+        hipLaunchKernelGGL(kernel, dim3(2 * blocks), dim3(kRowThreads), smem, st, S.q, S.qtr_in, S.fv, S.N, S.E, v[0], v[1],
+                           v[2], v[3], v[4], blocks, S, na, T.out);
         return hipGetLastError();
     }
     const size_t smem = grad + rows;
@@ -620,7 +648,7 @@ hipError_t launch_grad_net(int PPv, const SolveDesc& S, const NetArgs& na, const
                                   : k_grad_net<4, 0, 0>;
     const hipError_t e = allow_lds((const void*)kernel, nw, smem);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(kernel, dim3(T.E / kRows), dim3(kRowThreads), smem, st, S, na, T);
+    hipLaunchKernelGGL(kernel, dim3(T.E / kRows), dim3(kRowThreads), smem, st, S.q, S.qtr_in, S.fv, S.N, S.E, S, na, T);
     return hipGetLastError();
 }
 
@@ -629,7 +657,8 @@ static void launch_resid1(const SolveDesc& S, double rkA, double rkB, int first_
     const auto kernel = UPDATE && streams<PP>(S.E) ? k_resid1<PP, UPDATE, VISC, UPDATE ? kBack : kTurn>
                         : in_ranges<PP>(S)         ? k_resid1<PP, UPDATE, VISC, kRange>
                                                    : k_resid1<PP, UPDATE, VISC, kTurn>;
-    hipLaunchKernelGGL(kernel, dim3(groups<PP>(S.E)), dim3(Line<PP>::NT), 0, st, S, rkA, rkB, first_stage);
+    hipLaunchKernelGGL(kernel, dim3(groups<PP>(S.E)), dim3(Line<PP>::NT), 0, st, S.q, S.qtr_in, S.fv, S.N, S.E,
+                       first_stage, S, rkA, rkB);
 }
 
 template <int PP, int UPDATE>

@@ -270,8 +270,8 @@ struct Five {
 // are there: all wavefronts' loads go through one queue, and the last one's
 // states would wait for the others' weights.
 template <int K0>
-__device__ __forceinline__ void net_gather(const NetArgs& na, int NP, const NetTarget& T, int e0, uint16_t* bufA, int ld,
-                                           int wave, int lane, FirstTile<K0 ? K0 : 1>& first) {
+__device__ __forceinline__ void net_gather(const NetArgs& na, const int (&in_var)[5], int NP, const NetTarget& T, int e0,
+                                           uint16_t* bufA, int ld, int wave, int lane, FirstTile<K0 ? K0 : 1>& first) {
     const size_t vs = (size_t)T.E * NP;
     const int din = na.dims[0], pin = na.pdims[0];
     const int e = e0 + wave;
@@ -280,7 +280,7 @@ __device__ __forceinline__ void net_gather(const NetArgs& na, int NP, const NetT
     const global_t<const double>* q = gmem(T.q) + (size_t)(in ? e : e0) * NP;
     size_t var[5];   // beyond n_in: variable 0, read and not used
 #pragma unroll
-    for (int j = 0; j < 5; ++j) var[j] = na.in_var[j] * vs;
+    for (int j = 0; j < 5; ++j) var[j] = in_var[j] * vs;
     for (int n0 = 0; n0 < NP; n0 += 64) {
         const int n = n0 + lane;
         const int nc = n < NP ? n : NP - 1;

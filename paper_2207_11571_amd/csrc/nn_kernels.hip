@@ -48,7 +48,7 @@ __global__ void __launch_bounds__(kRowThreads) k_net_forcing(NetArgs na, int NP,
     const size_t vs = (size_t)E * NP;
 
     FirstTile<K0 ? K0 : 1> first;
-    net_gather<K0>(na, NP, T, e0, bufA, ld, wave, lane, first);
+    net_gather<K0>(na, na.in_var, NP, T, e0, bufA, ld, wave, lane, first);
     if (!accumulate) net_zero_unforced(na, NP, T, e0, t);
     __syncthreads();
     if constexpr (K0 > 0) net256_forward<K0, ACT>(na, NP, T, e0, accumulate, bufA, bufB, ld, wave, lane, first);
@@ -246,9 +246,13 @@ __device__ __forceinline__ void warm_weights(const NetArgs& na, int t) {
     asm volatile("" ::"v"(sum));
 }
 
+// What a block's first loads need is ahead of the structures: the first sixteen
+// words of a kernel's arguments are in scalar registers when it starts.
 template <int K0, int ACT>
-__global__ void __launch_bounds__(kRowThreads) k_train256(NetArgs na, TrainArgs ta) {
-    if ((int)blockIdx.x >= ta.Bp / kRows) return warm_weights(na, threadIdx.x);
+__global__ void __launch_bounds__(kRowThreads)
+k_train256(const float* rows, const int32_t* idx, int B, int Bp, int npv, int v0, int v1, int v2, int v3, int v4, NetArgs na,
+           TrainArgs ta) {
+    if ((int)blockIdx.x >= Bp / kRows) return warm_weights(na, threadIdx.x);
     extern __shared__ __attribute__((aligned(16))) uint16_t smem[];
     const int L = na.n_layers, ld = na.ld;
     auto act = [&](int l) { return smem + l * kRows * ld; };
@@ -259,9 +263,9 @@ __global__ void __launch_bounds__(kRowThreads) k_train256(NetArgs na, TrainArgs 
     const int t = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(t >> 6), lane = t & 63;
     const int r = lane & 15, g = lane >> 4;
-    const int r0 = blockIdx.x * kRows, B = ta.B, Bp = ta.Bp;
+    const int r0 = blockIdx.x * kRows;
+    const int in_var[5] = {v0, v1, v2, v3, v4};
     const int Np = na.pdims[L], Nd = na.dims[L], nt = Np / 16;
-    const int npv = na.dims[0] / na.n_in;
     const size_t rw = (size_t)5 * npv;
 
     // gather + normalise + bf16: wavefront w row w
@@ -271,15 +275,15 @@ __global__ void __launch_bounds__(kRowThreads) k_train256(NetArgs na, TrainArgs 
         const int row = r0 + wave;
         const bool in = row < B;
         const int rc = in ? row : B - 1;
-        const size_t src = ta.idx ? (size_t)gmem(ta.idx)[rc] : (size_t)rc;
-        const global_t<const float>* x = gmem(ta.x) + src * rw;
+        const size_t src = idx ? (size_t)gmem(idx)[rc] : (size_t)rc;
+        const global_t<const float>* x = gmem(rows) + src * rw;
         uint16_t* o = act(0) + wave * ld;
         float xv[5];
         for (int n0 = 0; n0 < npv; n0 += 64) {
             const int n = n0 + lane;
             const int nc = n < npv ? n : npv - 1;
 #pragma unroll
-            for (int j = 0; j < 5; ++j) xv[j] = x[na.in_var[j] * npv + nc];
+            for (int j = 0; j < 5; ++j) xv[j] = x[in_var[j] * npv + nc];
             if (n0 == 0) {
 #pragma unroll
                 for (int j = 0; j < 5; ++j) arrived(xv[j]);
@@ -299,7 +303,7 @@ __global__ void __launch_bounds__(kRowThreads) k_train256(NetArgs na, TrainArgs 
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         const int row = r0 + 4 * g + i < B ? r0 + 4 * g + i : B - 1;
-        ysrc[i] = (ta.idx ? (size_t)gmem(ta.idx)[row] : (size_t)row) * rw;
+        ysrc[i] = (idx ? (size_t)gmem(idx)[row] : (size_t)row) * rw;
     }
     __syncthreads();
     // its place in the transposed arrays, in column tile 0: batch rows
@@ -778,26 +782,38 @@ hipError_t launch_fill_f32(float* p, float v, size_t n, hipStream_t st) {
 
 size_t train_smem_bytes(const NetArgs& na) { return net_smem_bytes(na, na.n_layers + 2); }
 
-hipError_t launch_train_rows(const NetArgs& na, const TrainArgs& ta, int nblocks, hipStream_t st) {
-    const size_t smem = train_smem_bytes(na);
-    auto kernel = k_train_rows;
-    // the backward chain starts with as many steps as the forward one where
-    // the network reads as many columns as it forces
-    if (na.pdims[na.n_layers] == na.pdims[0]) switch (net256_steps(na)) {
-        case 3: kernel = na.act ? k_train256<3, 1> : k_train256<3, 0>; break;
-        case 5: kernel = na.act ? k_train256<5, 1> : k_train256<5, 0>; break;
-        case 6: kernel = na.act ? k_train256<6, 1> : k_train256<6, 0>; break;
-        case 10: kernel = na.act ? k_train256<10, 1> : k_train256<10, 0>; break;
-        default: break;
-    }
+template <int K0>
+static hipError_t launch_train256(const NetArgs& na, const TrainArgs& ta, int blocks, size_t smem, hipStream_t st) {
+    const auto kernel = na.act ? k_train256<K0, 1> : k_train256<K0, 0>;
     if (smem > 65536) {
         hipError_t e = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
         if (e != hipSuccess) return e;
     }
+    const int* v = na.in_var;
+    hipLaunchKernelGGL(kernel, dim3(blocks), dim3(kRowThreads), smem, st, ta.x, ta.idx, ta.B, ta.Bp,
+                       na.dims[0] / na.n_in, v[0], v[1], v[2], v[3], v[4], na, ta);
+    return hipGetLastError();
+}
+
+hipError_t launch_train_rows(const NetArgs& na, const TrainArgs& ta, int nblocks, hipStream_t st) {
+    const size_t smem = train_smem_bytes(na);
     // one block on each XCD reads the weights ahead of the row blocks (batch
     // 1024, eight row blocks an XCD: no change; 2048 21.6 -> 21.9 us)
-    const int warm = kernel != k_train_rows && 8 * nblocks <= cu_count() ? 8 : 0;
-    hipLaunchKernelGGL(kernel, dim3(nblocks + warm), dim3(kRowThreads), smem, st, na, ta);
+    const int ahead = nblocks + (8 * nblocks <= cu_count() ? 8 : 0);
+    // the backward chain starts with as many steps as the forward one where
+    // the network reads as many columns as it forces
+    if (na.pdims[na.n_layers] == na.pdims[0]) switch (net256_steps(na)) {
+        case 3: return launch_train256<3>(na, ta, ahead, smem, st);
+        case 5: return launch_train256<5>(na, ta, ahead, smem, st);
+        case 6: return launch_train256<6>(na, ta, ahead, smem, st);
+        case 10: return launch_train256<10>(na, ta, ahead, smem, st);
+        default: break;
+    }
+    if (smem > 65536) {
+        hipError_t e = hipFuncSetAttribute((const void*)k_train_rows, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+        if (e != hipSuccess) return e;
+    }
+    hipLaunchKernelGGL(k_train_rows, dim3(nblocks), dim3(kRowThreads), smem, st, na, ta);
     return hipGetLastError();
 }
 
