@@ -20,7 +20,6 @@ host (all threads and one thread, plain P = 6 and the corrected P = 3 stage).
     python bench.py [--gpus 1] [--steps 100] [--warmup 1]
 """
 import argparse
-import hashlib
 import json
 import math
 import os
@@ -255,14 +254,14 @@ def cpu_baseline(steps=2):
                                              f"network) of the 16^3 P=3 Re-200 TGV, {t_c3:.2f} s"}}
 
 
-def counter_traffic(kernel_file, tag):
+def counter_traffic(tag):
     """HBM bytes per launch from the committed rocprofv3 counter summary,
     if it was taken on the current kernel source."""
     path = os.path.join(ROOT, "profiles", f"{tag}_counters.md")
     if not os.path.exists(path):
         return None
-    src = open(os.path.join(ROOT, "paper_2207_11571_amd", "csrc", kernel_file), "rb").read()
-    sha = hashlib.sha256(src).hexdigest()[:16]
+    from paper_2207_11571_amd.prof_summary import stage_sources_sha
+    sha = stage_sources_sha()
     rec = {}
     for line in open(path):
         if ":" in line and line.startswith("- "):
@@ -336,7 +335,7 @@ def main():
         ms = case["kernel_ms"]["resid"]
         alg = ALG_BYTES_RESID * case["nodes"]
         achieved = alg / (ms * 1e-3) / 1e9
-        traffic = counter_traffic("dg_kernels.hip", tag)
+        traffic = counter_traffic(tag)
         return {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                 "frac": achieved / HBM_PEAK_GBS, "traffic": traffic, "kernel": kernel,
                 "algorithmic_bytes_per_launch": alg, "mean_launch_ms": ms,
@@ -345,8 +344,8 @@ def main():
                 "counter_frac": None if traffic is None else traffic / (ms * 1e-3) / 1e9 / HBM_PEAK_GBS,
                 "stage_algorithmic_frac": case["dof_updates_per_s"] * ALG_BYTES_RESID / (HBM_PEAK_GBS * 1e9)}
 
-    roofline = resid_roofline(head, "k_resid1<7,1> (residual + RK stage update, 16^3 P=6, one solve: descriptor in the kernel arguments)", "k_resid_p6")
-    roofline["p8"] = resid_roofline(p8, "k_resid_loop<9,1> (residual + RK stage update, 16^3 P=8, one block per CU walking the elements)", "k_resid_p8")
+    roofline = resid_roofline(head, "k_resid1<7,1,1,kTurn> (residual + RK stage update, 16^3 P=6, a line of nodes per thread)", "k_resid_p6")
+    roofline["p8"] = resid_roofline(p8, "k_resid1<9,1,1,kBack> (residual + RK stage update, 16^3 P=8, a line of nodes per thread)", "k_resid_p8")
     stage_alg_frac = roofline["stage_algorithmic_frac"]
 
     serving = None

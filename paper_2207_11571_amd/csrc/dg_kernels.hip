@@ -609,8 +609,9 @@ static hipError_t allow_lds(const void* kernel, int slot, size_t smem) {
     return hipSuccess;
 }
 
-// Two corrected steps of 8^3 elements take 130 us apart, 114 us beside; 16^3
-// elements fill every CU with one fused block (one step 118 us).  In between,
+// Two corrected steps of 8^3 elements took 130 us apart and 114 us beside (96 us
+// with what came after); 16^3 elements fill every CU with one fused block (one
+// step 112 us).  In between,
 // blocks of both kinds would take more than one round of the CUs.
 GradNetForm grad_net_form(const NetArgs& na, int E) {
     if (E % kRows == 0 && E / kRows >= cu_count()) return kGradNetFused;

@@ -20,10 +20,10 @@
 //
 // What bounds the stage kernels is the traffic to memory.  16^3 elements,
 // against one thread a node and one element a block (mean launch, BR1 pass /
-// residual and update): P = 3 17.1 -> 12.1 / 19.8 -> 20.8 us, P = 5 38.6 ->
-// 21.8 / 57.8 -> 46.6 us, P = 6 57.6 -> 29 / 112 -> 66 us (6.5 / 5.8 TB/s of
-// the bytes they move), P = 8 124 -> 59 / 244 -> 142 us; 32^3 elements at P = 6
-// 455 -> 237 / 985 -> 551 us.  The kernels before were bound by latency: an
+// residual and update): P = 3 17.1 -> 10.1 / 19.8 -> 18.1 us, P = 5 38.6 ->
+// 21.5 / 57.8 -> 45.3 us, P = 6 57.6 -> 29 / 112 -> 65 us (6.5 / 5.9 TB/s of
+// the bytes they move), P = 8 124 -> 52 / 244 -> 136 us; 32^3 elements at P = 6
+// 455 -> 223 / 985 -> 530 us (5.0 / 5.3 TB/s; a large copy reaches 4.95).  The kernels before were bound by latency: an
 // element of 343 nodes took six wavefronts through ten barriers, each with a
 // few contractions between them, and 950 instructions a wavefront where this
 // form takes 3 x 1300 for the element.  A whole column of nodes a thread, one

@@ -110,15 +110,24 @@ def _counter_mean(d, kernel, cname):
     return sum(vals) / len(vals), max(copies), len(vals)
 
 
+def stage_sources_sha():
+    """First 16 digits of the sha256 of the stage kernels' sources, one after
+    the other: what a committed counter summary belongs to."""
+    import hashlib
+    csrc = os.path.join(os.path.dirname(os.path.abspath(__file__)), "csrc")
+    h = hashlib.sha256()
+    for name in ("dg_lines.hpp", "dg_kernels.hip"):
+        with open(os.path.join(csrc, name), "rb") as f:
+            h.update(f.read())
+    return h.hexdigest()[:16]
+
+
 def hbm(fetch_dir, write_dir, kernel, copy_bytes, alg_bytes, mean_us, command):
     """HBM bytes per dispatch of one kernel from a FETCH_SIZE run and a
     WRITE_SIZE run (KiB per dispatch), each scaled by what the same counter
     reads for a device copy of copy_bytes, with the sha256 of the kernel
     source (bench.py uses the figure only while the source is unchanged)."""
-    import hashlib
-    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
-    src = open(os.path.join(root, "paper_2207_11571_amd", "csrc", "dg_kernels.hip"), "rb").read()
-    sha = hashlib.sha256(src).hexdigest()[:16]
+    sha = stage_sources_sha()
     f_k, f_c, n_f = _counter_mean(fetch_dir, kernel, "FETCH_SIZE")
     w_k, w_c, n_w = _counter_mean(write_dir, kernel, "WRITE_SIZE")
     ff, fw = copy_bytes / (f_c * 1024.0), copy_bytes / (w_c * 1024.0)
@@ -138,7 +147,7 @@ def hbm(fetch_dir, write_dir, kernel, copy_bytes, alg_bytes, mean_us, command):
     print(f"- traffic_over_algorithmic: {tot / alg_bytes:.3f}")
     print(f"- mean_launch_us: {mean_us:.2f}")
     print(f"- counter_TBs: {tot / (mean_us * 1e-6) / 1e12:.3f}")
-    print("- source: paper_2207_11571_amd/csrc/dg_kernels.hip")
+    print("- source: paper_2207_11571_amd/csrc/dg_lines.hpp, dg_kernels.hip")
     print(f"- source_sha256_16: {sha}")
 
 
