@@ -161,7 +161,8 @@ int dg_stable_dt(const dg_mesh* m, const double* q, double cfl, double* dt_host,
                  void* ws, size_t ws_bytes, void* stream);
 
 /* Infinity-norm error of Eq. (9) for rho u, rho v, rho w between q and q_ref
- * (same mesh): out_dev (device, double[3]). */
+ * (same mesh): out_dev (device, double[3]).  NaN for a variable that is NaN
+ * at some node of either state. */
 int dg_error_inf(const dg_mesh* m, const double* q, const double* q_ref, double* out_dev,
                  void* ws, size_t ws_bytes, void* stream);
 

@@ -355,6 +355,10 @@ __global__ void __launch_bounds__(256) k_diag_final(int rows, double mean_factor
     if ((t & 31) == 0) out[o] = o == 0 ? r * mean_factor : (o < 3 ? r : r * vol_factor);
 }
 
+// Maximum that keeps a NaN of either operand (fmax drops it: a state that has
+// blown up would show the largest error of its finite nodes)
+__device__ __forceinline__ double max_nan(double a, double b) { return a > b || a != a ? a : b; }
+
 // Eq. (9): max |q_v - qref_v| of the three momenta, per block (rows of four)
 __global__ void __launch_bounds__(256) k_err_partial(size_t vs, const double* __restrict__ q,
                                                     const double* __restrict__ qr, double* __restrict__ part) {
@@ -365,14 +369,14 @@ __global__ void __launch_bounds__(256) k_err_partial(size_t vs, const double* __
     for (size_t n = (size_t)blockIdx.x * 256 + t; n < vs; n += step)
         for (int c = 0; c < 3; ++c) {
             const size_t idx = (1 + c) * vs + n;
-            m[c] = fmax(m[c], fabs(q[idx] - qr[idx]));
+            m[c] = max_nan(m[c], fabs(q[idx] - qr[idx]));
         }
     for (int c = 0; c < 3; ++c)
-        for (int w = 32; w > 0; w >>= 1) m[c] = fmax(m[c], __shfl_xor(m[c], w));
+        for (int w = 32; w > 0; w >>= 1) m[c] = max_nan(m[c], __shfl_xor(m[c], w));
     if ((t & 63) == 0)
         for (int c = 0; c < 3; ++c) red[t >> 6][c] = m[c];
     __syncthreads();
-    if (t < 3) part[(size_t)blockIdx.x * 4 + t] = fmax(fmax(red[0][t], red[1][t]), fmax(red[2][t], red[3][t]));
+    if (t < 3) part[(size_t)blockIdx.x * 4 + t] = max_nan(max_nan(red[0][t], red[1][t]), max_nan(red[2][t], red[3][t]));
 }
 
 __global__ void __launch_bounds__(256) k_err_final(int rows, const double* __restrict__ part, double* __restrict__ out) {
@@ -380,11 +384,11 @@ __global__ void __launch_bounds__(256) k_err_final(int rows, const double* __res
     const int t = threadIdx.x;
     double m = 0.0;
     if ((t & 3) < 3)
-        for (int x = t; x < rows * 4; x += 256) m = fmax(m, part[x]);
-    for (int w = 32; w > 3; w >>= 1) m = fmax(m, __shfl_xor(m, w));
+        for (int x = t; x < rows * 4; x += 256) m = max_nan(m, part[x]);
+    for (int w = 32; w > 3; w >>= 1) m = max_nan(m, __shfl_xor(m, w));
     if ((t & 63) < 4) red[t >> 6][t & 3] = m;
     __syncthreads();
-    if (t < 3) out[t] = fmax(fmax(red[0][t], red[1][t]), fmax(red[2][t], red[3][t]));
+    if (t < 3) out[t] = max_nan(max_nan(red[0][t], red[1][t]), max_nan(red[2][t], red[3][t]));
 }
 
 // Filter G: tensor-product 1D projection, one element per block, five

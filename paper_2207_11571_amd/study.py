@@ -238,7 +238,7 @@ def evolve(ref, win, mesh, q0, window, model=None, mode="stage", cfl=0.4):
 
 def _gain(base, run):
     e0, e1 = np.array(base["e_max_momentum"]), np.array(run["e_max_momentum"])
-    worse = np.nonzero(e1[1:] > e0[1:])[0]
+    worse = np.nonzero(~(e1[1:] <= e0[1:]))[0]   # NaN: a run that has blown up
     return {"window_ratio": run["mean_e_window"] / base["mean_e_window"],
             "beyond_ratio": (run["mean_e_beyond"] / base["mean_e_beyond"]) if base["mean_e_beyond"] else None,
             "better_than_uncorrected_until": base["times"][1 + worse[0]] if len(worse) else base["times"][-1]}
@@ -412,7 +412,7 @@ def run_online(N=8, Re=200.0, P_lo=3, t0=4.0, t_end=7.0, window=0.15, snapshots=
             B.dg_error_inf(m_lo, q[nm], g, err)
             hist[nm].append(float(err.max().item()))
         e_on = hist["online"][-1]
-        if e_on > tol and len(events) < max_retrains and ref.t + retrain_window < t_end:
+        if not e_on <= tol and len(events) < max_retrains and ref.t + retrain_window < t_end:
             s0 = ref.seconds
             w = ref.window(retrain_snapshots, retrain_snapshots, [net["target"]], (), log)
             seconds["reference"] += ref.seconds - s0
