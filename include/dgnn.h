@@ -150,13 +150,17 @@ int dg_profile_steps(const dg_mesh* m, double* q, double* k, double dt, int32_t 
 /* Diagnostics, written to out_dev (device, double[8]):
  * [0] kinetic energy (volume mean of rho |v|^2 / 2), [1] max over nodes of
  * |v| + c, [2] min density, [3..7] integrals of the five conserved variables.
+ * What a node makes NaN (a NaN of the state; for [1] also a negative
+ * pressure) is NaN here.
  * The reduction order is fixed: results are bitwise reproducible. */
 int dg_diagnostics(const dg_mesh* m, const double* q, double* out_dev,
                    void* ws, size_t ws_bytes, void* stream);
 
 /* Time step of Eq. (7) with the (P+1)^2 order scaling, from the state q:
  * min(CFL h/((P+1)^2 max(|v|+c)), CFL h^2/((P+1)^4 max(nu, gamma nu/Pr))),
- * nu = mu/min(rho).  Synchronises `stream`; *dt_host receives the value. */
+ * nu = mu/min(rho).  Synchronises `stream`; *dt_host receives the value.
+ * DG_ENONFINITE where a diagnostic of the state (dg_diagnostics) is not finite
+ * or its density not positive. */
 int dg_stable_dt(const dg_mesh* m, const double* q, double cfl, double* dt_host,
                  void* ws, size_t ws_bytes, void* stream);
 

@@ -314,7 +314,7 @@ double stable_dt_from_diag(const Mesh& m, const double* diag_host, double cfl) {
     const double nu = m.ph.mu / diag_host[2];
     const double diff = std::fmax(nu, m.prm.gamma * nu / m.prm.Pr);
     const double dt_v = cfl * m.ph.h * m.ph.h / (n * n * n * n * diff);
-    return std::fmin(dt_a, dt_v);
+    return dt_a <= dt_v || std::isnan(dt_a) ? dt_a : dt_v;   // NaN where either is
 }
 
 int make_mesh(const dg_params* prm, Mesh& M) {
@@ -546,7 +546,9 @@ int dg_stable_dt(const dg_mesh* m, const double* q, double cfl, double* dt_host,
     double h[8];
     DG_HIP(hipMemcpyAsync(h, out, sizeof(h), hipMemcpyDeviceToHost, st));
     DG_HIP(hipStreamSynchronize(st));
-    if (!std::isfinite(h[1]) || !(h[2] > 0)) return set_error(DG_ENONFINITE, "state is not finite/positive");
+    bool ok = h[2] > 0;
+    for (double x : h) ok = ok && std::isfinite(x);
+    if (!ok) return set_error(DG_ENONFINITE, "state is not finite/positive");
     *dt_host = stable_dt_from_diag(m->m, h, cfl);
     return DG_OK;
 }

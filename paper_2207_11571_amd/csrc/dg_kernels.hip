@@ -266,12 +266,17 @@ __global__ void __launch_bounds__(768) k_tgv(Phys ph, int N, double* __restrict_
     q[4 * vs + n] = p / ph.gm1 + 0.5 * (u * u + v * v);
 }
 
+// Maximum and minimum that keep a NaN of either operand (fmax and fmin drop it:
+// a state that has blown up would show the values of its finite nodes)
+__device__ __forceinline__ double max_nan(double a, double b) { return a > b || a != a ? a : b; }
+__device__ __forceinline__ double min_nan(double a, double b) { return a < b || a != a ? a : b; }
+
 // Reduction of eight values over 256 threads, in an order that depends on
 // nothing but the thread numbers: value 1 by maximum, 2 by minimum, the others
 // by sum.  In LDS red[c][x]; thread 32 c returns value c.
 constexpr int kReduceRow = 257;   // row stride of red: the writers of one x use different banks
 __device__ __forceinline__ double diag_join(int c, double a, double b) {
-    return c == 1 ? fmax(a, b) : (c == 2 ? fmin(a, b) : a + b);
+    return c == 1 ? max_nan(a, b) : (c == 2 ? min_nan(a, b) : a + b);
 }
 template <int COUNT>
 __device__ __forceinline__ double reduce_rows(const double (&red)[8][kReduceRow], int t) {
@@ -319,8 +324,8 @@ __global__ void __launch_bounds__(256) k_diag_partial(Phys ph, int E, const doub
         const double m2 = qq[1] * qq[1] + qq[2] * qq[2] + qq[3] * qq[3];
         val[0] += wq * 0.5 * m2 * ir;
         const double p = ph.gm1 * (qq[4] - 0.5 * m2 * ir);
-        val[1] = fmax(val[1], sqrt(m2) * ir + sqrt(ph.gamma * p * ir));
-        val[2] = fmin(val[2], qq[0]);
+        val[1] = max_nan(val[1], sqrt(m2) * ir + sqrt(ph.gamma * p * ir));
+        val[2] = min_nan(val[2], qq[0]);
         for (int v = 0; v < 5; ++v) val[3 + v] += wq * qq[v];
     }
     for (int c = 0; c < 8; ++c) red[c][t] = val[c];
@@ -354,10 +359,6 @@ __global__ void __launch_bounds__(256) k_diag_final(int rows, double mean_factor
     const int o = t >> 5;
     if ((t & 31) == 0) out[o] = o == 0 ? r * mean_factor : (o < 3 ? r : r * vol_factor);
 }
-
-// Maximum that keeps a NaN of either operand (fmax drops it: a state that has
-// blown up would show the largest error of its finite nodes)
-__device__ __forceinline__ double max_nan(double a, double b) { return a > b || a != a ? a : b; }
 
 // Eq. (9): max |q_v - qref_v| of the three momenta, per block (rows of four)
 __global__ void __launch_bounds__(256) k_err_partial(size_t vs, const double* __restrict__ q,

@@ -44,3 +44,50 @@ def test_error_norm_keeps_nan(B, N, P, where):
     ref = (q - r).abs().view(5, -1)[1:4].amax(dim=1)
     assert torch.isnan(ref).any()
     assert np.array_equal(err.cpu().numpy(), ref.cpu().numpy(), equal_nan=True)
+
+
+@pytest.mark.parametrize("N,P", [(1, 1), (3, 2), (9, 6)])
+@pytest.mark.parametrize("what", ["rho", "momentum", "energy", "all", "pressure", "density"])
+def test_diagnostics_of_a_state_that_blew_up(B, N, P, what):
+    """One node with a NaN, a negative pressure or an infinite density, or NaN
+    everywhere: the time step is refused, and the diagnostics that the node
+    enters are not finite.  What it does not enter stays as it was."""
+    say("diagnostics of a bad state", N, P, what)
+    m = B.Mesh(N, P, 100.0)
+    q = _state(N, P, 3)
+    good = B.dg_diagnostics(m, q).cpu().numpy().copy()
+    assert B.dg_stable_dt(m, q) > 0
+    flat = q.view(5, -1)
+    n = flat.shape[1] - 1
+    if what == "all":
+        q.fill_(float("nan"))
+    elif what == "pressure":
+        flat[4, n] = 0.1 * float((flat[1:4, n] ** 2).sum() / flat[0, n])
+    elif what == "density":
+        flat[0, n] = float("inf")
+    else:
+        flat[{"rho": 0, "momentum": 3, "energy": 4}[what], n] = float("nan")
+    d = B.dg_diagnostics(m, q).cpu().numpy()
+    bad = {"rho": {0, 1, 2, 3}, "momentum": {0, 1, 6}, "energy": {1, 7}, "all": set(range(8)), "pressure": {1},
+           "density": {3}}[what]
+    assert {c for c in range(8) if not np.isfinite(d[c])} == bad
+    if what in ("momentum", "energy"):
+        assert d[2] == good[2]
+    with pytest.raises(B.DGError) as ei:
+        B.dg_stable_dt(m, q)
+    assert ei.value.code == B.DG_ENONFINITE
+
+
+@pytest.mark.parametrize("Mach,state", [(0.5, 2), (2.0, 3)])
+def test_served_solve_with_negative_pressure_is_refused(B, Mach, state):
+    """Above Mach 1.4 the Taylor-Green pressure is negative at some nodes: no
+    time step exists, and the solve fails before its first step."""
+    say("served solve", Mach)
+    srv = B.Server(64 << 20, max_slots=2)
+    rid = srv.submit(Re=200.0, P=3, N=4, t_end=0.02, Mach=Mach)
+    srv.drain()
+    _, st = srv.poll(rid)
+    srv.close()
+    assert st.state == state
+    assert st.error == (B.DG_OK if state == B.SOLVE_DONE else B.DG_ENONFINITE)
+    assert (st.steps > 0) == (state == B.SOLVE_DONE)
