@@ -1,5 +1,7 @@
 // C ABI of the forcing network (Sec. 2.1, 2.2): model set-up, inference into a
 // DG residual, and one Adam training step on the MSE loss.
+#include <algorithm>
+#include <cfloat>
 #include <cmath>
 #include <cstring>
 
@@ -43,6 +45,10 @@ static int layout_dims(const int32_t* dims, int32_t n_layers, int* pd, int64_t* 
     return DG_OK;
 }
 
+// 1 / sigma, finite also for the smallest accepted sigma: a value equal to the
+// mean is 0 in units of any sigma, where 0 times infinity would be NaN
+static double inverse_scale(double sigma) { return std::min(1.0 / sigma, DBL_MAX); }
+
 NetArgs net_args(const nn_model* m) {
     NetArgs na;
     std::memset(&na, 0, sizeof(na));
@@ -66,10 +72,10 @@ NetArgs net_args(const nn_model* m) {
         na.in_var[v] = m->in_var[v];
         na.out_var[v] = m->out_var[v];
         na.in_mu[v] = m->norm[m->in_var[v]];
-        na.in_isig[v] = 1.0 / m->norm[5 + m->in_var[v]];
+        na.in_isig[v] = inverse_scale(m->norm[5 + m->in_var[v]]);
         const int o = m->out_var[v];
         na.out_mu[v] = m->norm[10 + o];
-        na.out_isig[v] = 1.0 / m->norm[15 + o];
+        na.out_isig[v] = inverse_scale(m->norm[15 + o]);
         na.out_scale[v] = m->mask[o] * m->norm[15 + o];
         na.out_shift[v] = m->mask[o] * m->norm[10 + o];
     }

@@ -91,3 +91,36 @@ def test_served_solve_with_negative_pressure_is_refused(B, Mach, state):
     assert st.state == state
     assert st.error == (B.DG_OK if state == B.SOLVE_DONE else B.DG_ENONFINITE)
     assert (st.steps > 0) == (state == B.SOLVE_DONE)
+
+
+# 1 / sigma is infinite below 5.6e-309
+@pytest.mark.parametrize("hidden", [(256, 256), (40,)])
+def test_constant_variable_with_the_smallest_scales(B, hidden):
+    """A variable that equals its mean everywhere is 0 in units of any
+    positive sigma: forcing, loss and gradient are the same bits with the
+    smallest as with 1."""
+    say("smallest normalisation scales", hidden)
+    N, n_p, batch = 2, 64, 20
+    dims = [5 * n_p, *hidden, 5 * n_p]
+    params = B.pack_params(synthetic.mlp_init(dims, seed=3))
+    m = B.Mesh(N, 3, 100.0)
+    q = _state(N, 3, 5)
+    q.view(5, -1)[0] = 1.0
+    rng = np.random.default_rng(0)
+    x = rng.standard_normal((batch, 5 * n_p)).astype(np.float32)
+    y = (1e-3 * rng.standard_normal((batch, 5 * n_p))).astype(np.float32)
+    x[:, :n_p], y[:, :n_p] = 1.0, 0.0
+    x, y = torch.from_numpy(x).cuda(), torch.from_numpy(y).cuda()
+    results = []
+    for tiny in (1.0, 1e-310):
+        norm = [1.0, 0.0, 0.0, 0.0, synthetic.TGV_ENERGY_LEVEL, tiny, 1.0, 1.0, 1.0, 1.0] + [0.0] * 5 + [
+            tiny] + [1e-3] * 4
+        model = B.Model(dims, params, norm)
+        s = m.field(0.0)
+        B.nn_forcing(model, m, q, s)
+        loss = torch.zeros(1, dtype=torch.float32, device="cuda")
+        B.nn_train_step(model, x, y, loss=loss)
+        # the forcing of the constant variable itself is in units of its sigma
+        results.append((s.view(5, -1)[1:].clone(), loss, model.grad.clone()))
+    for a, b in zip(*results):
+        assert torch.isfinite(a).all() and torch.equal(a, b)
