@@ -526,9 +526,9 @@ static hipError_t copy_out(Worker& W, char* dst, const char* src, size_t bytes) 
 }
 
 static void finish(solve_server* S, Worker& W, Solve* s) {
-    if (s->req.q_out_host)
-        (void)copy_out(W, (char*)s->req.q_out_host, (const char*)s->q,
-                       (size_t)5 * s->mesh.E * s->mesh.n_p * sizeof(double));
+    if (s->req.q_out_host && copy_out(W, (char*)s->req.q_out_host, (const char*)s->q,
+                                      (size_t)5 * s->mesh.E * s->mesh.n_p * sizeof(double)) != hipSuccess)
+        return fail(S, s, set_error(DG_EHIP, "copy of the final state failed"));
     if (s->req.ke_host) {
         const size_t pairs = std::min((size_t)s->req.ke_capacity, s->ke.size() / 2);
         std::memcpy(s->req.ke_host, s->ke.data(), pairs * 2 * sizeof(double));

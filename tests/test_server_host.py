@@ -1,0 +1,35 @@
+"""The solve server's handling of failures and its bookkeeping, without a GPU:
+csrc/server.cpp built with the host compiler against a HIP runtime that does,
+or fails, everything at once (host/server_host.cpp)."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+CSRC = os.path.join(os.path.dirname(HERE), "paper_2207_11571_amd", "csrc")
+ROCM_INCLUDE = "/opt/rocm/include"
+
+
+@pytest.fixture(scope="module")
+def server_host(tmp_path_factory):
+    if not shutil.which("g++") or not os.path.isdir(os.path.join(ROCM_INCLUDE, "hip")):
+        pytest.skip("no host compiler or no HIP headers")
+    exe = str(tmp_path_factory.mktemp("host") / "server_host")
+    r = subprocess.run(["g++", "-std=c++17", "-O1", "-pthread", "-w", "-D__HIP_PLATFORM_AMD__", "-I", ROCM_INCLUDE,
+                        "-I", CSRC, os.path.join(HERE, "host", "server_host.cpp"), os.path.join(CSRC, "server.cpp"),
+                        "-o", exe], capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr
+    return exe
+
+
+def _run(exe, scenario):
+    r = subprocess.run([exe, scenario], capture_output=True, text=True, timeout=100)
+    assert r.returncode == 0, r.stdout + r.stderr
+
+
+@pytest.mark.parametrize("result", ["small", "large"])
+def test_copy_that_fails_fails_the_solve(server_host, result):
+    """A finished state that cannot be copied out whole is no result."""
+    _run(server_host, f"copy_error_{result}")
