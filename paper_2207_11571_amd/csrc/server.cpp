@@ -120,6 +120,8 @@ struct Solve {
     SolveDesc* ddesc = nullptr;
     double* hist = nullptr;
     double* health = nullptr;        // diagnostics of the state at the end of a round
+    int slot = -1;                   // of the server's slots, while running
+    double* records = nullptr;       // pinned: the slot's records read back at the end of a round
     double* ckpt = nullptr;          // corrected solves: state at the start of the round
     bool nn_active = false;          // the correction is applied
     bool fell_back = false;          // continued uncorrected after a failed check
@@ -181,13 +183,11 @@ struct Worker {
     int PP = 0;
     std::thread th;
     std::vector<Solve*> inbox;   // admitted, not yet set up (under the server's lock)
-    hipStream_t st = nullptr;
-    double* records = nullptr;   // pinned: records read back at the end of a round
-    size_t records_for = 0;      // solves it has room for
+    hipStream_t st = nullptr;    // one of the server's, with the first request
     char* stage = nullptr;       // pinned: kStageSlots chunks of states on their way out
 };
 
-// per solve in Worker::records: a round's kinetic-energy records, then the
+// per slot in solve_server::records: a round's kinetic-energy records, then the
 // health record
 constexpr size_t kRecords = (kHist + 1) * kDiagDoubles;
 
@@ -202,10 +202,17 @@ struct solve_server {
     std::condition_variable cv;
     std::map<uint64_t, std::unique_ptr<Solve>> solves;
     std::deque<Solve*> queue;
-    int running = 0;             // admitted, not done
+    std::vector<int> free_slots; // of max_slots, those no admitted solve holds
     uint64_t next_id = 1;
     bool stop = false;
     Worker workers[dgnn::kMaxPP + 1];
+    // What the solves need besides the arena is made with the server, so that
+    // its creation fails and not the solves later: a stream for each order,
+    // given out in turn as orders come into use (consecutive streams go to
+    // different hardware queues), and the slots' records.
+    hipStream_t streams[DG_MAX_ORDER] = {};
+    int streams_used = 0;
+    double* records = nullptr;   // pinned
     Arena arena;
     double busy = 0.0;           // time in which some order had a round running
     int in_round = 0;
@@ -219,7 +226,7 @@ namespace dgnn {
 // slots are free; one that finds no room in the arena lets later ones pass
 // (lock held)
 static void admit_waiting(solve_server* S) {
-    for (auto it = S->queue.begin(); it != S->queue.end() && S->running < S->max_slots;) {
+    for (auto it = S->queue.begin(); it != S->queue.end() && !S->free_slots.empty();) {
         Solve* s = *it;
         size_t off;
         if (!S->arena.alloc(s->bytes, off)) {
@@ -229,7 +236,9 @@ static void admit_waiting(solve_server* S) {
         s->off = off;
         s->state = SOLVE_RUNNING;
         s->t_admit = now_s();
-        ++S->running;
+        s->slot = S->free_slots.back();
+        S->free_slots.pop_back();
+        s->records = S->records + s->slot * kRecords;
         S->workers[s->mesh.PP].inbox.push_back(s);
         it = S->queue.erase(it);
     }
@@ -243,7 +252,7 @@ static void leave(solve_server* S, Solve* s, int state, int code) {
         s->error = code;
         s->t_done = now_s();
         S->arena.release(s->off, s->bytes);
-        --S->running;
+        S->free_slots.push_back(s->slot);
         admit_waiting(S);
     }
     S->cv.notify_all();
@@ -251,26 +260,12 @@ static void leave(solve_server* S, Solve* s, int state, int code) {
 
 static void fail(solve_server* S, Solve* s, int code) { leave(S, s, SOLVE_FAILED, code); }
 
-static int reserve_records(Worker& W, size_t solves) {
-    if (solves <= W.records_for) return DG_OK;
-    if (W.records) (void)hipHostFree(W.records);
-    W.records = nullptr;
-    W.records_for = 0;
-    const size_t n = std::max<size_t>(16, 2 * solves);
-    if (hipHostMalloc((void**)&W.records, n * kRecords * sizeof(double), hipHostMallocDefault) != hipSuccess) {
-        W.records = nullptr;
-        return set_error(DG_EHIP, "pinned buffer allocation failed");
-    }
-    W.records_for = n;
-    return DG_OK;
-}
-
 static int write_descs(Solve* s, hipStream_t st);
 static void stage_desc(const Solve* s, int par, SolveDesc& d);
 
 // admitted solves, first half: pointers, TGV state, its traces and
 // diagnostics (which are also the record at t = 0), on their way back
-static int admit_begin(solve_server* S, Worker& W, Solve* s, double* rec) {
+static int admit_begin(solve_server* S, Worker& W, Solve* s) {
     const dg_params prm = request_params(s->req);
     int rc = make_mesh(&prm, s->mesh);
     if (rc) return rc;
@@ -286,7 +281,7 @@ static int admit_begin(solve_server* S, Worker& W, Solve* s, double* rec) {
     s->nn_active = s->req.use_nn != 0;
     if ((rc = init_tgv_impl(s->mesh, s->q, W.st))) return rc;
     if ((rc = diag_impl(s->mesh, s->q, s->hist, s->ws, W.st))) return rc;
-    if (hipMemcpyAsync(rec, s->hist, kDiagDoubles * sizeof(double), hipMemcpyDeviceToHost, W.st) != hipSuccess)
+    if (hipMemcpyAsync(s->records, s->hist, kDiagDoubles * sizeof(double), hipMemcpyDeviceToHost, W.st) != hipSuccess)
         return set_error(DG_EHIP, "admission readback failed");
     SolveDesc d;
     stage_desc(s, 1, d);
@@ -295,7 +290,8 @@ static int admit_begin(solve_server* S, Worker& W, Solve* s, double* rec) {
 }
 
 // second half, with the diagnostics: time step and stage descriptors
-static int admit_end(solve_server* S, Worker& W, Solve* s, const double* rec) {
+static int admit_end(solve_server* S, Worker& W, Solve* s) {
+    const double* rec = s->records;
     const double dt0 = stable_dt_from_diag(s->mesh, rec, 0.4);
     if (!(dt0 > 0) || !std::isfinite(dt0)) return set_error(DG_ENONFINITE, "bad initial state");
     s->ke0 = rec[0];
@@ -316,13 +312,11 @@ static int admit_end(solve_server* S, Worker& W, Solve* s, const double* rec) {
 static void admit(solve_server* S, Worker& W, std::vector<Solve*>& admitted, std::vector<Solve*>& run) {
     if (admitted.empty()) return;
     std::vector<int> rc(admitted.size(), DG_OK);
-    const int all = reserve_records(W, admitted.size());
-    for (size_t i = 0; i < admitted.size(); ++i)
-        rc[i] = all ? all : admit_begin(S, W, admitted[i], W.records + i * kRecords);
+    for (size_t i = 0; i < admitted.size(); ++i) rc[i] = admit_begin(S, W, admitted[i]);
     const bool back = hipStreamSynchronize(W.st) == hipSuccess;
     for (size_t i = 0; i < admitted.size(); ++i) {
         if (!rc[i] && !back) rc[i] = set_error(DG_EHIP, "admission synchronise failed");
-        if (!rc[i]) rc[i] = admit_end(S, W, admitted[i], W.records + i * kRecords);
+        if (!rc[i]) rc[i] = admit_end(S, W, admitted[i]);
         if (rc[i]) fail(S, admitted[i], rc[i]);
         else run.push_back(admitted[i]);
     }
@@ -462,7 +456,8 @@ static bool record_healthy(const Solve* s, const double* rec) {
 // the end-of-round health record) that the round read back.  Returns true when
 // a corrected solve must fall back: its pending records are then dropped,
 // except those at or before the state copy it returns to.
-static bool collect(solve_server* S, Solve* s, const double* records) {
+static bool collect(solve_server* S, Solve* s) {
+    const double* const records = s->records;
     const size_t n = s->pending_t.size();
     const bool check = s->nn_active;
     std::lock_guard<std::mutex> lk(S->mu);
@@ -538,8 +533,7 @@ static void finish(solve_server* S, Worker& W, Solve* s) {
 
 // enqueues one round of the running solves, up to the read-back of its records
 static int enqueue_round(solve_server* S, Worker& W, const std::vector<Solve*>& run) {
-    int rc = reserve_records(W, run.size());
-    if (rc) return rc;
+    int rc = DG_OK;
     const std::vector<int64_t> plan = round_plan(run);
     const int64_t steps = *std::max_element(plan.begin(), plan.end());
     // corrected solves: copy of the (already checked) state the round starts from
@@ -560,7 +554,7 @@ static int enqueue_round(solve_server* S, Worker& W, const std::vector<Solve*>& 
     }
     for (size_t i = 0; i < run.size(); ++i) {
         Solve* s = run[i];
-        double* rec = W.records + i * kRecords;
+        double* const rec = s->records;
         if (s->nn_active && (rc = diag_impl(s->mesh, s->q, s->health, s->ws, W.st))) return rc;
         if ((!s->pending_t.empty() &&
              hipMemcpyAsync(rec, s->hist, s->pending_t.size() * kDiagDoubles * sizeof(double), hipMemcpyDeviceToHost,
@@ -583,11 +577,7 @@ static void mark_round(solve_server* S, bool begin) {
 
 static void worker_loop(solve_server* S, Worker& W) {
     int broken = DG_OK;
-    if (hipSetDevice(S->device) != hipSuccess ||
-        hipStreamCreateWithFlags(&W.st, hipStreamNonBlocking) != hipSuccess) {
-        W.st = nullptr;
-        broken = set_error(DG_EHIP, "stream creation failed");
-    }
+    if (hipSetDevice(S->device) != hipSuccess) broken = set_error(DG_EHIP, "hipSetDevice failed");
     std::vector<Solve*> admitted, run, keep, done;
     while (true) {
         bool stop;
@@ -620,7 +610,7 @@ static void worker_loop(solve_server* S, Worker& W) {
             Solve* s = run[i];
             int err = rc;
             if (err == DG_OK) {
-                if (collect(S, s, W.records + i * kRecords)) err = fall_back(S, W, s);
+                if (collect(S, s)) err = fall_back(S, W, s);
                 else {
                     std::lock_guard<std::mutex> lk(S->mu);
                     err = s->error;
@@ -632,15 +622,19 @@ static void worker_loop(solve_server* S, Worker& W) {
         }
         run.swap(keep);
     }
-    if (W.st) {
-        (void)hipStreamSynchronize(W.st);
-        (void)hipStreamDestroy(W.st);
-    }
-    if (W.records) (void)hipHostFree(W.records);
+    (void)hipStreamSynchronize(W.st);
     if (W.stage) (void)hipHostFree(W.stage);
 }
 
 }  // namespace dgnn
+
+// frees a server whose threads have ended, or were not started
+static void destroy(solve_server* S) {
+    for (hipStream_t st : S->streams)
+        if (st) (void)hipStreamDestroy(st);
+    if (S->records) (void)hipHostFree(S->records);
+    delete S;
+}
 
 extern "C" {
 
@@ -667,9 +661,21 @@ int solve_server_create(void* arena, size_t arena_bytes, int32_t max_slots, solv
     S->bytes = arena_bytes & ~(size_t)255;
     S->max_slots = max_slots;
     S->arena.reset(S->bytes);
+    for (int i = max_slots; i-- > 0;) S->free_slots.push_back(i);
     if (hipGetDevice(&S->device) != hipSuccess) {
-        delete S;
+        destroy(S);
         return set_error(DG_EHIP, "hipGetDevice failed");
+    }
+    for (hipStream_t& st : S->streams)
+        if (hipStreamCreateWithFlags(&st, hipStreamNonBlocking) != hipSuccess) {
+            st = nullptr;
+            destroy(S);
+            return set_error(DG_EHIP, "stream creation failed");
+        }
+    if (hipHostMalloc((void**)&S->records, max_slots * kRecords * sizeof(double), hipHostMallocDefault) != hipSuccess) {
+        S->records = nullptr;
+        destroy(S);
+        return set_error(DG_EHIP, "pinned buffer allocation failed");
     }
     for (int pp = 0; pp <= kMaxPP; ++pp) S->workers[pp].PP = pp;
     *out = S;
@@ -702,6 +708,7 @@ int solve_submit(solve_server* S, const solve_request* r, uint64_t* id) {
         if (S->stop) return set_error(DG_EINVAL, "server is shutting down");
         Worker& W = S->workers[m.PP];
         if (!W.th.joinable()) {
+            if (!W.st) W.st = S->streams[S->streams_used++];
             try {
                 W.th = std::thread(worker_loop, S, std::ref(W));
             } catch (const std::exception&) {
@@ -778,7 +785,7 @@ void solve_server_free(solve_server* S) {
     S->cv.notify_all();
     for (Worker& W : S->workers)
         if (W.th.joinable()) W.th.join();
-    delete S;
+    destroy(S);
 }
 
 }  // extern "C"

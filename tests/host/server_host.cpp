@@ -269,9 +269,44 @@ void copy_error(int N, int nth) {
     b.expect_done(S, "the next request");
 }
 
+// What the solves need is there once the server is made, or it is not made:
+// every stream and pinned buffer of its creation fails in turn, then all of
+// them after it.
+void create_errors() {
+    std::atomic<int> calls{0};
+    int fail_at = 0;
+    const auto nth = [&] { return calls++ == fail_at; };
+    g_fail_stream = g_fail_pinned = nth;
+    for (;; ++fail_at) {
+        calls = 0;
+        char* arena = (char*)std::aligned_alloc(256, 4096);
+        solve_server* s = (solve_server*)arena;
+        const int rc = solve_server_create(arena, 4096, 40, &s);
+        const bool failed = calls > fail_at;
+        if (failed && (rc != DG_EHIP || s)) complain("creation %d failed: code %d", fail_at, rc);
+        if (!failed && rc != DG_OK) complain("created without a failure: code %d", rc);
+        if (s) solve_server_free(s);
+        std::free(arena);
+        if (!g_streams.empty() || !g_pinned.empty()) complain("creation %d failed: something left", fail_at);
+        if (!failed) break;
+    }
+    if (fail_at == 0) complain("nothing is made with the server");
+    g_fail_stream = g_fail_pinned = nullptr;
+    Server S(40);
+    g_fail_stream = g_fail_pinned = [] { return true; };
+    std::vector<Request> r;
+    for (int i = 0; i < 40; ++i) r.emplace_back(1 + i % 2, 2 + i % 3, 3 + i);
+    r.emplace_back(3, 16, 3);   // a result of several pieces
+    for (int P = 4; P <= DG_MAX_ORDER; ++P) r.emplace_back(P, 2, 3);
+    for (Request& x : r) x.submit(S);
+    solve_server_drain(S.s);
+    for (Request& x : r) x.expect_done(S, "without further streams and buffers");
+}
+
 int run(const std::string& what) {
     if (what == "copy_error_small") copy_error(kSmallN, 0);
     else if (what == "copy_error_large") copy_error(kLargeN, 2);
+    else if (what == "create_errors") create_errors();
     else complain("no scenario %s", what.c_str());
     return g_bad;
 }

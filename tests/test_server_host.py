@@ -33,3 +33,9 @@ def _run(exe, scenario):
 def test_copy_that_fails_fails_the_solve(server_host, result):
     """A finished state that cannot be copied out whole is no result."""
     _run(server_host, f"copy_error_{result}")
+
+
+def test_missing_streams_and_buffers_fail_the_creation(server_host):
+    """A stream or a pinned buffer that cannot be had is an error of
+    solve_server_create, not of the solves."""
+    _run(server_host, "create_errors")
