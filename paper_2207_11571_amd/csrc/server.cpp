@@ -209,8 +209,10 @@ struct solve_server {
     // What the solves need besides the arena is made with the server, so that
     // its creation fails and not the solves later: a stream for each order,
     // given out in turn as orders come into use (consecutive streams go to
-    // different hardware queues), and the slots' records.
-    hipStream_t streams[DG_MAX_ORDER] = {};
+    // different hardware queues), one after them for finished states, and the
+    // slots' records.  (A stream for each order's states: the copy of 10 MB
+    // took 1 ms longer.)
+    hipStream_t streams[DG_MAX_ORDER + 1] = {};
     int streams_used = 0;
     double* records = nullptr;   // pinned
     Arena arena;
@@ -495,20 +497,27 @@ static int fall_back(solve_server* S, Worker& W, Solve* s) {
     return DG_OK;
 }
 
+static hipError_t copy_and_wait(solve_server* S, char* dst, const char* src, size_t n) {
+    const hipStream_t st = S->streams[DG_MAX_ORDER];
+    const hipError_t e = hipMemcpyAsync(dst, src, n, hipMemcpyDeviceToHost, st);
+    return e != hipSuccess ? e : hipStreamSynchronize(st);
+}
+
 // Device to pageable host memory, a chunk on its way to pinned memory while
 // others go on from there, each in a thread of its own (new pages are what
-// takes long: 15 MB in four threads 0.8 ms, in one 1.4).
-static hipError_t copy_out(Worker& W, char* dst, const char* src, size_t bytes) {
+// takes long: 15 MB in four threads 0.8 ms, in one 1.4).  On a stream of the
+// server: a copy on the null stream waits for what the caller has there.
+static hipError_t copy_out(solve_server* S, Worker& W, char* dst, const char* src, size_t bytes) {
     if (bytes > kStageChunk && !W.stage &&
         hipHostMalloc((void**)&W.stage, kStageSlots * kStageChunk, hipHostMallocDefault) != hipSuccess)
         W.stage = nullptr;
-    if (bytes <= kStageChunk || !W.stage) return hipMemcpy(dst, src, bytes, hipMemcpyDeviceToHost);
+    if (bytes <= kStageChunk || !W.stage) return copy_and_wait(S, dst, src, bytes);
     std::future<void> going[kStageSlots];   // their destructors wait
     for (size_t at = 0, i = 0; at < bytes; at += kStageChunk, ++i) {
         const size_t slot = i % kStageSlots, n = std::min(kStageChunk, bytes - at);
         char* const piece = W.stage + slot * kStageChunk;
         if (going[slot].valid()) going[slot].wait();
-        const hipError_t e = hipMemcpy(piece, src + at, n, hipMemcpyDeviceToHost);
+        const hipError_t e = copy_and_wait(S, piece, src + at, n);
         if (e != hipSuccess) return e;
         const auto move = [=] { std::memcpy(dst + at, piece, n); };
         try {
@@ -521,7 +530,7 @@ static hipError_t copy_out(Worker& W, char* dst, const char* src, size_t bytes) 
 }
 
 static void finish(solve_server* S, Worker& W, Solve* s) {
-    if (s->req.q_out_host && copy_out(W, (char*)s->req.q_out_host, (const char*)s->q,
+    if (s->req.q_out_host && copy_out(S, W, (char*)s->req.q_out_host, (const char*)s->q,
                                       (size_t)5 * s->mesh.E * s->mesh.n_p * sizeof(double)) != hipSuccess)
         return fail(S, s, set_error(DG_EHIP, "copy of the final state failed"));
     if (s->req.ke_host) {

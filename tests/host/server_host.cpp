@@ -303,10 +303,21 @@ void create_errors() {
     for (Request& x : r) x.expect_done(S, "without further streams and buffers");
 }
 
+// no copy on the null stream, where it would wait for the caller's work
+void null_stream() {
+    Server S(4);
+    Request a(1, kSmallN, 3), b(2, kSmallN, 3), c(1, kLargeN, 2);
+    for (Request* r : {&a, &b, &c}) r->submit(S);
+    solve_server_drain(S.s);
+    for (Request* r : {&a, &b, &c}) r->expect_done(S, "request");
+    if (g_null_copies) complain("%d copies on the null stream", g_null_copies.load());
+}
+
 int run(const std::string& what) {
     if (what == "copy_error_small") copy_error(kSmallN, 0);
     else if (what == "copy_error_large") copy_error(kLargeN, 2);
     else if (what == "create_errors") create_errors();
+    else if (what == "null_stream") null_stream();
     else complain("no scenario %s", what.c_str());
     return g_bad;
 }

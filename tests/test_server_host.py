@@ -39,3 +39,7 @@ def test_missing_streams_and_buffers_fail_the_creation(server_host):
     """A stream or a pinned buffer that cannot be had is an error of
     solve_server_create, not of the solves."""
     _run(server_host, "create_errors")
+
+
+def test_copies_leave_the_null_stream_alone(server_host):
+    _run(server_host, "null_stream")
