@@ -17,7 +17,7 @@
 // each result is what the solve computes alone.  After each round the stream
 // is synchronised once: kinetic-energy records are collected, non-finite
 // solves are failed.  Finished solves are copied out, and their arena blocks
-// released, while the next round runs.
+// released, by another thread while the next round is enqueued and runs.
 // (Two corrected P=3, two P=6 and two P=8 solves on 4^3, one of each on 8^3:
 // 7.6 ms with one thread for all orders, whose rounds waited for the slowest
 // order and for the copies, 3.9 so.)
@@ -184,6 +184,9 @@ struct Worker {
     std::thread th;
     std::vector<Solve*> inbox;   // admitted, not yet set up (under the server's lock)
     hipStream_t st = nullptr;    // one of the server's, with the first request
+    std::deque<Solve*> done;     // finished, not yet copied out (under the server's lock)
+    bool delivering = false;     // a thread is at it (likewise)
+    std::future<void> delivery;  // that thread
     char* stage = nullptr;       // pinned: kStageSlots chunks of states on their way out
 };
 
@@ -540,6 +543,39 @@ static void finish(solve_server* S, Worker& W, Solve* s) {
     leave(S, s, SOLVE_DONE, s->error);
 }
 
+// copies out what an order has finished until nothing is left
+static void deliver_all(solve_server* S, Worker& W) {
+    (void)hipSetDevice(S->device);
+    while (true) {
+        Solve* s;
+        {
+            std::lock_guard<std::mutex> lk(S->mu);
+            W.delivering = !W.done.empty();
+            if (!W.delivering) return;
+            s = W.done.front();
+            W.done.pop_front();
+        }
+        finish(S, W, s);
+    }
+}
+
+// Hands a finished solve to the thread that copies results out, started where
+// none is at it: beside the next round's enqueueing, which may take as long as
+// the round, and beside the round.
+static void deliver(solve_server* S, Worker& W, Solve* s) {
+    {
+        std::lock_guard<std::mutex> lk(S->mu);
+        W.done.push_back(s);
+        if (W.delivering) return;
+        W.delivering = true;
+    }
+    try {
+        W.delivery = std::async(std::launch::async, deliver_all, S, std::ref(W));
+    } catch (const std::exception&) {
+        deliver_all(S, W);
+    }
+}
+
 // enqueues one round of the running solves, up to the read-back of its records
 static int enqueue_round(solve_server* S, Worker& W, const std::vector<Solve*>& run) {
     int rc = DG_OK;
@@ -587,30 +623,22 @@ static void mark_round(solve_server* S, bool begin) {
 static void worker_loop(solve_server* S, Worker& W) {
     int broken = DG_OK;
     if (hipSetDevice(S->device) != hipSuccess) broken = set_error(DG_EHIP, "hipSetDevice failed");
-    std::vector<Solve*> admitted, run, keep, done;
+    std::vector<Solve*> admitted, run, keep;
     while (true) {
-        bool stop;
         {
             std::unique_lock<std::mutex> lk(S->mu);
-            S->cv.wait(lk, [&] { return S->stop || !W.inbox.empty() || !run.empty() || !done.empty(); });
-            stop = S->stop;
-            if (!stop) admitted.swap(W.inbox);
+            S->cv.wait(lk, [&] { return S->stop || !W.inbox.empty() || !run.empty(); });
+            if (S->stop) break;
+            admitted.swap(W.inbox);
         }
         if (broken) {
             for (Solve* s : admitted) fail(S, s, broken);
             admitted.clear();
         }
-        if (!stop) admit(S, W, admitted, run);
-        int rc = DG_OK;
-        const bool round = !stop && !run.empty();
-        if (round) {
-            mark_round(S, true);
-            rc = enqueue_round(S, W, run);
-        }
-        for (Solve* s : done) finish(S, W, s);   // beside the round on the device
-        done.clear();
-        if (stop) break;
-        if (!round) continue;
+        admit(S, W, admitted, run);
+        if (run.empty()) continue;
+        mark_round(S, true);
+        int rc = enqueue_round(S, W, run);
         const bool synced = hipStreamSynchronize(W.st) == hipSuccess;
         mark_round(S, false);
         if (!synced && rc == DG_OK) rc = set_error(DG_EHIP, "round synchronise failed");
@@ -626,12 +654,13 @@ static void worker_loop(solve_server* S, Worker& W) {
                 }
             }
             if (err) fail(S, s, err);
-            else if (s->steps >= s->n_steps) done.push_back(s);
+            else if (s->steps >= s->n_steps) deliver(S, W, s);
             else keep.push_back(s);
         }
         run.swap(keep);
     }
     (void)hipStreamSynchronize(W.st);
+    if (W.delivery.valid()) W.delivery.wait();
     if (W.stage) (void)hipHostFree(W.stage);
 }
 

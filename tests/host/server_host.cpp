@@ -313,11 +313,43 @@ void null_stream() {
     if (g_null_copies) complain("%d copies on the null stream", g_null_copies.load());
 }
 
+// A solve that ends while another of its order goes on is delivered, and its
+// slot given to the next request, without waiting for the other's next round:
+// the first launch of that round is held until both happened.
+void delivery(int N) {
+    Server S(2);
+    Request a(1, N, 20), b(1, N, 100), next(2, 1, 1);
+    std::atomic<bool> submitted{false}, late{false}, held{false};
+    std::atomic<int> ended_at{-1};
+    g_on_grad = [&](hipStream_t st, const DescList& dl) {
+        within_seconds(5, [&] { return submitted.load(); });
+        if (dl.n != 1 || held || a.status(S).steps < 20) return;
+        int none = -1;
+        if (ended_at.compare_exchange_strong(none, st->syncs)) return;   // in the round that ends it
+        if (st->syncs == ended_at) return;
+        held = true;
+        late = !within_seconds(5, [&] {
+            return a.status(S).state == SOLVE_DONE && next.status(S).state != SOLVE_QUEUED;
+        });
+    };
+    a.submit(S);
+    b.submit(S);
+    next.submit(S);
+    submitted = true;
+    solve_server_drain(S.s);
+    g_on_grad = nullptr;
+    for (Request* r : {&a, &b, &next}) r->expect_done(S, "request");
+    if (!held) complain("no launch after the round in which the first solve ended");
+    if (late) complain("the next round began before the finished solve was delivered");
+}
+
 int run(const std::string& what) {
     if (what == "copy_error_small") copy_error(kSmallN, 0);
     else if (what == "copy_error_large") copy_error(kLargeN, 2);
     else if (what == "create_errors") create_errors();
     else if (what == "null_stream") null_stream();
+    else if (what == "delivery_small") delivery(kSmallN);
+    else if (what == "delivery_large") delivery(kLargeN);
     else complain("no scenario %s", what.c_str());
     return g_bad;
 }

@@ -43,3 +43,10 @@ def test_missing_streams_and_buffers_fail_the_creation(server_host):
 
 def test_copies_leave_the_null_stream_alone(server_host):
     _run(server_host, "null_stream")
+
+
+@pytest.mark.parametrize("result", ["small", "large"])
+def test_finished_solve_does_not_wait_for_the_next_round(server_host, result):
+    """Its result is delivered and its slot free while the next round of its
+    order is still being enqueued."""
+    _run(server_host, f"delivery_{result}")
