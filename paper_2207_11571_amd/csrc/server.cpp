@@ -647,8 +647,11 @@ static void worker_loop(solve_server* S, Worker& W) {
             Solve* s = run[i];
             int err = rc;
             if (err == DG_OK) {
-                if (collect(S, s)) err = fall_back(S, W, s);
-                else {
+                if (collect(S, s)) {
+                    err = fall_back(S, W, s);
+                    // what it enqueued before it failed still writes to the block
+                    if (err) (void)hipStreamSynchronize(W.st);
+                } else {
                     std::lock_guard<std::mutex> lk(S->mu);
                     err = s->error;
                 }

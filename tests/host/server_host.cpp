@@ -5,6 +5,7 @@
 // with the number of complaints.
 #include <atomic>
 #include <chrono>
+#include <cmath>
 #include <cstdarg>
 #include <cstdio>
 #include <cstdlib>
@@ -343,6 +344,37 @@ void delivery(int N) {
     if (late) complain("the next round began before the finished solve was delivered");
 }
 
+// A corrected solve has to fall back, and that fails half-way, with the copy of
+// its state already enqueued: its block goes to another order's solve only
+// when nothing is pending that writes to it.
+void fallback_error() {
+    nn_model model;
+    Request a(1, kSmallN, 40), b(2, kSmallN, 3);
+    a.r.use_nn = 1;
+    a.r.model = &model;
+    Server S(2, solve_footprint(2, kSmallN, 0));   // one at a time
+    std::atomic<hipStream_t> failing{nullptr};
+    std::atomic<int> energies{0}, pending{-1};
+    g_energy = [&](const double*) { return energies++ ? NAN : 1.0; };
+    g_fail_descs = [&] { return energies > 1; };
+    g_on_grad = [&](hipStream_t st, const DescList&) { failing = st; };
+    g_on_init = [&](hipStream_t st, const double*) {
+        if (!failing) return;
+        pending = failing.load()->pending.load();
+        g_energy = nullptr;   // of the next solve: healthy
+        g_fail_descs = nullptr;
+        g_on_grad = nullptr;
+    };
+    a.submit(S);
+    b.submit(S);
+    solve_server_drain(S.s);
+    const solve_status st = a.status(S);
+    if (st.state != SOLVE_FAILED || st.error != DG_EHIP) complain("the solve: state %d, error %d", st.state, st.error);
+    if (pending < 0) complain("the next solve was not set up");
+    if (pending > 0) complain("%d operations pending on a block that was given away", pending.load());
+    b.expect_done(S, "the next solve");
+}
+
 int run(const std::string& what) {
     if (what == "copy_error_small") copy_error(kSmallN, 0);
     else if (what == "copy_error_large") copy_error(kLargeN, 2);
@@ -350,6 +382,7 @@ int run(const std::string& what) {
     else if (what == "null_stream") null_stream();
     else if (what == "delivery_small") delivery(kSmallN);
     else if (what == "delivery_large") delivery(kLargeN);
+    else if (what == "fallback_error") fallback_error();
     else complain("no scenario %s", what.c_str());
     return g_bad;
 }

@@ -50,3 +50,7 @@ def test_finished_solve_does_not_wait_for_the_next_round(server_host, result):
     """Its result is delivered and its slot free while the next round of its
     order is still being enqueued."""
     _run(server_host, f"delivery_{result}")
+
+
+def test_failed_fallback_gives_its_block_away_when_nothing_writes_to_it(server_host):
+    _run(server_host, "fallback_error")
