@@ -271,9 +271,15 @@ static void stage_desc(const Solve* s, int par, SolveDesc& d);
 // admitted solves, first half: pointers, TGV state, its traces and
 // diagnostics (which are also the record at t = 0), on their way back
 static int admit_begin(solve_server* S, Worker& W, Solve* s) {
+    // once more, on this thread's device (solve_submit built it on the caller's)
     const dg_params prm = request_params(s->req);
-    int rc = make_mesh(&prm, s->mesh);
+    Mesh mesh;
+    int rc = make_mesh(&prm, mesh);
     if (rc) return rc;
+    {
+        std::lock_guard<std::mutex> lk(S->mu);
+        s->mesh = mesh;
+    }
     const Foot f = foot(s->mesh, s->req.use_nn != 0);
     char* p = S->base + s->off;
     s->q = (double*)(p + f.q);

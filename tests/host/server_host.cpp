@@ -375,6 +375,23 @@ void fallback_error() {
     b.expect_done(S, "the next solve");
 }
 
+// requests that are polled from another thread from their submission on
+void polling() {
+    Server S(3);
+    std::vector<Request> r;
+    for (int i = 0; i < 12; ++i) r.emplace_back(1 + i % 3, 2, 40);
+    for (Request& x : r) {
+        x.submit(S);
+        for (int n = 0; n < 200; ++n) x.status(S);
+    }
+    while (true) {
+        int done = 0;
+        for (Request& x : r) done += x.status(S).state == SOLVE_DONE;
+        if (done == (int)r.size()) break;
+    }
+    for (Request& x : r) x.expect_done(S, "request");
+}
+
 int run(const std::string& what) {
     if (what == "copy_error_small") copy_error(kSmallN, 0);
     else if (what == "copy_error_large") copy_error(kLargeN, 2);
@@ -383,6 +400,7 @@ int run(const std::string& what) {
     else if (what == "delivery_small") delivery(kSmallN);
     else if (what == "delivery_large") delivery(kLargeN);
     else if (what == "fallback_error") fallback_error();
+    else if (what == "polling") polling();
     else complain("no scenario %s", what.c_str());
     return g_bad;
 }

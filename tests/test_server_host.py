@@ -12,16 +12,19 @@ CSRC = os.path.join(os.path.dirname(HERE), "paper_2207_11571_amd", "csrc")
 ROCM_INCLUDE = "/opt/rocm/include"
 
 
-@pytest.fixture(scope="module")
-def server_host(tmp_path_factory):
+def _build(exe, *flags):
     if not shutil.which("g++") or not os.path.isdir(os.path.join(ROCM_INCLUDE, "hip")):
         pytest.skip("no host compiler or no HIP headers")
-    exe = str(tmp_path_factory.mktemp("host") / "server_host")
     r = subprocess.run(["g++", "-std=c++17", "-O1", "-pthread", "-w", "-D__HIP_PLATFORM_AMD__", "-I", ROCM_INCLUDE,
-                        "-I", CSRC, os.path.join(HERE, "host", "server_host.cpp"), os.path.join(CSRC, "server.cpp"),
-                        "-o", exe], capture_output=True, text=True)
+                        "-I", CSRC, *flags, os.path.join(HERE, "host", "server_host.cpp"),
+                        os.path.join(CSRC, "server.cpp"), "-o", exe], capture_output=True, text=True)
     assert r.returncode == 0, r.stderr
     return exe
+
+
+@pytest.fixture(scope="module")
+def server_host(tmp_path_factory):
+    return _build(str(tmp_path_factory.mktemp("host") / "server_host"))
 
 
 def _run(exe, scenario):
@@ -54,3 +57,14 @@ def test_finished_solve_does_not_wait_for_the_next_round(server_host, result):
 
 def test_failed_fallback_gives_its_block_away_when_nothing_writes_to_it(server_host):
     _run(server_host, "fallback_error")
+
+
+@pytest.mark.parametrize("scenario", ["polling", "null_stream", "delivery_large", "copy_error_large",
+                                      "fallback_error"])
+def test_threads_of_the_server_do_not_race(tmp_path_factory, scenario):
+    """The scenarios, and requests polled from the start, under the thread
+    sanitizer."""
+    exe = os.path.join(tmp_path_factory.getbasetemp(), "server_host_threads")
+    if not os.path.exists(exe):
+        _build(exe, "-g", "-fsanitize=thread")
+    _run(exe, scenario)
