@@ -106,8 +106,10 @@ __device__ __forceinline__ int group_of_block(int E) {
 // What a block's first loads need comes as arguments of its own ahead of the
 // descriptor: the first sixteen words of a kernel's arguments are in scalar
 // registers when its wavefronts start (the build asks for that), where a load
-// of them would be the first of three dependent ones.  A step: 4^3 P=3 24.3 ->
-// 21.5 us, 8^3 P=3 27.9 -> 25.9, 8^3 P=6 57.0 -> 55.0, 16^3 P=3 76.8 -> 73.1.
+// of them would be the first of three dependent ones.  A step of a long call:
+// 4^3 P=3 24.3 -> 21.5 us, 8^3 P=3 27.9 -> 25.9, 8^3 P=6 57.0 -> 55.0, 16^3 P=3
+// 76.8 -> 73.1.  (A call of one step takes the trace launch more, 8 % and
+// above; of small meshes it is bound by the host's enqueueing.)
 __device__ __forceinline__ SolveDesc with_head(const SolveDesc& D, const double* state, const double* qtr_in, double* fv, int N,
                                                int E) {
     SolveDesc S = D;
@@ -573,11 +575,12 @@ static DescList in_groups(const DescList& dl) {
 }
 
 // Whether what a stage goes through (state, register, two sets of traces,
-// viscous fluxes) exceeds the 256 MB of the memory-side cache: then the
+// viscous fluxes) exceeds the 256 MiB of the memory-side cache: then the
 // register is kept out of it, and the stage update takes the groups in
-// reverse.  A step, us, without -> with: 16^3 P=7 (356 MB) 446 -> 424, 16^3
-// P=8 605 -> 565, 20^3 P=5 392 -> 372, 24^3 P=6 1030 -> 974, 32^3 P=6 2389 ->
-// 2266; below, 24^3 P=3 (230 MB) 223 -> 234, 16^3 P=6 (253 MB) 298 -> 304.
+// reverse.  A step of a long call, us, without -> with: 16^3 P=7 (328 MiB) 446
+// -> 424, 16^3 P=8 605 -> 565, 20^3 P=5 (316 MiB) 392 -> 372, 24^3 P=6 1030 ->
+// 974, 32^3 P=6 2389 -> 2266; below, 24^3 P=3 (209 MiB) 223 -> 234, 16^3 P=6
+// (236 MiB) 298 -> 304.
 template <int PP>
 static bool streams(int E) {
     using L = Line<PP>;
@@ -585,7 +588,7 @@ static bool streams(int E) {
 }
 
 // Where the single solves' launches take the groups in ranges: while the data
-// fit the memory-side cache, a step, us: 11^3 P=5 91.5 -> 83.3, 12^3 P=6 143 ->
+// fit the memory-side cache, a step of a long call, us: 11^3 P=5 91.5 -> 83.3, 12^3 P=6 143 ->
 // 136, 14^3 P=7 302 -> 286, two of 8^3 P=3 with the network (whose blocks take
 // sixteen elements in a row) 111 -> 100.  With N a multiple of eight, groups in
 // turn have their y and z neighbours on the same XCD already, and ranges gain

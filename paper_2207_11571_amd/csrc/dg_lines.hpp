@@ -20,13 +20,15 @@
 //
 // What bounds the stage kernels is the traffic to memory.  16^3 elements,
 // against one thread a node and one element a block (mean launch, BR1 pass /
-// residual and update): P = 3 17.1 -> 10.1 / 19.8 -> 18.1 us, P = 5 38.6 ->
-// 21.5 / 57.8 -> 45.3 us, P = 6 57.6 -> 29 / 112 -> 65 us (6.5 / 5.9 TB/s of
-// the bytes they move), P = 8 124 -> 52 / 244 -> 136 us; 32^3 elements at P = 6
-// 455 -> 223 / 985 -> 530 us (5.0 / 5.3 TB/s; a large copy reaches 4.95).  The kernels before were bound by latency: an
-// element of 343 nodes took six wavefronts through ten barriers, each with a
-// few contractions between them, and 950 instructions a wavefront where this
-// form takes 3 x 1300 for the element.  A whole column of nodes a thread, one
+// residual and update): P = 3 17.1 -> 8.3 / 19.8 -> 17.3 us, P = 5 38.6 ->
+// 21.5 / 57.8 -> 45.3 us, P = 6 57.6 -> 27 / 112 -> 64 us (102 and 257
+// bytes a node, with neighbours' traces and fluxes from the caches: 5.3 / 5.6
+// TB/s), P = 8 124 -> 50 / 244 -> 137 us; 32^3 elements at P = 6 455 -> 222 /
+// 985 -> 530 us (5.1 / 5.4 TB/s; a large copy reaches 4.95).  The
+// kernels before were bound by latency: an element of 343 nodes took six
+// wavefronts through ten barriers, each with a few contractions between them,
+// and 950 instructions a wavefront where this form takes 3 x 1300 for the
+// element.  A whole column of nodes a thread, one
 // wavefront an element, was measured too: it needs 450 registers, so one
 // wavefront a SIMD, and nothing covers its loads (P = 6 37 / 87 us).
 #pragma once
@@ -231,8 +233,8 @@ __device__ __forceinline__ double strain_square(const double g[3][4]) {
 // LDS index of node (i, j, k) where PP is a power of two: rows and entries
 // permuted by the coordinates above them, so that the lines of each direction
 // spread over all banks (in node order, lines along x are PP entries apart).
-// 16^3 P=7: BR1 pass 47 -> 41 us, residual 127 -> 110, a step 511 -> 440;
-// 8^3 P=3: a step 29.0 -> 27.9.  Odd PP has no conflicts in node order, and
+// 16^3 P=7: BR1 pass 47 -> 41 us, residual 127 -> 110, a step of a long call
+// 511 -> 440; 8^3 P=3: 29.0 -> 27.9.  Odd PP has no conflicts in node order, and
 // PP = 6 a two-way one along x alone.
 template <int PP>
 __device__ __forceinline__ int lds_index(int i, int j, int k) {
@@ -446,7 +448,8 @@ __device__ __forceinline__ void nodes_to_traces(const Place<PP>& p, Tab B, const
 }
 
 // Wavefronts per SIMD that a stage kernel is compiled for: as many as its LDS
-// area lets share a CU (160 KB), at most four.
+// area lets share a CU (160 KB), at most three (four at P = 3, in 128
+// registers: spills, a 16^3 step 79 -> 90 us).
 template <class Lds, int NT>
 constexpr int line_waves() {
     constexpr int groups = (160 * 1024) / (Lds::N * 8);

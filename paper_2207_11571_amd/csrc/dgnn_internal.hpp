@@ -1,5 +1,6 @@
-// Internal declarations shared by the HIP kernels (kernels.hip) and the host
-// side of the library (api.cpp, server.cpp).  Not part of the public ABI.
+// Internal declarations shared by the HIP kernels (dg_kernels.hip,
+// nn_kernels.hip) and the host side of the library (api.cpp, nn_api.cpp,
+// server.cpp).  Not part of the public ABI.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -17,15 +18,16 @@ constexpr int kMaxHalf = (kMaxPP + 1) / 2;   // of them, up to and with the midd
 constexpr int kMaxLayers = 8;               // weight layers of the forcing network
 constexpr int kMaxDevices = 64;             // GPUs a process can build meshes on
 
-// Gauss-Legendre nodal basis of one order (Sec. 2.6).  D[i*PP + j] = l_j'(xi_i);
-// Dhat[i*PP + m] = D[m][i] w_m / w_i is the weak-form volume operator;
-// bpw = b+/w and bmw = b-/w lift interface values into the volume.
+// Gauss-Legendre nodal basis of one order (Sec. 2.6): nodes and quadrature
+// weights, and the operators along a line of nodes.
 struct BasisTab {
     double nodes[kMaxPP];
     double w[kMaxPP];
-    // The weak derivative Dhat[i][m] = D[m][i] w[m] / w[i], its lifting weights
-    // bpw[i] = bp[i] / w[i] and the end values' weights bp, split by parity about
-    // the middle of the line (the nodes are symmetric): with H = PP / 2 pairs, M = (PP + 1) / 2, mirrored index i' = P - i,
+    // With D[i][j] = l_j'(xi_i) and bp[j] = l_j(1): the weak derivative
+    // Dhat[i][m] = D[m][i] w[m] / w[i], the weights bpw[i] = bp[i] / w[i] that lift
+    // interface values into the line, and the end values' weights bp, split by
+    // parity about the middle of the line (the nodes are symmetric): with
+    // H = PP / 2 pairs, M = (PP + 1) / 2, mirrored index i' = P - i,
     //   nS[i*H + m] = -(Dhat[i][m] - Dhat[i][m']) / 2,  nT[i*M + m] = -(Dhat[i][m] + Dhat[i][m']) / 2
     // (-Dhat[i][m] at the middle m), lS[i] = (bpw[i] + bpw[i']) / 2, lT[i] = (bpw[i] - bpw[i']) / 2
     // (lS = bpw at the middle i), iE[m] = (bp[m] + bp[m']) / 2 (bp at the middle), iO[m] = (bp[m] - bp[m']) / 2

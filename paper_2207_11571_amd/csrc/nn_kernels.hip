@@ -221,15 +221,6 @@ __global__ void __launch_bounds__(kRowThreads) k_train_rows(NetArgs na, TrainArg
     }
 }
 
-// The same for networks with hidden layers of 256 (net256_steps), K0 steps of
-// input and nt column tiles of output.  Each wavefront owns the same column
-// tile of every hidden layer, forward and backward, and the lane that forms
-// rows 4 g .. 4 g + 3 of a column holds four consecutive batch entries of it,
-// so activations and output gradients go to their transposed arrays straight
-// from the epilogues, 8 bytes a lane, and the bias sums of a column are three
-// additions and a butterfly over its four lanes; only the input's transpose
-// goes through LDS.  Weights are loaded ahead as in net256_forward, the
-// targets before the output layer.
 // Touches every line of the weights that a row block reads after its input
 // layer, in that order, so that they are in the L2 of this block's XCD.  The
 // last step's update left them in other XCDs', and with few row blocks each
@@ -246,6 +237,15 @@ __device__ __forceinline__ void warm_weights(const NetArgs& na, int t) {
     asm volatile("" ::"v"(sum));
 }
 
+// k_train_rows for networks with hidden layers of 256 (net256_steps), K0 steps of
+// input and nt column tiles of output.  Each wavefront owns the same column
+// tile of every hidden layer, forward and backward, and the lane that forms
+// rows 4 g .. 4 g + 3 of a column holds four consecutive batch entries of it,
+// so activations and output gradients go to their transposed arrays straight
+// from the epilogues, 8 bytes a lane, and the bias sums of a column are three
+// additions and a butterfly over its four lanes; only the input's transpose
+// goes through LDS.  Weights are loaded ahead as in net256_forward, the
+// targets before the output layer.
 // What a block's first loads need is ahead of the structures: the first sixteen
 // words of a kernel's arguments are in scalar registers when it starts.
 template <int K0, int ACT>
