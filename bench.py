@@ -202,7 +202,7 @@ def serving_sample(B, torch, synthetic, n_req):
         fallbacks += st.fallback
         lat.append(st.latency_s)
         dofs += st.dof_updates
-    busy, batches = srv.stats()
+    busy, batches = srv.stats()   # batched steps, summed over the orders
     srv.close()
     return {"requests": len(reqs), "failed": failed, "fell_back_uncorrected": fallbacks,
             "p50_latency_s": percentile(lat, 50),

@@ -283,12 +283,15 @@ int nn_data_stats(const float* x, const float* y, int64_t rows, int32_t n_p, dou
 
 /* ----------------------------------------------------------------- serving */
 
-/* A continuous-batching server of Taylor-Green solves (one host thread and
- * one HIP stream of its own).  Solves are admitted by device footprint into
- * the caller's arena; the Runge-Kutta stages of all running solves of the
- * same order run in shared launches, so requests that arrive while others run
- * join them at the next step.  Each solve computes exactly what it would
- * compute alone (no cross-solve reductions).
+/* A continuous-batching server of Taylor-Green solves.  Solves are admitted by
+ * device footprint into the caller's arena; the Runge-Kutta stages of all
+ * running solves of the same order run in shared launches, so requests that
+ * arrive while others run join them at the order's next round of steps.  Each
+ * order has a host thread (from its first request on) and a HIP stream of its
+ * own, and runs beside the others; results are copied out by another thread
+ * on a further stream while the next round runs.  Nothing runs on the null
+ * stream.  Each solve computes exactly what it would compute alone (no
+ * cross-solve reductions).
  *
  * Fallback of the learned part: the uncorrected low-order evolution (Eq. (3),
  * the base method of Sec. 2.1) backs every corrected solve.  The server
@@ -319,7 +322,8 @@ enum { SOLVE_QUEUED = 0, SOLVE_RUNNING = 1, SOLVE_DONE = 2, SOLVE_FAILED = 3 };
 
 typedef struct solve_status {
     int32_t state;                  /* SOLVE_*                                     */
-    int32_t error;                  /* DG_* code when failed                       */
+    int32_t error;                  /* DG_* code when failed (DG_EHIP also for a
+                                       result that could not be copied out)        */
     int64_t steps, n_steps;         /* executed / total Runge-Kutta steps          */
     int32_t ke_count;               /* (t, KE) pairs written                       */
     int32_t fallback;               /* 1: a corrected solve continued uncorrected  */
@@ -332,6 +336,8 @@ typedef struct solve_status {
 
 /* Bytes a solve of order P on N^3 elements occupies in the arena. */
 size_t solve_footprint(int32_t P, int32_t N, int32_t use_nn);
+/* Makes the streams and the pinned host memory that the solves need beside the
+ * arena; DG_EHIP when they cannot be had. */
 int solve_server_create(void* arena, size_t arena_bytes, int32_t max_slots, solve_server** out);
 /* Thread-safe and non-blocking.  DG_ENOSPC at once when the request can never
  * fit the arena; otherwise queued until a slot and arena space are free. */
@@ -344,7 +350,10 @@ int solve_server_drain(solve_server* srv);
 /* Host-side test hook: on the next step boundary of request id, writes a NaN
  * into its state (exercises the non-finite detection of one solve). */
 int solve_inject_nan(solve_server* srv, uint64_t id);
-/* Totals: device-busy seconds (sum of step-batch wall times), launches. */
+/* Totals.  busy_s: wall seconds in which a round of at least one order was
+ * running, from its enqueueing to its end; batches: batched Runge-Kutta steps
+ * (a step of all solves of one order that take it together is one), summed
+ * over the orders. */
 int solve_server_stats(solve_server* srv, double* busy_s, int64_t* batches);
 void solve_server_free(solve_server* srv);
 
