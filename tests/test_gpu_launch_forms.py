@@ -40,8 +40,8 @@ def test_list_past_the_cache(B, P, sizes):
         m = B.Mesh(N, P, 200.0, Cs=0.1 if j else 0.0)
         q = m.field()
         B.dg_init_tgv(m, q)
-        # the others run longer than a round alone (16 steps) and the largest
-        steps = 20 if N == sizes[-1] else 150
+        # the others run much longer than it takes to submit the largest
+        steps = 20 if N == sizes[-1] else 600
         reqs.append((m, dict(Re=200.0, P=P, N=N, Cs=0.1 if j else 0.0, t_end=(steps - 0.5) * B.dg_stable_dt(m, q))))
     srv = B.Server(3 << 30, max_slots=8)
     ids = [srv.submit(want_state=True, **r) for _, r in reqs]

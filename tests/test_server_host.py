@@ -67,4 +67,7 @@ def test_threads_of_the_server_do_not_race(tmp_path_factory, scenario):
     exe = os.path.join(tmp_path_factory.getbasetemp(), "server_host_threads")
     if not os.path.exists(exe):
         _build(exe, "-g", "-fsanitize=thread")
-    _run(exe, scenario)
+    r = subprocess.run([exe, scenario], capture_output=True, text=True, timeout=100)
+    if "FATAL: ThreadSanitizer" in r.stderr:
+        pytest.skip("the thread sanitizer does not run on this kernel")
+    assert r.returncode == 0, r.stdout + r.stderr
